@@ -503,7 +503,7 @@ bh_status walk_until_fits(bh_ctx *c, hipStream_t s) {
     for (int attempt = 0;; ++attempt) {
         refresh_state(c);
         ev_begin(c, EV_WALK, s);
-        bhk::walk(c->d, s);
+        bhk::walk(c->d, c->n_groups, s);
         ev_end(c, EV_WALK, s);
         STCHK(read_counters(c, s));
         const DevCounters &h = *c->h_cnt;

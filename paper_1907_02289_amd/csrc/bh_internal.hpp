@@ -27,17 +27,15 @@ struct DevCounters {
     uint32_t lvl_off[BH_NLEVELS + 2];   // node-id range of each level
     uint32_t n_groups;
     uint32_t max_level;
-    unsigned long long pc_used;         // list-pool fill (may exceed capacity: overflow)
-    unsigned long long pp_used;
-    unsigned long long interactions;
     uint32_t walk_need_front;           // largest frontier seen
     uint32_t walk_need_list;            // longest list seen
-    uint32_t work_counter;              // persistent-kernel work queue head
-    uint32_t work_counter2;
+    uint32_t work_counter2;             // force kernel's work queue head
     uint32_t pad[4];
+    // the walk's totals, on cache lines of their own: their atomics go in parallel
+    alignas(128) unsigned long long pc_used;    // list-pool fill (may exceed capacity: overflow)
+    alignas(128) unsigned long long pp_used;
+    alignas(128) unsigned long long interactions;
     unsigned long long cand_used;       // learned rule: candidate pairs recorded (may exceed capacity)
-    uint32_t work_counter3;
-    uint32_t pad2;
     uint32_t stale[BH_NLEVELS];         // drift monitor: particles in drifted nodes, per level
 };
 
@@ -153,7 +151,7 @@ struct DevState {
     uint32_t node_cap;
     uint64_t *nd_prefix;
     uint32_t *nd_begin, *nd_count, *nd_first, *nd_meta;
-    int4 *nd_walk;                 // corner x | level << 24, corner y | n_child << 24, corner z, first child
+    int4 *nd_walk;                 // corner x | level << 24, corner y | n_child << 24, corner z, first child (a leaf: its particle count)
     double4 *nd_mom;               // com x, y, z, mass
     double *nd_quad;               // [node_cap][6] second moments (learned rule only), may be null
     uint32_t *tmp_a, *tmp_b;       // [node_cap] level scratch
@@ -234,7 +232,7 @@ void reset_flags(const DevState &d, hipStream_t s);
 void regroup(const DevState &d, hipStream_t s);   // group flags for d.n_grp on the current tree
 
 // lists (bh_walk.hip)
-void walk(const DevState &d, hipStream_t s);
+void walk(const DevState &d, uint32_t n_groups, hipStream_t s);
 void order_groups(const DevState &d, uint32_t n_groups, uint64_t *key_a, uint32_t *val_a, uint64_t *key_b,
                   uint32_t *val_b, hipStream_t s);
 

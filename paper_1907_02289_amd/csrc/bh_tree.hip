@@ -338,8 +338,10 @@ __global__ void k_node_finalize(DevState d) {
         uint64_t p = d.nd_prefix[v];
         int sh = BH_MAXLEVEL - (int)l;
         uint32_t cx = compact3(p >> 2) << sh, cy = compact3(p >> 1) << sh, cz = compact3(p) << sh;
-        d.nd_walk[v] = make_int4((int)(cx | (l << 24)), (int)(cy | (meta_nch(meta) << 24)), (int)cz,
-                                 (int)d.nd_first[v]);
+        // a leaf has no first child: its record carries the particle count for the walk
+        const uint32_t nch = meta_nch(meta);
+        d.nd_walk[v] = make_int4((int)(cx | (l << 24)), (int)(cy | (nch << 24)), (int)cz,
+                                 (int)(nch ? d.nd_first[v] : d.nd_count[v]));
     }
 }
 

@@ -142,10 +142,31 @@ __device__ __forceinline__ bool decide(const DevState &d, const GroupCtx &gc, ui
     return learned_accept(d.mlp, pg, mom.w, gc.amin, d.tau, d.G);
 }
 
+// Persistent blocks of four waves, one group per wave and round.  What
+// bounded an earlier form was neither the walk's memory traffic nor its
+// arithmetic but atomics on one cache line: each wave popped its groups from
+// a counter and reserved its list space with four more returning atomics per
+// group, and same-line atomics of the whole chip are served one per 12 ns
+// (measured: walk time / number of atomics = 11.6..12.4 ns from 172 to
+// 138,763 groups).  Now a wave's groups follow from its index (no counter),
+// the four waves of a block reserve list space together, the two pools with
+// one instruction on two cache lines (one atomic per pool and four groups),
+// and the interaction total is summed in registers and added once per block.
+// Blocks are dealt to the eight XCDs in turn, so each XCD takes one eighth of
+// the groups, contiguous along the curve: neighbouring groups open the same
+// nodes, which then stay in that XCD's L2.
+// The next 64 nodes are loaded before the current 64 are tested; a leaf's
+// particle count rides in the node record, so a visit is one 16-byte load.
+// Kernel time before and after: 172 groups (4096-particle ring) 105 -> 15 us,
+// 9,311 groups (200k, theta 0.2) 560 -> 81 us, 15,739 groups (2^20, theta 0.5)
+// 863 -> 100 us, 64 Plummer spheres 878 -> 230 us; with 60,426 groups of
+// 10^4-entry lists (2^24, theta 0.0865) the visits themselves take the time,
+// 5.2 -> 4.9 ms.
 template <bool GEO>
 __global__ void __launch_bounds__(WALK_TPB, (GEO ? 8 : 1)) k_walk(DevState d) {
-    const uint32_t wave = (blockIdx.x * WALK_TPB + threadIdx.x) >> 6;
-    if (wave >= d.walk_waves) return;
+    constexpr uint32_t WPB = WALK_TPB / 64;
+    const uint32_t wib = threadIdx.x >> 6;
+    const uint32_t wave = blockIdx.x * WPB + wib;
     const int lane = __lane_id();
     const uint64_t lt = lanemask_lt();
     const uint32_t F = d.walk_front_cap, P = d.walk_list_cap;
@@ -159,184 +180,189 @@ __global__ void __launch_bounds__(WALK_TPB, (GEO ? 8 : 1)) k_walk(DevState d) {
     // LDS, the rest at the same index in the wave's global scratch
     uint32_t *la = nullptr, *lb = nullptr;
     if constexpr (GEO) {
-        __shared__ uint32_t lfront[WALK_TPB / 64][2][WALK_LFRONT];
-        la = lfront[threadIdx.x >> 6][0];
-        lb = lfront[threadIdx.x >> 6][1];
+        __shared__ uint32_t lfront[WPB][2][WALK_LFRONT];
+        la = lfront[wib][0];
+        lb = lfront[wib][1];
     }
+    __shared__ uint32_t s_len[WPB][2];             // list lengths of the block's four groups
+    __shared__ unsigned long long s_at[2];         // the block's starts in the two pools
+    __shared__ unsigned long long s_cost[WPB];
+    unsigned long long cost_sum = 0;
 
-    for (;;) {
-        uint32_t g = 0;
-        if (lane == 0) g = atomicAdd(&d.cnt->work_counter, 1u);
-        g = __shfl(g, 0, 64);
-        if (g >= ng) break;
-        const GroupInfo gi = d.grp[g];
-        GroupCtx gc;
-        gc.glo = d.g_lo[g];
-        gc.ghi = d.g_hi[g];
-        if (!GEO && d.walk_mode != WALK_GEOMETRIC) {
-            gc.cen = d.g_cen[g];
-            gc.rad = d.g_rad[g];
-            gc.amin = d.walk_mode == WALK_LEARNED ? d.g_amin[g] : 0.0;
-            gc.Msys = d.nd_mom[gi.sys].w;
-            gc.S = (double)(1u << BH_MAXLEVEL) / d.box[gi.sys].w;
-        }
+    // the block's groups: every bx-th group of four in its XCD's eighth
+    const uint32_t xcd = blockIdx.x & 7u, bx = gridDim.x >> 3;        // gridDim.x is a multiple of 8
+    const uint32_t g_lo = (uint32_t)((unsigned long long)ng * xcd >> 3);
+    const uint32_t g_hi = (uint32_t)((unsigned long long)ng * (xcd + 1) >> 3);
+    for (uint32_t g0 = g_lo + (blockIdx.x >> 3) * WPB; g0 < g_hi; g0 += bx * WPB) {
+        const uint32_t g = g0 + wib;
+        const bool has = g < g_hi;
+        uint32_t npc = 0, npp = 0, n_part = 0;
+        unsigned long long pp_particles = 0;
+        bool skip = !has;       // no lists to store (no group, or its walk was cut short)
         // the enumerating walk visits only the sampled groups and stores no lists
         const bool enumerate = !GEO && d.walk_mode == WALK_ENUMERATE;
         const bool record = enumerate && (g % d.group_stride) == 0;
-        if (enumerate && !record) {
+        if (has && !(enumerate && !record)) {
+            const GroupInfo gi = d.grp[g];
+            n_part = gi.count;
+            GroupCtx gc;
+            gc.glo = d.g_lo[g];
+            gc.ghi = d.g_hi[g];
+            if (!GEO && d.walk_mode != WALK_GEOMETRIC) {
+                gc.cen = d.g_cen[g];
+                gc.rad = d.g_rad[g];
+                gc.amin = d.walk_mode == WALK_LEARNED ? d.g_amin[g] : 0.0;
+                gc.Msys = d.nd_mom[gi.sys].w;
+                gc.S = (double)(1u << BH_MAXLEVEL) / d.box[gi.sys].w;
+            }
+            uint32_t *cur = fa, *nxt = fb;
+            uint32_t *lcur = la, *lnxt = lb;
             if (lane == 0) {
-                d.g_pc_len[g] = 0;
-                d.g_pp_len[g] = 0;
-                d.g_cost[g] = 0;
+                if constexpr (GEO) lcur[0] = gi.sys;  // root of the group's system
+                else cur[0] = gi.sys;
             }
-            continue;
-        }
-        uint32_t *cur = fa, *nxt = fb;
-        uint32_t *lcur = la, *lnxt = lb;
-        if (lane == 0) {
-            if constexpr (GEO) lcur[0] = gi.sys;  // root of the group's system
-            else cur[0] = gi.sys;
-        }
-        __threadfence_block();
-        uint32_t ncur = 1, npc = 0, npp = 0;
-        unsigned long long pp_particles = 0;
-        unsigned long long pp_lane = 0;          // geometric walk: this lane's share, summed once per group
-        bool ovf = false, bound = false;
-        // A walk of a well-formed tree descends one level per frontier and
-        // visits every node at most once; a frontier beyond the deepest level
-        // or more visits than nodes can only come from a malformed tree, and
-        // ends the walk with a flag instead of running on.
-        uint32_t levels = 0;
-        unsigned long long visits = 0;
-        while (ncur > 0 && !ovf && !bound) {
-            visits += ncur;
-            if (++levels > (uint32_t)BH_NLEVELS || visits > (unsigned long long)n_nodes) {
-                bound = true;
-                break;
-            }
-            uint32_t nnext = 0;
-            for (uint32_t base = 0; base < ncur; base += 64) {
-                const uint32_t k = base + lane;
-                const bool valid = k < ncur;
-                uint32_t v;
-                if constexpr (GEO) v = valid ? (k < (uint32_t)WALK_LFRONT ? lcur[k] : cur[k]) : 0u;
-                else v = valid ? cur[k] : 0u;
-                int4 wr = valid ? d.nd_walk[v] : make_int4(0, 0, 0, 0);
-                const int nch = (int)((uint32_t)wr.y >> 24);
-                bool is_cand = false;
-                const bool acc = valid && decide<GEO>(d, gc, v, wr, &is_cand);
-                is_cand = is_cand && valid && record;
-                const uint64_t mc = __ballot(is_cand);
-                if (mc) {
-                    unsigned long long at = 0;
-                    if (lane == 0) at = atomicAdd(&d.cnt->cand_used, (unsigned long long)__popcll(mc));
-                    at = __shfl(at, 0, 64) + (unsigned long long)__popcll(mc & lt);
-                    if (is_cand && at < d.cand_cap) d.cand[at] = make_uint2(g, v);
+            __threadfence_block();
+            uint32_t ncur = 1;
+            unsigned long long pp_lane = 0;          // this lane's share, summed once per group
+            bool ovf = false, bound = false;
+            // A walk of a well-formed tree descends one level per frontier and
+            // visits every node at most once; a frontier beyond the deepest level
+            // or more visits than nodes can only come from a malformed tree, and
+            // ends the walk with a flag instead of running on.
+            uint32_t levels = 0;
+            unsigned long long visits = 0;
+            while (ncur > 0 && !ovf && !bound) {
+                visits += ncur;
+                if (++levels > (uint32_t)BH_NLEVELS || visits > (unsigned long long)n_nodes) {
+                    bound = true;
+                    break;
                 }
-                const bool is_pp = valid && !acc && nch == 0;
-                const uint32_t nopen = (valid && !acc && nch > 0) ? (uint32_t)nch : 0u;
+                uint32_t nnext = 0;
+                auto front = [&](uint32_t k) -> uint32_t {
+                    if constexpr (GEO) return k < (uint32_t)WALK_LFRONT ? lcur[k] : cur[k];
+                    else return cur[k];
+                };
+                uint32_t v_next = (uint32_t)lane < ncur ? front(lane) : 0u;
+                int4 wr_next = (uint32_t)lane < ncur ? d.nd_walk[v_next] : make_int4(0, 0, 0, 0);
+                for (uint32_t base = 0; base < ncur; base += 64) {
+                    const uint32_t k = base + lane;
+                    const bool valid = k < ncur;
+                    const uint32_t v = v_next;
+                    const int4 wr = wr_next;
+                    const uint32_t kn = k + 64;
+                    if (kn < ncur) {
+                        v_next = front(kn);
+                        wr_next = d.nd_walk[v_next];
+                    }
+                    const int nch = (int)((uint32_t)wr.y >> 24);
+                    bool is_cand = false;
+                    const bool acc = valid && decide<GEO>(d, gc, v, wr, &is_cand);
+                    if constexpr (!GEO) {
+                        is_cand = is_cand && valid && record;
+                        const uint64_t mc = __ballot(is_cand);
+                        if (mc) {
+                            unsigned long long at = 0;
+                            if (lane == 0) at = atomicAdd(&d.cnt->cand_used, (unsigned long long)__popcll(mc));
+                            at = __shfl(at, 0, 64) + (unsigned long long)__popcll(mc & lt);
+                            if (is_cand && at < d.cand_cap) d.cand[at] = make_uint2(g, v);
+                        }
+                    }
+                    const bool is_pp = valid && !acc && nch == 0;
+                    const uint32_t nopen = (valid && !acc && nch > 0) ? (uint32_t)nch : 0u;
 
-                const uint64_t mpc = __ballot(acc);
-                const uint64_t mpp = __ballot(is_pp);
-                uint32_t o, tot;
-                if constexpr (GEO) {
+                    const uint64_t mpc = __ballot(acc);
+                    const uint64_t mpp = __ballot(is_pp);
                     const uint32_t opc = npc + mbcnt(mpc);
                     const uint32_t opp = npp + mbcnt(mpp);
-                    if (acc && opc < P) pcb[opc] = v;
-                    if (is_pp && opp < P) ppb[opp] = v;
-                    if (is_pp) pp_lane += d.nd_count[v];
-                    npc += (uint32_t)__popcll(mpc);
-                    npp += (uint32_t)__popcll(mpp);
-                    o = nnext + wave_excl_small(nopen, tot);
-                } else {
-                    const uint32_t opc = npc + (uint32_t)__popcll(mpc & lt);
-                    const uint32_t opp = npp + (uint32_t)__popcll(mpp & lt);
                     if (acc && opc < P && !enumerate) pcb[opc] = v;
                     if (is_pp && opp < P && !enumerate) ppb[opp] = v;
-                    unsigned long long cnt_pp = is_pp ? (unsigned long long)d.nd_count[v] : 0ull;
-                    pp_particles += wave_sum(cnt_pp);
+                    if (is_pp) pp_lane += (uint32_t)wr.w;       // a leaf's record holds its particle count
                     npc += (uint32_t)__popcll(mpc);
                     npp += (uint32_t)__popcll(mpp);
-
-                    const uint32_t incl = wave_incl_scan(nopen);
-                    tot = __shfl(incl, 63, 64);
-                    o = nnext + incl - nopen;
+                    uint32_t tot;
+                    const uint32_t o = nnext + wave_excl_small(nopen, tot);
+                    for (uint32_t c = 0; c < nopen; ++c)
+                        if constexpr (GEO) {
+                            const uint32_t q = o + c;
+                            if (q < (uint32_t)WALK_LFRONT) lnxt[q] = (uint32_t)wr.w + c;
+                            else if (q < F) nxt[q] = (uint32_t)wr.w + c;
+                        } else if (o + c < F) {
+                            nxt[o + c] = (uint32_t)wr.w + c;
+                        }
+                    nnext += tot;
                 }
-                for (uint32_t c = 0; c < nopen; ++c)
-                    if constexpr (GEO) {
-                        const uint32_t q = o + c;
-                        if (q < (uint32_t)WALK_LFRONT) lnxt[q] = (uint32_t)wr.w + c;
-                        else if (q < F) nxt[q] = (uint32_t)wr.w + c;
-                    } else if (o + c < F) {
-                        nxt[o + c] = (uint32_t)wr.w + c;
-                    }
-                nnext += tot;
+                if (nnext > F || (!enumerate && (npc > P || npp > P))) ovf = true;
+                // the next frontier is read by other lanes of this wave than wrote it: LDS
+                // accesses of a wave complete in order; entries in global memory need the wait
+                if (!GEO || nnext > (uint32_t)WALK_LFRONT) __threadfence_block();
+                else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                uint32_t *t = cur; cur = nxt; nxt = t;
+                if constexpr (GEO) { t = lcur; lcur = lnxt; lnxt = t; }
+                ncur = nnext;
             }
-            if (nnext > F || (!enumerate && (npc > P || npp > P))) ovf = true;
-            __threadfence_block();
-            uint32_t *t = cur; cur = nxt; nxt = t;
-            if constexpr (GEO) { t = lcur; lcur = lnxt; lnxt = t; }
-            ncur = nnext;
-        }
-        if (bound) {
-            if (lane == 0) {
-                atomicOr(&d.cnt->flags[FLAG_WALK_BOUND], 1u);
-                d.g_pc_len[g] = 0;
-                d.g_pp_len[g] = 0;
-                d.g_cost[g] = 0;
+            if (bound) {
+                if (lane == 0) atomicOr(&d.cnt->flags[FLAG_WALK_BOUND], 1u);
+            } else if (ovf) {
+                if (lane == 0) {
+                    atomicOr(&d.cnt->flags[FLAG_WALK_OVF], 1u);
+                    atomicMax(&d.cnt->walk_need_front, ncur);
+                    if (!enumerate) atomicMax(&d.cnt->walk_need_list, max(npc, npp));
+                }
+            } else {
+                pp_particles = wave_sum(pp_lane);
             }
-            continue;
+            skip = bound || ovf || enumerate;
+        } else {
+            skip = true;
         }
-        if (ovf) {
-            if (lane == 0) {
-                atomicOr(&d.cnt->flags[FLAG_WALK_OVF], 1u);
-                atomicMax(&d.cnt->walk_need_front, ncur);
-                if (!enumerate) atomicMax(&d.cnt->walk_need_list, max(npc, npp));
-            }
-            d.g_pc_len[g] = 0;
-            d.g_pp_len[g] = 0;
-            d.g_cost[g] = 0;
-            continue;
-        }
-        if (enumerate) {
-            if (lane == 0) {
-                d.g_pc_len[g] = 0;
-                d.g_pp_len[g] = 0;
-                d.g_cost[g] = 0;
-            }
-            continue;
-        }
-        if constexpr (GEO) pp_particles = wave_sum(pp_lane);
-        unsigned long long at_pc = 0, at_pp = 0;
+        if (skip) npc = npp = 0;
         if (lane == 0) {
-            at_pc = atomicAdd(&d.cnt->pc_used, (unsigned long long)npc);
-            at_pp = atomicAdd(&d.cnt->pp_used, (unsigned long long)npp);
+            s_len[wib][0] = npc;
+            s_len[wib][1] = npp;
         }
-        at_pc = __shfl(at_pc, 0, 64);
-        at_pp = __shfl(at_pp, 0, 64);
-        const bool fit = (at_pc + npc <= d.pc_cap) && (at_pp + npp <= d.pp_cap);
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            unsigned long long sum = 0;
+            for (uint32_t k = 0; k < WPB; ++k) sum += s_len[k][threadIdx.x];
+            unsigned long long *head = threadIdx.x == 0 ? &d.cnt->pc_used : &d.cnt->pp_used;
+            s_at[threadIdx.x] = sum ? atomicAdd(head, sum) : 0ull;
+        }
+        __syncthreads();
+        unsigned long long at_pc = s_at[0], at_pp = s_at[1];
+        for (uint32_t k = 0; k < wib; ++k) {
+            at_pc += s_len[k][0];
+            at_pp += s_len[k][1];
+        }
+        const bool fit = !skip && (at_pc + npc <= d.pc_cap) && (at_pp + npp <= d.pp_cap);
         if (fit) {
+            __threadfence_block();              // the scratch lists, written by other lanes
             for (uint32_t k = lane; k < npc; k += 64) d.pc_pool[at_pc + k] = pcb[k];
             for (uint32_t k = lane; k < npp; k += 64) d.pp_pool[at_pp + k] = ppb[k];
-        } else if (lane == 0) {
+        } else if (lane == 0 && !skip) {
             atomicOr(&d.cnt->flags[FLAG_POOL_OVF], 1u);
         }
-        const unsigned long long cost = (unsigned long long)gi.count * (pp_particles + npc);
-        if (lane == 0) {
+        const unsigned long long cost = skip ? 0ull : (unsigned long long)n_part * (pp_particles + npc);
+        cost_sum += cost;
+        if (lane == 0 && has) {
             d.g_pc_off[g] = fit ? at_pc : 0ull;
             d.g_pc_len[g] = fit ? npc : 0u;
             d.g_pp_off[g] = fit ? at_pp : 0ull;
             d.g_pp_len[g] = fit ? npp : 0u;
             d.g_cost[g] = cost;
-            atomicAdd(&d.cnt->interactions, cost);
         }
-        __threadfence_block();
+        __syncthreads();                        // s_len and s_at are free for the next round
+    }
+    if (lane == 0) s_cost[wib] = cost_sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long sum = 0;
+        for (uint32_t k = 0; k < WPB; ++k) sum += s_cost[k];
+        if (sum) atomicAdd(&d.cnt->interactions, sum);
     }
 }
 
 __global__ void k_walk_reset(DevState d) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
-        d.cnt->work_counter = 0;
         d.cnt->pc_used = 0;
         d.cnt->pp_used = 0;
         d.cnt->interactions = 0;
@@ -372,10 +398,17 @@ __global__ void k_order_keys(DevState d, uint64_t *key, uint32_t *val) {
 
 namespace bhk {
 
-void walk(const DevState &d, hipStream_t s) {
+void walk(const DevState &d, uint32_t n_groups, hipStream_t s) {
     k_walk_reset<<<1, 64, 0, s>>>(d);
+    if (n_groups == 0) return;
+    // as many blocks as stay resident (and have scratch), fewer when there are
+    // fewer groups than waves; a multiple of 8, one share per XCD
     const uint32_t waves = d.walk_mode == WALK_GEOMETRIC ? d.walk_waves : d.walk_waves_net;
-    unsigned blocks = (waves * 64 + WALK_TPB - 1) / WALK_TPB;
+    constexpr uint32_t WPB = WALK_TPB / 64;
+    const uint32_t most = waves / WPB & ~7u;
+    const uint32_t want = ((n_groups + WPB - 1) / WPB + 7) & ~7u;
+    // each XCD's share of the groups may need one more block than the even split
+    const uint32_t blocks = want + 8 < most ? want + 8 : most;
     if (d.walk_mode == WALK_GEOMETRIC)
         k_walk<true><<<blocks, WALK_TPB, 0, s>>>(d);
     else
