@@ -15,10 +15,6 @@
 #include "bh.h"
 #include "bh_learned.hpp"
 
-namespace bhk {
-size_t mlp_act_floats(uint32_t B);
-}
-
 namespace {
 
 struct DevBuf {
@@ -95,8 +91,8 @@ struct bh_ctx {
         hipGraphExec_t exec = nullptr;
     };
     // learned opening rule
-    DevBuf nd_qn, amag, amag_in, g_amin, g_rad, cand, mlp_w, mlp_m, mlp_v, mlp_g, act;
-    DevBuf ds_x, ds_y, ds_pairs, pk_a, pk_b, pv_a, pv_b, phist, eval_out;
+    DevBuf nd_qn, amag, amag_in, g_amin, g_rad, cand, mlp_w, mlp_m, mlp_v, mlp_scratch;
+    DevBuf ds_x, ds_y, ds_pairs, pk_a, pk_b, pv_a, pv_b, phist;
     uint64_t cand_cap = 0, ds_n = 0, ds_cap = 0;
     int walk_mode = WALK_GEOMETRIC;
     uint32_t group_stride = 1, count_cap = 65536;
@@ -716,8 +712,8 @@ bh_status bh_destroy(bh_ctx *c) {
                      &c->g_pp_off, &c->g_pp_len, &c->g_cost, &c->order, &c->gkey_a, &c->gkey_b, &c->gval_a,
                      &c->gval_b, &c->pc_pool, &c->pp_pool, &c->walk_scratch, &c->counters, &c->direct_part,
                      &c->nd_qn, &c->amag, &c->amag_in, &c->g_amin, &c->g_rad, &c->cand, &c->mlp_w, &c->mlp_m,
-                     &c->mlp_v, &c->mlp_g, &c->act, &c->ds_x, &c->ds_y, &c->ds_pairs, &c->pk_a, &c->pk_b,
-                     &c->pv_a, &c->pv_b, &c->phist, &c->eval_out, &c->pos_b, &c->nd_mom_b, &c->nd_drift};
+                     &c->mlp_v, &c->mlp_scratch, &c->ds_x, &c->ds_y, &c->ds_pairs, &c->pk_a, &c->pk_b,
+                     &c->pv_a, &c->pv_b, &c->phist, &c->pos_b, &c->nd_mom_b, &c->nd_drift};
     for (DevBuf *b : all) release(*b);
     if (c->h_cnt) (void)hipHostFree(c->h_cnt);
     if (c->h_systab) (void)hipHostFree(c->h_systab);
@@ -1115,8 +1111,7 @@ void init_weights(float *w, uint64_t seed) {
 bh_status ensure_mlp_train_buffers(bh_ctx *c, uint32_t B, uint64_t n) {
     HIPCHK(c, grow(c->mlp_m, MLP_NTRAIN * 4));
     HIPCHK(c, grow(c->mlp_v, MLP_NTRAIN * 4));
-    HIPCHK(c, grow(c->mlp_g, (MLP_NTRAIN + 1) * 4));
-    HIPCHK(c, grow(c->act, bhk::mlp_act_floats(B) * 4));
+    HIPCHK(c, grow(c->mlp_scratch, bhk::mlp_scratch_bytes()));
     HIPCHK(c, grow(c->pk_a, std::max<uint64_t>(n, B) * 8));
     HIPCHK(c, grow(c->pk_b, std::max<uint64_t>(n, B) * 8));
     HIPCHK(c, grow(c->pv_a, std::max<uint64_t>(n, B) * 4));
@@ -1188,7 +1183,7 @@ bh_status bh_mlp_train(bh_ctx *c, const bh_train_opts *o, double *mse, void *str
         std::vector<float> h(BH_MLP_NPARAM);
         init_weights(h.data(), o->seed);
         HIPCHK(c, hipMemcpyAsync(w, h.data(), BH_MLP_NPARAM * 4, hipMemcpyHostToDevice, s));
-        bhk::mlp_stats(P<float4>(c->ds_x), P<float>(c->ds_y), n, w, s);
+        bhk::mlp_stats(P<float4>(c->ds_x), P<float>(c->ds_y), n, w, c->mlp_scratch.p, s);
         HIPCHK(c, hipMemsetAsync(c->mlp_m.p, 0, MLP_NTRAIN * 4, s));
         HIPCHK(c, hipMemsetAsync(c->mlp_v.p, 0, MLP_NTRAIN * 4, s));
         HIPCHK(c, hipStreamSynchronize(s));
@@ -1203,23 +1198,19 @@ bh_status bh_mlp_train(bh_ctx *c, const bh_train_opts *o, double *mse, void *str
                             (uint32_t)n, 0, 32, P<uint32_t>(c->phist), P<uint32_t>(c->scan_tmp), s, nullptr, 0);
         }
         const uint32_t *idx = P<uint32_t>(c->pv_a) + ((uint64_t)it % spe) * B;
-        bhk::mlp_batch_grad(w, P<float4>(c->ds_x), P<float>(c->ds_y), idx, B, P<float>(c->act), P<float>(c->mlp_g),
-                            nullptr, s);
-        bhk::mlp_adam(w, P<float>(c->mlp_g), P<float>(c->mlp_m), P<float>(c->mlp_v), o->lr, o->beta1, o->beta2,
-                      o->eps, ++c->adam_t, s);
+        const bhk::Adam ad{w, P<float>(c->mlp_m), P<float>(c->mlp_v), o->lr, o->beta1, o->beta2, o->eps, ++c->adam_t};
+        bhk::mlp_batch_grad(w, P<float4>(c->ds_x), P<float>(c->ds_y), idx, B, c->mlp_scratch.p, nullptr, nullptr, &ad,
+                            s);
     }
     HIPCHK(c, hipGetLastError());
     c->mlp_ready = true;
     c->lists_valid = false;
     if (mse) {
-        HIPCHK(c, grow(c->eval_out, n * 4));
-        bhk::mlp_eval(w, P<float4>(c->ds_x), n, P<float>(c->eval_out), s);
-        std::vector<float> pr(n), y(n);
-        HIPCHK(c, hipMemcpyAsync(pr.data(), c->eval_out.p, n * 4, hipMemcpyDeviceToHost, s));
-        HIPCHK(c, hipMemcpyAsync(y.data(), c->ds_y.p, n * 4, hipMemcpyDeviceToHost, s));
+        const double *part = bhk::mlp_sq_error(w, P<float4>(c->ds_x), P<float>(c->ds_y), n, c->mlp_scratch.p, s);
+        double h[bhk::MSE_BLOCKS], acc = 0;
+        HIPCHK(c, hipMemcpyAsync(h, part, sizeof h, hipMemcpyDeviceToHost, s));
         HIPCHK(c, hipStreamSynchronize(s));
-        double acc = 0;
-        for (uint64_t k = 0; k < n; ++k) acc += ((double)pr[k] - y[k]) * ((double)pr[k] - y[k]);
+        for (double v : h) acc += v;
         *mse = acc / (double)n;
     }
     return BH_OK;
@@ -1250,8 +1241,9 @@ bh_status bh_mlp_adam(bh_ctx *c, const float *grad, float lr, float beta1, float
         return fail(c, BH_EINVAL, "bh_mlp_adam: bad arguments");
     if (!c->mlp_ready || !c->mlp_m.p || !c->mlp_v.p)
         return fail(c, BH_ESTATE, "bh_mlp_adam: no weights (bh_mlp_train or bh_mlp_weights)");
-    bhk::mlp_adam(P<float>(c->mlp_w), grad, P<float>(c->mlp_m), P<float>(c->mlp_v), lr, beta1, beta2, eps,
-                  ++c->adam_t, (hipStream_t)stream);
+    bhk::mlp_adam(bhk::Adam{P<float>(c->mlp_w), P<float>(c->mlp_m), P<float>(c->mlp_v), lr, beta1, beta2, eps,
+                            ++c->adam_t},
+                  grad, (hipStream_t)stream);
     c->lists_valid = false;
     HIPCHK(c, hipGetLastError());
     return BH_OK;
@@ -1312,10 +1304,9 @@ bh_status bh_mlp_gradient(bh_ctx *c, const float *x, const float *y, int32_t B, 
     if (!c || !x || !y || !grad || B < 1 || B > 65536) return BH_EINVAL;
     if (!c->mlp_ready) return fail(c, BH_ESTATE, "bh_mlp_gradient: no weights (bh_mlp_train or bh_mlp_weights)");
     hipStream_t s = (hipStream_t)stream;
-    STCHK(ensure_mlp_train_buffers(c, (uint32_t)B, (uint64_t)B));
-    bhk::perm_keys(P<uint64_t>(c->pk_a), P<uint32_t>(c->pv_a), (uint64_t)B, 0, s);   // identity order
-    bhk::mlp_batch_grad(P<float>(c->mlp_w), reinterpret_cast<const float4 *>(x), y, P<uint32_t>(c->pv_a),
-                        (uint32_t)B, P<float>(c->act), grad, loss, s);
+    HIPCHK(c, grow(c->mlp_scratch, bhk::mlp_scratch_bytes()));
+    bhk::mlp_batch_grad(P<float>(c->mlp_w), reinterpret_cast<const float4 *>(x), y, nullptr, (uint32_t)B,
+                        c->mlp_scratch.p, grad, loss, nullptr, s);
     HIPCHK(c, hipGetLastError());
     return BH_OK;
 }

@@ -256,11 +256,23 @@ void sample_acc(const DevState &d, int sys, const int64_t *targets, int64_t nt, 
 void node_qn(const DevState &d, hipStream_t s);
 void group_amin(const DevState &d, hipStream_t s);
 void cand_features_labels(const DevState &d, uint64_t n_cand, float4 *X, float *Y, hipStream_t s);
-void mlp_stats(const float4 *X, const float *Y, uint64_t n, float *w, hipStream_t s);
-void mlp_batch_grad(const float *w, const float4 *X, const float *Y, const uint32_t *idx, uint32_t B,
-                    float *act, float *grad, float *loss, hipStream_t s);
-void mlp_adam(float *w, const float *grad, float *m, float *v, float lr, float b1, float b2, float eps,
-              int step, hipStream_t s);
+// network training: scratch of mlp_scratch_bytes() for each call below that takes one
+struct Adam {
+    float *w, *m, *v;
+    float lr, b1, b2, eps;
+    int step;                      // 1-based
+};
+constexpr int MSE_BLOCKS = 512;
+size_t mlp_scratch_bytes();
+void mlp_stats(const float4 *X, const float *Y, uint64_t n, float *w, void *scratch, hipStream_t s);
+// Gradient of a batch (rows idx[0..B), or 0..B when idx is null) into grad and
+// the loss into loss (may be null); adam != null: no outputs, the weights take
+// the optimiser's step instead.
+void mlp_batch_grad(const float *w, const float4 *X, const float *Y, const uint32_t *idx, uint32_t B, void *scratch,
+                    float *grad, float *loss, const Adam *adam, hipStream_t s);
+void mlp_adam(const Adam &a, const float *grad, hipStream_t s);
+// MSE_BLOCKS partial sums (device) of the squared error over the set
+const double *mlp_sq_error(const float *w, const float4 *X, const float *Y, uint64_t n, void *scratch, hipStream_t s);
 void mlp_eval(const float *w, const float4 *X, uint64_t n, float *out, hipStream_t s);
 void perm_keys(uint64_t *key, uint32_t *val, uint64_t n, uint64_t seed, hipStream_t s);
 

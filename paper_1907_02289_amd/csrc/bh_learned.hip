@@ -124,147 +124,269 @@ __global__ void __launch_bounds__(TPB) k_cand(DevState d, uint64_t n_cand, float
 }
 
 // ---------------------------------------------------------------- training
-// Normalisation: mean and 1/std of each feature and of the label, summed in
-// FP64 by one workgroup in a fixed order.
-__global__ void __launch_bounds__(TPB) k_stats(const float4 *X, const float *Y, uint64_t n, float *w) {
-    __shared__ double part[TPB][10];
-    double s[5] = {0, 0, 0, 0, 0}, q[5] = {0, 0, 0, 0, 0};
-    for (uint64_t i = threadIdx.x; i < n; i += TPB) {
+// Normalisation: mean and 1/std of each feature and of the label.  Sums in
+// FP64 in a fixed order: STAT_BLOCKS blocks over the rows, then one block over
+// their partial sums (one block alone took 543 us for 300,000 rows, a chain of
+// 1,200 dependent loads per thread; in two launches 12 us).
+constexpr int STAT_BLOCKS = 256;
+
+__global__ void __launch_bounds__(TPB) k_stats_part(const float4 *X, const float *Y, uint64_t n, double *part) {
+    __shared__ double red[TPB / 64][10];
+    double s[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    for (uint64_t i = (uint64_t)blockIdx.x * TPB + threadIdx.x; i < n; i += (uint64_t)STAT_BLOCKS * TPB) {
         const float4 x = X[i];
         const double v[5] = {x.x, x.y, x.z, x.w, Y[i]};
+#pragma unroll
         for (int k = 0; k < 5; ++k) {
             s[k] += v[k];
-            q[k] += v[k] * v[k];
+            s[5 + k] += v[k] * v[k];
         }
     }
-    for (int k = 0; k < 5; ++k) {
-        part[threadIdx.x][k] = s[k];
-        part[threadIdx.x][5 + k] = q[k];
+#pragma unroll
+    for (int k = 0; k < 10; ++k) {
+        const double t = wave_sum(s[k]);
+        if (__lane_id() == 0) red[threadIdx.x >> 6][k] = t;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double S[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-        for (int t = 0; t < TPB; ++t)
-            for (int k = 0; k < 10; ++k) S[k] += part[t][k];
-        for (int k = 0; k < 5; ++k) {
-            const double mean = S[k] / (double)n;
-            double var = S[5 + k] / (double)n - mean * mean;
-            const double sd = var > 1e-24 ? sqrt(var) : 1.0;
-            if (k < 4) {
-                w[MLP_XMEAN + k] = (float)mean;
-                w[MLP_XISTD + k] = (float)(1.0 / sd);
-            } else {
-                w[MLP_YMEAN] = (float)mean;
-                w[MLP_YSTD] = (float)sd;
-            }
+    if (threadIdx.x < 10) {
+        double t = 0;
+        for (int w = 0; w < TPB / 64; ++w) t += red[w][threadIdx.x];
+        part[blockIdx.x * 10 + threadIdx.x] = t;
+    }
+}
+
+__global__ void __launch_bounds__(TPB) k_stats_final(const double *part, uint64_t n, float *w) {
+    __shared__ double red[TPB / 64][10];
+    static_assert(STAT_BLOCKS == TPB, "one partial per thread");
+#pragma unroll
+    for (int k = 0; k < 10; ++k) {
+        const double t = wave_sum(part[threadIdx.x * 10 + k]);
+        if (__lane_id() == 0) red[threadIdx.x >> 6][k] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < 5) {
+        const int k = threadIdx.x;
+        double S = 0, Q = 0;
+        for (int v = 0; v < TPB / 64; ++v) {
+            S += red[v][k];
+            Q += red[v][5 + k];
+        }
+        const double mean = S / (double)n;
+        double var = Q / (double)n - mean * mean;
+        const double sd = var > 1e-24 ? sqrt(var) : 1.0;
+        if (k < 4) {
+            w[MLP_XMEAN + k] = (float)mean;
+            w[MLP_XISTD + k] = (float)(1.0 / sd);
+        } else {
+            w[MLP_YMEAN] = (float)mean;
+            w[MLP_YSTD] = (float)sd;
         }
     }
 }
 
-// Activations per sample of a batch: x (4), h1 (32), h2 (32), g1 (32) and g2 (32)
-// the loss gradients at the two hidden pre-activations, go (1) at the output.
-#define ACT_X 0
-#define ACT_H1 4
-#define ACT_H2 36
-#define ACT_G2 68
-#define ACT_G1 100
-#define ACT_GO 132
-#define ACT_N 133
+// Gradient of a batch.  An earlier form wrote each sample's activations to
+// memory and gave each of the 1249 parameters one thread that read them all
+// in turn: 963 us for 4096 samples, a serial chain of 4096 dependent
+// multiply-adds on 20 wavefronts.  Here a block takes 64 samples at a time
+// through forward, backward and the sum over its samples without leaving the
+// CU: one sample per lane, an eighth of each hidden layer's units per wave
+// and half, activations in LDS (rows of 65 floats: lanes of one row and rows
+// of one lane both fall in distinct banks).  The 32 x 32 gradient of the
+// second layer is a contraction over samples and runs on the matrix cores
+// (v_mfma_f32_32x32x2_f32, FP32 products and sums, 16 samples per wave), the
+// other 225 sums take a thread each.  At most GRAD_BLOCKS blocks, so that
+// k_grad_final reads at most that many partial sums per parameter.
+// Forward and backward of a sample round exactly as the one-thread form did.
+// 4096 samples: 969 + 30 us before (gradient sums, forward and backward), 12 + 3.4 us now;
+// 100 training steps of 4096 rows 101.3 -> 1.85 ms.
+constexpr int GS = 64;              // samples per block and round
+constexpr int GLD = GS + 1;         // LDS row of one unit over the samples
+constexpr int GRAD_BLOCKS = 256;
 
-__global__ void __launch_bounds__(TPB) k_fwd_bwd(const float *__restrict__ w, const float4 *X, const float *Y,
-                                                const uint32_t *idx, uint32_t B, float *act, float *lossv) {
-    const uint32_t b = blockIdx.x * TPB + threadIdx.x;
-    if (b >= B) return;
-    const uint32_t i = idx[b];
-    const float4 xx = X[i];
-    const float f[4] = {xx.x, xx.y, xx.z, xx.w};
-    float x[4];
-    for (int k = 0; k < 4; ++k) {
-        const float t = f[k] - w[MLP_XMEAN + k];
-        x[k] = t * w[MLP_XISTD + k];
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+__global__ void __launch_bounds__(TPB) k_grad_part(const float *__restrict__ w, const float4 *X, const float *Y,
+                                                  const uint32_t *idx, uint32_t B, float *part, double *lossp) {
+    __shared__ float xs[4][GLD], h1[MLP_NH][GLD], h2[MLP_NH][GLD], g1[MLP_NH][GLD], g2[MLP_NH][GLD], gos[GS];
+    __shared__ float red[4][MLP_NH * MLP_NH];
+    const int lane = __lane_id();
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int U = MLP_NH / 4;   // units of a layer per wave
+    const int u0 = wv * U;
+    // this thread's share of the 225 sums outside W2: operand rows a * b (b null: a alone)
+    const int t = threadIdx.x;
+    const float *ra = gos, *rb = nullptr;
+    int dst = -1;
+    if (t < 128) {
+        dst = MLP_W1 + t;
+        ra = g1[t >> 2];
+        rb = xs[t & 3];
+    } else if (t < 160) {
+        dst = MLP_B1 + (t - 128);
+        ra = g1[t - 128];
+    } else if (t < 192) {
+        dst = MLP_B2 + (t - 160);
+        ra = g2[t - 160];
+    } else if (t < 224) {
+        dst = MLP_W3 + (t - 192);
+        rb = h2[t - 192];
+    } else if (t == 224) {
+        dst = MLP_B3;
     }
-    float h1[MLP_NH], h2[MLP_NH];
-    for (int j = 0; j < MLP_NH; ++j) {
-        float a = w[MLP_B1 + j];
-        for (int k = 0; k < 4; ++k) a = fmaf(w[MLP_W1 + j * 4 + k], x[k], a);
-        h1[j] = a > 0.0f ? a : 0.0f;
+    float sum = 0.0f;
+    double loss = 0.0;
+    floatx16 acc = {};
+    const uint32_t rounds = (B + GS - 1) / GS;
+    for (uint32_t c = blockIdx.x; c < rounds; c += gridDim.x) {
+        const uint32_t b = c * GS + lane;
+        const bool valid = b < B;
+        const uint32_t i = valid ? (idx ? idx[b] : b) : 0u;
+        const float4 xx = X[i];
+        const float f[4] = {xx.x, xx.y, xx.z, xx.w};
+        float x[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float tt = f[k] - w[MLP_XMEAN + k];
+            x[k] = valid ? tt * w[MLP_XISTD + k] : 0.0f;        // lanes past the batch add exact zeros
+            if (wv == 0) xs[k][lane] = x[k];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float a = w[MLP_B1 + u0 + u];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) a = fmaf(w[MLP_W1 + (u0 + u) * 4 + k], x[k], a);
+            h1[u0 + u][lane] = a > 0.0f ? a : 0.0f;
+        }
+        __syncthreads();
+        float a2[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) a2[u] = w[MLP_B2 + u0 + u];
+#pragma unroll 4
+        for (int k = 0; k < MLP_NH; ++k) {
+            const float hk = h1[k][lane];
+#pragma unroll
+            for (int u = 0; u < U; ++u) a2[u] = fmaf(w[MLP_W2 + (u0 + u) * MLP_NH + k], hk, a2[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            a2[u] = a2[u] > 0.0f ? a2[u] : 0.0f;
+            h2[u0 + u][lane] = a2[u];
+        }
+        __syncthreads();
+        float out = w[MLP_B3];
+#pragma unroll 8
+        for (int j = 0; j < MLP_NH; ++j) out = fmaf(w[MLP_W3 + j], h2[j][lane], out);
+        // loss on the normalised label: (out - (y - mean) / sd)^2, averaged over the batch
+        const float yt = (Y[i] - w[MLP_YMEAN]) / w[MLP_YSTD];
+        const float r = out - yt;
+        const float go = valid ? 2.0f * r / (float)B : 0.0f;
+        if (wv == 0) {
+            gos[lane] = go;
+            const float r2 = r * r;
+            if (valid) loss += (double)r2;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) g2[u0 + u][lane] = a2[u] > 0.0f ? go * w[MLP_W3 + u0 + u] : 0.0f;
+        __syncthreads();
+        float gk[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) gk[u] = 0.0f;
+#pragma unroll 4
+        for (int j = 0; j < MLP_NH; ++j) {
+            const float gj = g2[j][lane];
+#pragma unroll
+            for (int u = 0; u < U; ++u) gk[u] = fmaf(w[MLP_W2 + j * MLP_NH + u0 + u], gj, gk[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) g1[u0 + u][lane] = h1[u0 + u][lane] > 0.0f ? gk[u] : 0.0f;
+        __syncthreads();
+        // W2: sum over this wave's 16 samples, two per instruction
+#pragma unroll
+        for (int st = 0; st < GS / 8; ++st) {
+            const int sm = 16 * wv + 2 * st + (lane >> 5);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(g2[lane & 31][sm], h1[lane & 31][sm], acc, 0, 0, 0);
+        }
+        if (dst >= 0) {
+#pragma unroll 8
+            for (int sm = 0; sm < GS; ++sm) sum = rb ? fmaf(ra[sm], rb[sm], sum) : sum + ra[sm];
+        }
+        __syncthreads();
     }
-    float out = w[MLP_B3];
-    for (int j = 0; j < MLP_NH; ++j) {
-        float a = w[MLP_B2 + j];
-        for (int k = 0; k < MLP_NH; ++k) a = fmaf(w[MLP_W2 + j * MLP_NH + k], h1[k], a);
-        h2[j] = a > 0.0f ? a : 0.0f;
-        out = fmaf(w[MLP_W3 + j], h2[j], out);
+    // matrix layout: element r of a lane is row 8 (r / 4) + r % 4 + 4 (lane / 32), column lane % 32
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[wv][(8 * (r >> 2) + (r & 3) + 4 * (lane >> 5)) * MLP_NH + (lane & 31)] = acc[r];
+    __syncthreads();
+    float *o = part + (size_t)blockIdx.x * MLP_NTRAIN;
+    for (int e = t; e < MLP_NH * MLP_NH; e += TPB) o[MLP_W2 + e] = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
+    if (dst >= 0) o[dst] = sum;
+    if (wv == 0) {
+        loss = wave_sum(loss);
+        if (lane == 0) lossp[blockIdx.x] = loss;
     }
-    // loss on the normalised label: (out - (y - mean) / sd)^2, averaged over the batch
-    const float yt = (Y[i] - w[MLP_YMEAN]) / w[MLP_YSTD];
-    const float r = out - yt;
-    const float go = 2.0f * r / (float)B;
-    float *a = act + (size_t)b * ACT_N;
-    for (int k = 0; k < 4; ++k) a[ACT_X + k] = x[k];
-    for (int j = 0; j < MLP_NH; ++j) {
-        a[ACT_H1 + j] = h1[j];
-        a[ACT_H2 + j] = h2[j];
-        a[ACT_G2 + j] = h2[j] > 0.0f ? go * w[MLP_W3 + j] : 0.0f;
-    }
-    for (int k = 0; k < MLP_NH; ++k) {
-        float g = 0.0f;
-        if (h1[k] > 0.0f)
-            for (int j = 0; j < MLP_NH; ++j) g = fmaf(w[MLP_W2 + j * MLP_NH + k], a[ACT_G2 + j], g);
-        a[ACT_G1 + k] = g;
-    }
-    a[ACT_GO] = go;
-    lossv[b] = r * r;
 }
 
-// One thread per trained parameter: its gradient summed over the batch in order.
-__global__ void k_param_grad(const float *act, uint32_t B, float *grad, const float *lossv, float *loss) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p == MLP_NTRAIN && loss) {
-        double s = 0;
-        for (uint32_t b = 0; b < B; ++b) s += lossv[b];
-        *loss = (float)(s / B);
-    }
-    if (p >= MLP_NTRAIN) return;
-    int src_g, src_a;      // gradient = sum_b act[g] * act[a]   (src_a < 0: act[g] alone)
-    if (p < MLP_B1) {
-        src_g = ACT_G1 + p / 4;
-        src_a = ACT_X + p % 4;
-    } else if (p < MLP_W2) {
-        src_g = ACT_G1 + (p - MLP_B1);
-        src_a = -1;
-    } else if (p < MLP_B2) {
-        const int q = p - MLP_W2;
-        src_g = ACT_G2 + q / MLP_NH;
-        src_a = ACT_H1 + q % MLP_NH;
-    } else if (p < MLP_W3) {
-        src_g = ACT_G2 + (p - MLP_B2);
-        src_a = -1;
-    } else if (p < MLP_B3) {
-        src_g = ACT_GO;
-        src_a = ACT_H2 + (p - MLP_W3);
-    } else {
-        src_g = ACT_GO;
-        src_a = -1;
-    }
+// Adam step of one parameter (Kingma & Ba 2015); c1, c2 = 1 - beta^t.
+struct AdamArgs {
+    float *w, *m, *v;
+    float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ void adam_step(const AdamArgs &a, int p, float gp) {
+    const float mp = a.b1 * a.m[p] + (1.0f - a.b1) * gp;
+    const float vp = a.b2 * a.v[p] + (1.0f - a.b2) * gp * gp;
+    a.m[p] = mp;
+    a.v[p] = vp;
+    a.w[p] -= a.lr * (mp / a.c1) / (sqrtf(vp / a.c2) + a.eps);
+}
+
+// The blocks' partial sums added in a fixed order, four threads per
+// parameter; ADAM: the parameter's optimiser step in the same launch.
+template <bool ADAM>
+__global__ void __launch_bounds__(TPB) k_grad_final(const float *part, const double *lossp, int nb, uint32_t B,
+                                                   float *grad, float *loss, AdamArgs ad) {
+    __shared__ float red[4][64];
+    const int q = threadIdx.x >> 6, lane = __lane_id();
+    const int p = blockIdx.x * 64 + lane;
     float s = 0.0f;
-    for (uint32_t b = 0; b < B; ++b) {
-        const float *a = act + (size_t)b * ACT_N;
-        s = (src_a < 0) ? s + a[src_g] : fmaf(a[src_g], a[src_a], s);
+    if (p < MLP_NTRAIN) {
+#pragma unroll 8
+        for (int b = q; b < nb; b += 4) s += part[(size_t)b * MLP_NTRAIN + p];
     }
-    grad[p] = s;
+    red[q][lane] = s;
+    __syncthreads();
+    if (q == 0 && p < MLP_NTRAIN) {
+        const float g = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+        if (ADAM) adam_step(ad, p, g);
+        else grad[p] = g;
+    }
+    if (q == 1 && loss && blockIdx.x == 0) {
+        double l = 0.0;
+        for (int b = lane; b < nb; b += 64) l += lossp[b];
+        l = wave_sum(l);
+        if (lane == 0) *loss = (float)(l / B);
+    }
 }
 
-__global__ void k_adam(float *w, const float *g, float *m, float *v, float lr, float b1, float b2, float eps,
-                       float c1, float c2) {
+__global__ void k_adam(AdamArgs ad, const float *g) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= MLP_NTRAIN) return;
-    const float gp = g[p];
-    const float mp = b1 * m[p] + (1.0f - b1) * gp;
-    const float vp = b2 * v[p] + (1.0f - b2) * gp * gp;
-    m[p] = mp;
-    v[p] = vp;
-    w[p] -= lr * (mp / c1) / (sqrtf(vp / c2) + eps);
+    if (p < MLP_NTRAIN) adam_step(ad, p, g[p]);
+}
+
+// Squared error of the network over a set, summed in FP64: per block, in a fixed order.
+__global__ void __launch_bounds__(TPB) k_sq_error(const float *__restrict__ w, const float4 *X, const float *Y,
+                                                 uint64_t n, double *part) {
+    __shared__ double red[TPB / 64];
+    double s = 0.0;
+    for (uint64_t i = (uint64_t)blockIdx.x * TPB + threadIdx.x; i < n; i += (uint64_t)gridDim.x * TPB) {
+        const float4 x = X[i];
+        const float f[4] = {x.x, x.y, x.z, x.w};
+        const double e = (double)mlp_forward(w, f) - (double)Y[i];
+        s += e * e;
+    }
+    s = wave_sum(s);
+    if (__lane_id() == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) part[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
 __global__ void k_eval(const float *__restrict__ w, const float4 *X, uint64_t n, float *out) {
@@ -306,20 +428,53 @@ void cand_features_labels(const DevState &d, uint64_t n_cand, float4 *X, float *
     k_cand<<<blocks, TPB, 0, s>>>(d, n_cand, X, Y);
 }
 
-void mlp_stats(const float4 *X, const float *Y, uint64_t n, float *w, hipStream_t s) {
-    k_stats<<<1, TPB, 0, s>>>(X, Y, n, w);
+// Scratch of the training kernels: partial sums of the batch gradient and
+// loss (GRAD_BLOCKS), of the normalisation and of the squared error.
+size_t mlp_scratch_bytes() {
+    return (size_t)GRAD_BLOCKS * (MLP_NTRAIN * sizeof(float) + sizeof(double)) +
+           (size_t)STAT_BLOCKS * 10 * sizeof(double) + MSE_BLOCKS * sizeof(double);
 }
 
-void mlp_batch_grad(const float *w, const float4 *X, const float *Y, const uint32_t *idx, uint32_t B,
-                    float *act, float *grad, float *loss, hipStream_t s) {
-    k_fwd_bwd<<<(B + TPB - 1) / TPB, TPB, 0, s>>>(w, X, Y, idx, B, act, act + (size_t)B * ACT_N);
-    k_param_grad<<<(MLP_NTRAIN + 1 + 63) / 64, 64, 0, s>>>(act, B, grad, act + (size_t)B * ACT_N, loss);
+namespace {
+struct Scratch {
+    double *loss, *stat, *mse;
+    float *part;
+    explicit Scratch(void *p)
+        : loss((double *)p), stat(loss + GRAD_BLOCKS), mse(stat + STAT_BLOCKS * 10), part((float *)(mse + MSE_BLOCKS)) {}
+};
+AdamArgs adam_args(const Adam &a) {
+    return AdamArgs{a.w, a.m, a.v, a.lr, a.b1, a.b2, a.eps, 1.0f - powf(a.b1, (float)a.step),
+                    1.0f - powf(a.b2, (float)a.step)};
+}
+}  // namespace
+
+void mlp_stats(const float4 *X, const float *Y, uint64_t n, float *w, void *scratch, hipStream_t s) {
+    const Scratch sc(scratch);
+    k_stats_part<<<STAT_BLOCKS, TPB, 0, s>>>(X, Y, n, sc.stat);
+    k_stats_final<<<1, TPB, 0, s>>>(sc.stat, n, w);
 }
 
-void mlp_adam(float *w, const float *grad, float *m, float *v, float lr, float b1, float b2, float eps, int step,
-              hipStream_t s) {
-    const float c1 = 1.0f - powf(b1, (float)step), c2 = 1.0f - powf(b2, (float)step);
-    k_adam<<<(MLP_NTRAIN + 255) / 256, 256, 0, s>>>(w, grad, m, v, lr, b1, b2, eps, c1, c2);
+void mlp_batch_grad(const float *w, const float4 *X, const float *Y, const uint32_t *idx, uint32_t B, void *scratch,
+                    float *grad, float *loss, const Adam *adam, hipStream_t s) {
+    const Scratch sc(scratch);
+    const uint32_t rounds = (B + GS - 1) / GS;
+    const int nb = (int)(rounds < (uint32_t)GRAD_BLOCKS ? rounds : (uint32_t)GRAD_BLOCKS);
+    k_grad_part<<<nb, TPB, 0, s>>>(w, X, Y, idx, B, sc.part, sc.loss);
+    const unsigned blocks = (MLP_NTRAIN + 63) / 64;
+    if (adam)
+        k_grad_final<true><<<blocks, TPB, 0, s>>>(sc.part, sc.loss, nb, B, nullptr, nullptr, adam_args(*adam));
+    else
+        k_grad_final<false><<<blocks, TPB, 0, s>>>(sc.part, sc.loss, nb, B, grad, loss, AdamArgs{});
+}
+
+void mlp_adam(const Adam &a, const float *grad, hipStream_t s) {
+    k_adam<<<(MLP_NTRAIN + 255) / 256, 256, 0, s>>>(adam_args(a), grad);
+}
+
+const double *mlp_sq_error(const float *w, const float4 *X, const float *Y, uint64_t n, void *scratch, hipStream_t s) {
+    const Scratch sc(scratch);
+    k_sq_error<<<MSE_BLOCKS, TPB, 0, s>>>(w, X, Y, n, sc.mse);
+    return sc.mse;
 }
 
 void mlp_eval(const float *w, const float4 *X, uint64_t n, float *out, hipStream_t s) {
@@ -330,7 +485,5 @@ void mlp_eval(const float *w, const float4 *X, uint64_t n, float *out, hipStream
 void perm_keys(uint64_t *key, uint32_t *val, uint64_t n, uint64_t seed, hipStream_t s) {
     k_perm_keys<<<grid_for(n), TPB, 0, s>>>(key, val, n, seed);
 }
-
-size_t mlp_act_floats(uint32_t B) { return (size_t)B * (ACT_N + 1); }
 
 }  // namespace bhk
