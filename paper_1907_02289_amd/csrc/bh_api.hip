@@ -42,6 +42,7 @@ struct bh_ctx {
     std::vector<uint32_t> sys_off;
     bool tree_valid = false, lists_valid = false;
     uint32_t n_nodes = 0, n_groups = 0, max_level = 0;
+    int mom_deep = 0, mom_top = -1;      // launches of a moment pass on the current tree
     uint64_t n_pc = 0, n_pp = 0, interactions = 0;
     int n_grp_used = 64;
 
@@ -54,7 +55,7 @@ struct bh_ctx {
     DevBuf sys_off_b, sys_tab_b, acc_tab_b, box_b, box_part_b, sys_m0_b;
     DevBuf pos_in, vel_in, idx_in, pos, vel, acc, idx, inv;
     DevBuf key, key_tmp, val, val_tmp, hist, scan_tmp;
-    DevBuf nd_prefix, nd_begin, nd_count, nd_first, nd_meta, nd_walk, nd_mom, nd_quad, tmp_a, tmp_b;
+    DevBuf nd_prefix, nd_begin, nd_count, nd_first, nd_meta, nd_walk, nd_mom, nd_quad, tree_cnt;
     DevBuf gmark, grp, g_lo, g_hi, g_cen, g_pc_off, g_pc_len, g_pp_off, g_pp_len, g_cost, order;
     DevBuf gkey_a, gkey_b, gval_a, gval_b;
     DevBuf pc_pool, pp_pool, walk_scratch, counters;
@@ -191,8 +192,9 @@ void refresh_state(bh_ctx *c) {
     d.nd_walk = P<int4>(c->nd_walk);
     d.nd_mom = P<double4>(c->nd_mom);
     d.nd_quad = (c->P.criterion == BH_OPEN_LEARNED) ? P<double>(c->nd_quad) : nullptr;
-    d.tmp_a = P<uint32_t>(c->tmp_a);
-    d.tmp_b = P<uint32_t>(c->tmp_b);
+    d.tree_cnt = P<uint32_t>(c->tree_cnt);
+    d.mom_deep = c->mom_deep;
+    d.mom_top = c->mom_top;
     d.gmark = P<uint32_t>(c->gmark);
     d.grp = P<GroupInfo>(c->grp);
     d.g_lo = P<int4>(c->g_lo);
@@ -343,6 +345,7 @@ bh_status ensure_particles(bh_ctx *c, uint32_t n) {
     HIPCHK(c, grow(c->val_tmp, u4));
     HIPCHK(c, grow(c->hist, bhk::radix_hist_words(cap) * 4));
     HIPCHK(c, grow(c->scan_tmp, SCAN_TMP_WORDS * 4));
+    HIPCHK(c, grow(c->tree_cnt, bhk::tree_cnt_words(cap) * 4));
     HIPCHK(c, grow(c->gmark, u4));
     HIPCHK(c, grow(c->grp, (size_t)cap * sizeof(GroupInfo)));
     HIPCHK(c, grow(c->g_lo, (size_t)cap * sizeof(int4)));
@@ -401,8 +404,6 @@ bh_status ensure_nodes(bh_ctx *c, uint32_t cap) {
         HIPCHK(c, grow(c->nd_quad, (size_t)cap * 6 * sizeof(double)));
         HIPCHK(c, grow(c->nd_qn, (size_t)cap * 4));
     }
-    HIPCHK(c, grow(c->tmp_a, (size_t)cap * 4));
-    HIPCHK(c, grow(c->tmp_b, (size_t)cap * 4));
     c->node_cap = cap;
     STCHK(ensure_drift(c));
     return BH_OK;
@@ -476,6 +477,9 @@ bh_status rebuild(bh_ctx *c, hipStream_t s, bool from_caller) {
     }
     c->n_nodes = c->h_cnt->lvl_off[BH_NLEVELS];
     c->max_level = c->h_cnt->max_level;
+    bhk::moment_plan(c->h_cnt->lvl_off, c->max_level, &c->mom_deep, &c->mom_top);
+    c->d.mom_deep = c->mom_deep;
+    c->d.mom_top = c->mom_top;
     ev_begin(c, EV_MOM, s);
     bhk::moments(c->d, s);
     if (c->P.criterion == BH_OPEN_LEARNED) bhk::node_qn(c->d, s);
@@ -707,7 +711,7 @@ bh_status bh_destroy(bh_ctx *c) {
     DevBuf *all[] = {&c->sys_off_b, &c->sys_tab_b, &c->acc_tab_b, &c->box_b, &c->box_part_b, &c->sys_m0_b, &c->pos_in,
                      &c->vel_in, &c->idx_in, &c->pos, &c->vel, &c->acc, &c->idx, &c->inv, &c->key, &c->key_tmp,
                      &c->val, &c->val_tmp, &c->hist, &c->scan_tmp, &c->nd_prefix, &c->nd_begin, &c->nd_count,
-                     &c->nd_first, &c->nd_meta, &c->nd_walk, &c->nd_mom, &c->nd_quad, &c->tmp_a, &c->tmp_b,
+                     &c->nd_first, &c->nd_meta, &c->nd_walk, &c->nd_mom, &c->nd_quad, &c->tree_cnt,
                      &c->gmark, &c->grp, &c->g_lo, &c->g_hi, &c->g_cen, &c->g_pc_off, &c->g_pc_len,
                      &c->g_pp_off, &c->g_pp_len, &c->g_cost, &c->order, &c->gkey_a, &c->gkey_b, &c->gval_a,
                      &c->gval_b, &c->pc_pool, &c->pp_pool, &c->walk_scratch, &c->counters, &c->direct_part,
@@ -1037,7 +1041,6 @@ bh_status bh_autotune(bh_ctx *c, const int32_t *cand, int32_t n_cand, int32_t re
         for (int k = 0; k < (pass == 0 ? n_cand : 1); ++k) {
             c->n_grp_used = pass == 0 ? cand[k] : best_g;
             refresh_state(c);
-            bhk::regroup(c->d, s);
             bhk::make_groups(c->d, s);
             STCHK(read_counters(c, s));
             c->n_groups = c->h_cnt->n_groups;

@@ -30,7 +30,6 @@ struct DevCounters {
     uint32_t walk_need_front;           // largest frontier seen
     uint32_t walk_need_list;            // longest list seen
     uint32_t work_counter2;             // force kernel's work queue head
-    uint32_t pad[4];
     // the walk's totals, on cache lines of their own: their atomics go in parallel
     alignas(128) unsigned long long pc_used;    // list-pool fill (may exceed capacity: overflow)
     alignas(128) unsigned long long pp_used;
@@ -154,7 +153,8 @@ struct DevState {
     int4 *nd_walk;                 // corner x | level << 24, corner y | n_child << 24, corner z, first child (a leaf: its particle count)
     double4 *nd_mom;               // com x, y, z, mass
     double *nd_quad;               // [node_cap][6] second moments (learned rule only), may be null
-    uint32_t *tmp_a, *tmp_b;       // [node_cap] level scratch
+    uint32_t *tree_cnt;            // [22 levels][tiles of particles] nodes per level and tile, then 22 totals
+    int mom_deep, mom_top;         // moment launches: levels mom_deep-1 .. mom_top+1 one each, mom_top .. 0 together
     // groups
     uint32_t *gmark;               // [n] particle marks, then group index
     GroupInfo *grp;                // [n] (capacity: one per particle)
@@ -223,13 +223,15 @@ void root_box_keys(const DevState &d, hipStream_t s);
 void permute(const DevState &d, hipStream_t s);
 void build_octree(const DevState &d, hipStream_t s);
 void moments(const DevState &d, hipStream_t s);
+// d.mom_deep and d.mom_top for a tree with these level offsets
+void moment_plan(const uint32_t *lvl_off, uint32_t max_level, int *deep, int *top);
+size_t tree_cnt_words(uint32_t n);
 void make_groups(const DevState &d, hipStream_t s);
 // drift monitor: keep the build's positions and moments (after a build) and
 // clear the per-level counts (before each monitored moment pass)
 void drift_snapshot(const DevState &d, hipStream_t s);
 void drift_clear(const DevState &d, hipStream_t s);
 void reset_flags(const DevState &d, hipStream_t s);
-void regroup(const DevState &d, hipStream_t s);   // group flags for d.n_grp on the current tree
 
 // lists (bh_walk.hip)
 void walk(const DevState &d, uint32_t n_groups, hipStream_t s);

@@ -227,135 +227,313 @@ __global__ void k_permute(DevState d) {
 }
 
 // ---------------------------------------------------------------- octree
-__global__ void k_tree_init(DevState d) {
-    uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s == 0) {
-        d.cnt->flags[FLAG_NODE_OVF] = 0;
-        d.cnt->lvl_off[0] = 0;
-        for (int l = 1; l < BH_NLEVELS + 2; ++l) d.cnt->lvl_off[l] = (uint32_t)d.n_sys;
-        d.cnt->max_level = 0;
-        d.cnt->n_groups = 0;
+// All levels at once from the sorted keys.  With cp(i, j) the number of
+// leading octal digits that keys i and j share, a cell of level l starts at
+// particle i when cp(i - 1, i) < l (or i starts its system); it is a node when
+// its parent holds more than n_leaf particles, and it is split itself when
+// cp(i, i + n_leaf) >= l.  So the nodes that start at particle i are those of
+// levels first..last with
+//   first = cp(i - 1, i) + 1, present only when the level first - 1 cell around
+//           i holds more than n_leaf particles (its start is looked for among
+//           the n_leaf particles before i),
+//   last  = max(first, min(21, cp(i, i + n_leaf) + 1)).
+// Ids run by (level, particle), so three launches do: nodes per level and tile
+// of TREE_TILE particles, a scan of each level's tiles, and the nodes
+// themselves, whose ranks inside a tile come from ballots.  (Level after
+// level, 21 times count, three scans and emit, was 105 launches of 2.5 to
+// 35 us: 320 us at 4096 particles, 660 at 2^20, 1500 at 2^24; the four launches
+// now take 25, 60 and 690 us.)
+// A block keeps its tile's keys, and TREE_PAD more on either side, in LDS: the
+// searches around a particle are chains of dependent reads, and all but those
+// of cells wider than the pad stay there.  One row of 64 particles per wave: a
+// tile of 1024 (four rows in turn) takes 38 us instead of 15 at 4096
+// particles, 51 instead of 41 at 2^20 and 514 instead of 445 at 2^24.
+constexpr int TREE_TILE = TPB;
+constexpr int TREE_ROWS = TREE_TILE / 64;
+constexpr int TREE_PAD = 64;
+
+struct TileKeys {
+    const uint64_t *glob, *lds;
+    uint32_t lo, hi;                            // particles [lo, hi) are in LDS
+    __device__ __forceinline__ uint64_t operator[](uint32_t j) const {
+        return j - lo < hi - lo ? lds[j - lo] : glob[j];
     }
-    if (s < (uint32_t)d.n_sys) {
-        uint32_t b = d.sys_off[s], c = d.sys_off[s + 1] - b;
-        bool leaf = !(c > (uint32_t)d.n_leaf);
-        bool grp = (c <= (uint32_t)d.n_grp) || leaf;
-        d.nd_prefix[s] = 0;
-        d.nd_begin[s] = b;
-        d.nd_count[s] = c;
-        d.nd_first[s] = 0;
-        d.nd_meta[s] = make_meta(0, 0, grp ? 1u : 0u, s);
-    }
+};
+
+__device__ __forceinline__ TileKeys tile_keys(const DevState &d, uint64_t *lds) {
+    TileKeys t;
+    const uint32_t i0 = blockIdx.x * TREE_TILE;
+    t.glob = d.key;
+    t.lds = lds;
+    t.lo = i0 > TREE_PAD ? i0 - TREE_PAD : 0u;
+    t.hi = min(d.n, i0 + TREE_TILE + TREE_PAD + 1);
+    for (uint32_t j = t.lo + threadIdx.x; j < t.hi; j += TPB) lds[j - t.lo] = d.key[j];
+    __syncthreads();
+    return t;
 }
 
-// octant boundaries of node v (at level l): bnd[o] = first particle with octant >= o
-__device__ __forceinline__ void octant_bounds(const uint64_t *key, uint32_t b, uint32_t e, int shift,
-                                              uint32_t bnd[9]) {
-    bnd[0] = b;
-    bnd[8] = e;
-#pragma unroll
-    for (uint32_t o = 1; o < 8; ++o) {
-        uint32_t lo = bnd[o - 1], hi = e;     // first i in [lo, e) with octant(i) >= o
+// leading octal digits shared by two keys (0..21)
+__device__ __forceinline__ int common_digits(uint64_t a, uint64_t b) {
+    const uint64_t x = a ^ b;
+    return x ? (__clzll((long long)x) - 1) / 3 : BH_MAXLEVEL;
+}
+
+// Levels first..last of the nodes that start at particle i of the system
+// [b, e); none: first > last.
+__device__ __forceinline__ void node_levels(const TileKeys &key, uint32_t i, uint32_t b, uint32_t e, uint32_t n_leaf,
+                                            int &first, int &last) {
+    const uint64_t k = key[i];
+    int f = 0;
+    first = BH_MAXLEVEL + 1;                       // none, unless found below
+    last = 0;
+    if (i > b) {
+        const int L = common_digits(key[i - 1], k);
+        if (L >= BH_MAXLEVEL) return;              // equal keys
+        f = L + 1;
+        const int sh = 3 * (BH_MAXLEVEL - L);      // L = 0: every key of the system
+        // first particle of the parent's cell, at most n_leaf before i
+        uint32_t lo = i - b > n_leaf ? i - n_leaf : b, hi = i;
         while (lo < hi) {
-            uint32_t mid = (lo + hi) >> 1;
-            if (((uint32_t)(key[mid] >> shift) & 7u) < o) lo = mid + 1; else hi = mid;
+            const uint32_t mid = (lo + hi) >> 1;
+            if (((key[mid] ^ k) >> sh) == 0) hi = mid; else lo = mid + 1;
         }
-        bnd[o] = lo;
+        if (e - lo <= n_leaf || ((key[lo + n_leaf] ^ k) >> sh) != 0) return;
     }
+    int s = -1;
+    if (e - i > n_leaf) s = common_digits(k, key[i + n_leaf]);
+    first = f;
+    last = max(f, min(BH_MAXLEVEL, s + 1));
 }
 
-__global__ void k_tree_count(DevState d, int l) {
-    const uint32_t v0 = d.cnt->lvl_off[l], v1 = d.cnt->lvl_off[l + 1];
-    if (blockIdx.x == 0 && threadIdx.x == 0) d.cnt->pad[0] = v1 - v0;   // level size for the scan
-    const int shift = 3 * (BH_MAXLEVEL - 1 - l);
-    uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t v = v0 + blockIdx.x * blockDim.x + threadIdx.x; v < v1; v += stride) {
-        uint32_t c = d.nd_count[v], nch = 0;
-        if (c > (uint32_t)d.n_leaf && l < BH_MAXLEVEL) {
-            uint32_t bnd[9];
-            octant_bounds(d.key, d.nd_begin[v], d.nd_begin[v] + c, shift, bnd);
+// A particle's system and node levels.
+struct TreeLevels {
+    uint32_t i, b, e, sys;
+    int first, last;
+};
+__device__ __forceinline__ TreeLevels tree_levels(const DevState &d, const TileKeys &key, uint32_t i) {
+    TreeLevels t;
+    t.i = i;
+    t.first = BH_MAXLEVEL + 1;
+    t.last = 0;
+    t.b = t.e = t.sys = 0;
+    if (t.i < d.n) {
+        t.sys = (uint32_t)sys_of(d.sys_off, d.n_sys, t.i);
+        t.b = d.sys_off[t.sys];
+        t.e = d.sys_off[t.sys + 1];
+        node_levels(key, t.i, t.b, t.e, (uint32_t)d.n_leaf, t.first, t.last);
+    }
+    return t;
+}
+
+__global__ void __launch_bounds__(TPB) k_tree_count(DevState d, uint32_t tiles) {
+    __shared__ uint32_t cnt[BH_NLEVELS];
+    __shared__ uint64_t lkey[TREE_TILE + 2 * TREE_PAD + 1];
+    if (threadIdx.x < BH_NLEVELS) cnt[threadIdx.x] = 0;
+    const TileKeys key = tile_keys(d, lkey);
+    const TreeLevels t = tree_levels(d, key, blockIdx.x * TREE_TILE + threadIdx.x);
+    const int lo = wave_min(t.first), hi = wave_max(t.last);
+    for (int l = lo; l <= hi; ++l) {
+        const uint64_t m = __ballot(l >= t.first && l <= t.last);
+        if (m && __lane_id() == 0) atomicAdd(&cnt[l], (uint32_t)__popcll(m));
+    }
+    __syncthreads();
+    if (threadIdx.x < BH_NLEVELS) d.tree_cnt[threadIdx.x * tiles + blockIdx.x] = cnt[threadIdx.x];
+}
+
+// One block per level: exclusive scan of the level's tile counts in place, and
+// the level's total behind the last row.
+__global__ void __launch_bounds__(1024) k_tree_scan(DevState d, uint32_t tiles) {
+    __shared__ uint32_t wsum[16];
+    uint32_t *row = d.tree_cnt + (size_t)blockIdx.x * tiles;
+    uint32_t carry = 0;
+    const int w = threadIdx.x >> 6;
+    for (uint32_t t0 = 0; t0 < tiles; t0 += 1024) {
+        const uint32_t t = t0 + threadIdx.x;
+        const uint32_t v = t < tiles ? row[t] : 0u;
+        const uint32_t inc = wave_incl_scan(v);
+        if (__lane_id() == 63) wsum[w] = inc;
+        __syncthreads();
+        uint32_t off = 0, tot = 0;
 #pragma unroll
-            for (int o = 0; o < 8; ++o) nch += (bnd[o + 1] > bnd[o]) ? 1u : 0u;
+        for (int k = 0; k < 16; ++k) {
+            off += k < w ? wsum[k] : 0u;
+            tot += wsum[k];
         }
-        d.tmp_a[v - v0] = nch;
-        d.tmp_b[v - v0] = nch;
+        if (t < tiles) row[t] = carry + off + inc - v;
+        carry += tot;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) d.tree_cnt[(size_t)BH_NLEVELS * tiles + blockIdx.x] = carry;
+}
+
+// End of the cell that starts at particle i, of the given digit shift, inside
+// [i, e): called by whole waves (on = lanes with a cell).  Cells of up to 64
+// particles: a binary search per lane; larger ones in turn, the 64 lanes
+// probing the remaining range together.
+__device__ __forceinline__ uint32_t cell_end(const TileKeys &key, bool on, uint32_t i, uint32_t e, int sh) {
+    const uint64_t k = on ? key[i] >> sh : 0ull;
+    uint32_t lo = i, hi = i;                      // key[lo] is in the cell, key[hi] is not (or hi = e)
+    bool wide = false;
+    if (on) {
+        hi = e;
+        if (e - i > 64) {
+            wide = (key[i + 64] >> sh) == k;
+            if (!wide) hi = i + 64;
+        }
+        if (!wide)
+            while (hi - lo > 1) {
+                const uint32_t mid = (lo + hi) >> 1;
+                if ((key[mid] >> sh) == k) lo = mid; else hi = mid;
+            }
+    }
+    for (uint64_t m = __ballot(wide); m; m &= m - 1) {
+        const int src = __ffsll((unsigned long long)m) - 1;
+        const uint64_t ks = __shfl((unsigned long long)k, src, 64);
+        const int shs = __shfl(sh, src, 64);
+        uint32_t l = __shfl(i, src, 64) + 64, h = __shfl(e, src, 64);
+        while (h - l > 1) {
+            const uint32_t step = (h - l + 63) >> 6;
+            const uint32_t p = l + (uint32_t)(__lane_id() + 1) * step;
+            const bool in = p < h && p > l && (key.glob[p] >> shs) == ks;
+            const uint32_t c = (uint32_t)__popcll(__ballot(in));
+            l += c * step;
+            h = h - l > step ? l + step : h;
+        }
+        if (__lane_id() == src) hi = h;
+    }
+    return hi;
+}
+
+__global__ void __launch_bounds__(TPB) k_tree_emit(DevState d, uint32_t tiles) {
+    __shared__ uint64_t lkey[TREE_TILE + 2 * TREE_PAD + 1];
+    __shared__ uint32_t rank[TREE_ROWS][BH_NLEVELS];   // nodes of a row, then its first id, per level
+    static_assert(TREE_ROWS * BH_NLEVELS <= TPB && BH_NLEVELS < 64, "one thread per entry, one lane per level");
+    // lanes 0..21 of the first wave: a level's total, first id and the tile's nodes before this one
+    unsigned long long total = 0, end = 0;
+    uint32_t before = 0;
+    if (threadIdx.x < BH_NLEVELS) {
+        total = d.tree_cnt[(size_t)BH_NLEVELS * tiles + threadIdx.x];
+        before = d.tree_cnt[(size_t)threadIdx.x * tiles + blockIdx.x];
+    }
+    if (threadIdx.x < TREE_ROWS * BH_NLEVELS) (&rank[0][0])[threadIdx.x] = 0;
+    const TileKeys key = tile_keys(d, lkey);
+    const uint32_t row = threadIdx.x >> 6;
+    const TreeLevels t = tree_levels(d, key, blockIdx.x * TREE_TILE + threadIdx.x);
+    const int lo = wave_min(t.first), hi = wave_max(t.last);
+    for (int l = lo; l <= hi; ++l) {
+        const uint64_t m = __ballot(l >= t.first && l <= t.last);
+        if (__lane_id() == 0) rank[row][l] = (uint32_t)__popcll(m);
+    }
+    if (row == 0) end = wave_incl_scan(total);
+    __syncthreads();
+    if (threadIdx.x < BH_NLEVELS) {
+        uint32_t a = (uint32_t)min(end - total, (unsigned long long)d.node_cap) + before;
+        for (int r = 0; r < TREE_ROWS; ++r) {
+            const uint32_t c = rank[r][threadIdx.x];
+            rank[r][threadIdx.x] = a;
+            a += c;
+        }
+        if (blockIdx.x == 0) {
+            const uint32_t e = (uint32_t)min(end, (unsigned long long)d.node_cap);
+            d.cnt->lvl_off[threadIdx.x + 1] = e;
+            if (threadIdx.x == 0) d.cnt->lvl_off[0] = 0;
+            const uint64_t some = __ballot(total != 0);
+            if (threadIdx.x == BH_NLEVELS - 1) {
+                d.cnt->lvl_off[BH_NLEVELS + 1] = e;
+                d.cnt->flags[FLAG_NODE_OVF] = end > d.node_cap ? 1u : 0u;
+                d.cnt->max_level = 63 - __clzll((long long)some);
+                d.cnt->n_groups = 0;
+            }
+        }
+    }
+    __syncthreads();
+    uint32_t parent = 0;                        // this particle's node of the level above
+    for (int l = lo; l <= hi; ++l) {
+        const bool on = l >= t.first && l <= t.last;
+        const uint64_t m = __ballot(on);
+        const int sh = 3 * (BH_MAXLEVEL - l);
+        const uint32_t end_i = cell_end(key, on, t.i, t.e, sh);
+        if (!on) continue;
+        const uint32_t u = rank[row][l] + (uint32_t)__popcll(m & lanemask_lt());
+        // a node's first child starts where the node starts
+        if (l > t.first && parent < d.node_cap) d.nd_first[parent] = u;
+        parent = u;
+        if (u >= d.node_cap) continue;          // overflow, flagged above: ids below the cap stay valid
+        d.nd_prefix[u] = key[t.i] >> sh;
+        d.nd_begin[u] = t.i;
+        d.nd_count[u] = end_i - t.i;
+        d.nd_meta[u] = make_meta(l, l < t.last ? 1u : 0u, 0, t.sys);    // the number of children follows
+        if (l == t.last) d.nd_first[u] = 0;
     }
 }
 
-__global__ void k_tree_emit(DevState d, int l) {
-    const uint32_t v0 = d.cnt->lvl_off[l], v1 = d.cnt->lvl_off[l + 1];
-    const uint32_t total = d.cnt->pad[1];
-    const uint32_t base = v1;                       // first id of level l+1
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        uint64_t end = (uint64_t)base + total;
-        if (end > d.node_cap) {
-            atomicOr(&d.cnt->flags[FLAG_NODE_OVF], 1u);
-            end = d.node_cap;
-        }
-        for (int k = l + 2; k < BH_NLEVELS + 2; ++k) d.cnt->lvl_off[k] = (uint32_t)end;
-        if (total > 0) d.cnt->max_level = l + 1;
-    }
-    const int shift = 3 * (BH_MAXLEVEL - 1 - l);
-    uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t v = v0 + blockIdx.x * blockDim.x + threadIdx.x; v < v1; v += stride) {
-        uint32_t nch = d.tmp_b[v - v0];
-        uint32_t meta = d.nd_meta[v];
-        if (nch == 0) {
-            d.nd_first[v] = 0;
-            continue;
-        }
-        uint32_t first = base + d.tmp_a[v - v0];
-        d.nd_first[v] = first;
-        d.nd_meta[v] = make_meta(meta_level(meta), nch, meta_group(meta), meta_sys(meta));
-        uint32_t c = d.nd_count[v];
-        uint32_t bnd[9];
-        octant_bounds(d.key, d.nd_begin[v], d.nd_begin[v] + c, shift, bnd);
-        uint64_t pfx = d.nd_prefix[v];
-        bool parent_big = c > (uint32_t)d.n_grp;
-        uint32_t k = 0;
-        for (uint32_t o = 0; o < 8; ++o) {
-            uint32_t cb = bnd[o], cc = bnd[o + 1] - bnd[o];
-            if (cc == 0) continue;
-            uint32_t u = first + k++;
-            if (u >= d.node_cap) break;     // overflow, flagged above: ids below the cap stay valid
-            bool leaf = !(cc > (uint32_t)d.n_leaf && l + 1 < BH_MAXLEVEL);
-            bool grp = parent_big && (cc <= (uint32_t)d.n_grp || leaf);
-            d.nd_prefix[u] = (pfx << 3) | o;
-            d.nd_begin[u] = cb;
-            d.nd_count[u] = cc;
-            d.nd_first[u] = 0;
-            d.nd_meta[u] = make_meta(l + 1, 0, grp ? 1u : 0u, meta_sys(meta));
-        }
-    }
-}
-
+// Number of children and the walk's record of each node: the children are the
+// nodes from the first child on that start inside the node.
 __global__ void k_node_finalize(DevState d) {
     const uint32_t nn = d.cnt->lvl_off[BH_NLEVELS];
     uint32_t stride = gridDim.x * blockDim.x;
     for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nn; v += stride) {
-        uint32_t meta = d.nd_meta[v];
-        uint32_t l = meta_level(meta);
-        uint64_t p = d.nd_prefix[v];
-        int sh = BH_MAXLEVEL - (int)l;
-        uint32_t cx = compact3(p >> 2) << sh, cy = compact3(p >> 1) << sh, cz = compact3(p) << sh;
+        const uint32_t meta = d.nd_meta[v];
+        const uint32_t l = meta_level(meta);
+        const uint64_t p = d.nd_prefix[v];
+        uint32_t nch = 0, f = 0;
+        if (meta_nch(meta)) {
+            const uint32_t end = d.cnt->lvl_off[l + 2], e = d.nd_begin[v] + d.nd_count[v];
+            f = d.nd_first[v];
+            while (nch < 8 && f + nch < end && d.nd_begin[f + nch] < e) ++nch;
+            d.nd_meta[v] = make_meta(l, nch, 0, meta_sys(meta));
+        }
+        const int sh = BH_MAXLEVEL - (int)l;
+        const uint32_t cx = compact3(p >> 2) << sh, cy = compact3(p >> 1) << sh, cz = compact3(p) << sh;
         // a leaf has no first child: its record carries the particle count for the walk
-        const uint32_t nch = meta_nch(meta);
         d.nd_walk[v] = make_int4((int)(cx | (l << 24)), (int)(cy | (nch << 24)), (int)cz,
-                                 (int)(nch ? d.nd_first[v] : d.nd_count[v]));
+                                 (int)(nch ? f : d.nd_count[v]));
     }
 }
 
 // ---------------------------------------------------------------- moments
-// Bottom-up, one launch per level: a leaf sums its particles, an internal
-// node its children (mass and mass-weighted centre).
-__global__ void k_moments_level(DevState d, int l) {
-    const uint32_t v0 = d.cnt->lvl_off[l], v1 = d.cnt->lvl_off[l + 1];
-    uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t v = v0 + blockIdx.x * blockDim.x + threadIdx.x; v < v1; v += stride) {
-        uint32_t nch = meta_nch(d.nd_meta[v]);
-        double M = 0, sx = 0, sy = 0, sz = 0;
-        if (nch == 0) {
-            uint32_t b = d.nd_begin[v], e = b + d.nd_count[v];
+// Bottom-up: a leaf sums its particles, an internal node its children (mass
+// and mass-weighted centre).  All leaves of all levels in one launch, then the
+// internal nodes level by level, and all top levels of at most MOM_TOP nodes
+// in a single launch of one block with a
+// barrier between levels.  One launch per level of the deepest possible tree
+// was 22 launches of 2.4 to 31 us per refresh: 55 us at 4096 particles, 88 at
+// 2^20; now 16 and 50 us.
+
+// Adds n particles to the drift monitor's count of level l, for the lanes with
+// on: one atomic per wave and level (lanes of a wave hold one level or two).
+__device__ __forceinline__ void count_stale(const DevState &d, bool on, int l, uint32_t n) {
+    for (uint64_t m = __ballot(on); m; m = __ballot(on)) {
+        const int lv = __shfl(l, __ffsll((unsigned long long)m) - 1, 64);
+        const bool mine = on && l == lv;
+        const uint32_t sum = wave_sum(mine ? n : 0u);
+        if (__lane_id() == 0) atomicAdd(&d.cnt->stale[lv], sum);
+        on = on && !mine;
+    }
+}
+
+__device__ __forceinline__ bool has_drifted(const DevState &d, double dr, uint32_t sys, int l) {
+    const double side = ldexp((double)(1u << BH_MAXLEVEL) / d.box[sys].w, -l);
+    return dr > d.drift_kappa * side;
+}
+
+// Drift since the build: the largest distance by which a particle of
+// the node has moved relative to the node's centre of mass,
+//   leaf:     max_i |(x_i - x_i^b) - (c - c^b)|,
+//   internal: max_k (drift_k + |(c_k - c_k^b) - (c - c^b)|),
+// an upper bound of the leaf form over the node's particles.
+__global__ void __launch_bounds__(TPB) k_moments_leaf(DevState d) {
+    const uint32_t nn = d.cnt->lvl_off[BH_NLEVELS];
+    const uint32_t stride = gridDim.x * blockDim.x;
+    const uint32_t end = (nn + 63u) & ~63u;          // whole waves: count_stale needs every lane
+    for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < end; v += stride) {
+        const int4 wr = v < nn ? d.nd_walk[v] : make_int4(0, 1 << 24, 0, 0);
+        const bool leaf = ((uint32_t)wr.y >> 24) == 0;
+        const int l = (int)((uint32_t)wr.x >> 24);
+        bool stale = false;
+        if (leaf) {
+            const uint32_t b = d.nd_begin[v], e = b + (uint32_t)wr.w;
+            double M = 0, sx = 0, sy = 0, sz = 0;
             for (uint32_t i = b; i < e; ++i) {
                 double4 p = d.pos[i];
                 M += p.w;
@@ -363,71 +541,109 @@ __global__ void k_moments_level(DevState d, int l) {
                 sy += p.w * p.y;
                 sz += p.w * p.z;
             }
-        } else {
-            uint32_t f = d.nd_first[v];
-            for (uint32_t c = 0; c < nch; ++c) {
-                double4 q = d.nd_mom[f + c];
-                M += q.w;
-                sx += q.w * q.x;
-                sy += q.w * q.y;
-                sz += q.w * q.z;
-            }
-        }
-        double4 r = make_double4(sx / M, sy / M, sz / M, M);
-        d.nd_mom[v] = r;
-        if (d.nd_drift) {
-            // Drift since the build: the largest distance by which a particle of
-            // the node has moved relative to the node's centre of mass,
-            //   leaf:     max_i |(x_i - x_i^b) - (c - c^b)|,
-            //   internal: max_k (drift_k + |(c_k - c_k^b) - (c - c^b)|),
-            // an upper bound of the leaf form over the node's particles.
-            const double4 rb = d.nd_mom_b[v];
-            const double ux = r.x - rb.x, uy = r.y - rb.y, uz = r.z - rb.z;
-            double dr = 0.0;
-            if (nch == 0) {
-                uint32_t b = d.nd_begin[v], e = b + d.nd_count[v];
+            const double4 r = make_double4(sx / M, sy / M, sz / M, M);
+            d.nd_mom[v] = r;
+            if (d.nd_drift) {
+                const double4 rb = d.nd_mom_b[v];
+                const double ux = r.x - rb.x, uy = r.y - rb.y, uz = r.z - rb.z;
+                double dr = 0.0;
                 for (uint32_t i = b; i < e; ++i) {
                     const double4 p = d.pos[i], q = d.pos_b[i];
                     const double ex = (p.x - q.x) - ux, ey = (p.y - q.y) - uy, ez = (p.z - q.z) - uz;
                     dr = fmax(dr, sqrt(ex * ex + ey * ey + ez * ez));
                 }
-            } else {
-                uint32_t f = d.nd_first[v];
-                for (uint32_t c = 0; c < nch; ++c) {
-                    const double4 q = d.nd_mom[f + c], qb = d.nd_mom_b[f + c];
-                    const double ex = (q.x - qb.x) - ux, ey = (q.y - qb.y) - uy, ez = (q.z - qb.z) - uz;
-                    dr = fmax(dr, d.nd_drift[f + c] + sqrt(ex * ex + ey * ey + ez * ez));
-                }
+                d.nd_drift[v] = dr;
+                stale = has_drifted(d, dr, meta_sys(d.nd_meta[v]), l);
             }
-            d.nd_drift[v] = dr;
-            const uint32_t meta = d.nd_meta[v];
-            const double side = ldexp((double)(1u << BH_MAXLEVEL) / d.box[meta_sys(meta)].w, -l);
-            if (dr > d.drift_kappa * side) atomicAdd(&d.cnt->stale[l], d.nd_count[v]);
-        }
-        if (d.nd_quad) {
-            double Q[6] = {0, 0, 0, 0, 0, 0};
-            if (nch == 0) {
-                uint32_t b = d.nd_begin[v], e = b + d.nd_count[v];
+            if (d.nd_quad) {
+                double Q[6] = {0, 0, 0, 0, 0, 0};
                 for (uint32_t i = b; i < e; ++i) {
                     double4 p = d.pos[i];
                     double dx = p.x - r.x, dy = p.y - r.y, dz = p.z - r.z;
                     Q[0] += p.w * dx * dx; Q[1] += p.w * dx * dy; Q[2] += p.w * dx * dz;
                     Q[3] += p.w * dy * dy; Q[4] += p.w * dy * dz; Q[5] += p.w * dz * dz;
                 }
-            } else {
-                uint32_t f = d.nd_first[v];
-                for (uint32_t c = 0; c < nch; ++c) {
-                    double4 q = d.nd_mom[f + c];
-                    const double *qc = d.nd_quad + (size_t)(f + c) * 6;
-                    double dx = q.x - r.x, dy = q.y - r.y, dz = q.z - r.z;
-                    Q[0] += qc[0] + q.w * dx * dx; Q[1] += qc[1] + q.w * dx * dy;
-                    Q[2] += qc[2] + q.w * dx * dz; Q[3] += qc[3] + q.w * dy * dy;
-                    Q[4] += qc[4] + q.w * dy * dz; Q[5] += qc[5] + q.w * dz * dz;
-                }
+                double *o = d.nd_quad + (size_t)v * 6;
+                for (int k = 0; k < 6; ++k) o[k] = Q[k];
             }
-            double *o = d.nd_quad + (size_t)v * 6;
-            for (int k = 0; k < 6; ++k) o[k] = Q[k];
         }
+        if (d.nd_drift) count_stale(d, stale, l, (uint32_t)wr.w);
+    }
+}
+
+// One internal node of level l; returns whether it has drifted.
+__device__ __forceinline__ bool node_moments(const DevState &d, uint32_t v, int4 wr, int l) {
+    const uint32_t nch = (uint32_t)wr.y >> 24, f = (uint32_t)wr.w;
+    double4 q[8];
+#pragma unroll
+    for (uint32_t c = 0; c < 8; ++c)
+        if (c < nch) q[c] = d.nd_mom[f + c];        // all in flight at once, summed in order
+    double M = 0, sx = 0, sy = 0, sz = 0;
+#pragma unroll
+    for (uint32_t c = 0; c < 8; ++c)
+        if (c < nch) {
+            M += q[c].w;
+            sx += q[c].w * q[c].x;
+            sy += q[c].w * q[c].y;
+            sz += q[c].w * q[c].z;
+        }
+    const double4 r = make_double4(sx / M, sy / M, sz / M, M);
+    d.nd_mom[v] = r;
+    bool stale = false;
+    if (d.nd_drift) {
+        const double4 rb = d.nd_mom_b[v];
+        const double ux = r.x - rb.x, uy = r.y - rb.y, uz = r.z - rb.z;
+        double dr = 0.0;
+#pragma unroll
+        for (uint32_t c = 0; c < 8; ++c)
+            if (c < nch) {
+                const double4 qb = d.nd_mom_b[f + c];
+                const double ex = (q[c].x - qb.x) - ux, ey = (q[c].y - qb.y) - uy, ez = (q[c].z - qb.z) - uz;
+                dr = fmax(dr, d.nd_drift[f + c] + sqrt(ex * ex + ey * ey + ez * ez));
+            }
+        d.nd_drift[v] = dr;
+        stale = has_drifted(d, dr, meta_sys(d.nd_meta[v]), l);
+    }
+    if (d.nd_quad) {
+        double Q[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (uint32_t c = 0; c < 8; ++c)
+            if (c < nch) {
+                const double *qc = d.nd_quad + (size_t)(f + c) * 6;
+                double dx = q[c].x - r.x, dy = q[c].y - r.y, dz = q[c].z - r.z;
+                Q[0] += qc[0] + q[c].w * dx * dx; Q[1] += qc[1] + q[c].w * dx * dy;
+                Q[2] += qc[2] + q[c].w * dx * dz; Q[3] += qc[3] + q[c].w * dy * dy;
+                Q[4] += qc[4] + q[c].w * dy * dz; Q[5] += qc[5] + q[c].w * dz * dz;
+            }
+        double *o = d.nd_quad + (size_t)v * 6;
+        for (int k = 0; k < 6; ++k) o[k] = Q[k];
+    }
+    return stale;
+}
+
+// The internal nodes of level l, by the threads t0, t0 + stride, ...
+__device__ __forceinline__ void level_moments(const DevState &d, int l, uint32_t t0, uint32_t stride) {
+    const uint32_t v0 = d.cnt->lvl_off[l], v1 = d.cnt->lvl_off[l + 1];
+    const uint32_t end = v0 + ((v1 - v0 + 63u) & ~63u);
+    for (uint32_t v = v0 + t0; v < end; v += stride) {
+        bool stale = false;
+        if (v < v1) {
+            const int4 wr = d.nd_walk[v];
+            if (((uint32_t)wr.y >> 24) != 0) stale = node_moments(d, v, wr, l);
+        }
+        if (d.nd_drift) count_stale(d, stale, l, stale ? d.nd_count[v] : 0u);
+    }
+}
+
+__global__ void __launch_bounds__(TPB) k_moments_level(DevState d, int l) {
+    level_moments(d, l, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+}
+
+// Levels from `top` (or the deepest but one, whichever is higher up) to 0 in one block.
+__global__ void __launch_bounds__(1024) k_moments_top(DevState d, int top) {
+    for (int l = min(top, (int)d.cnt->max_level - 1); l >= 0; --l) {
+        level_moments(d, l, threadIdx.x, 1024);
+        __syncthreads();
     }
 }
 
@@ -439,6 +655,7 @@ __global__ void k_moments_level(DevState d, int l) {
 // the first node of each pack: the parent's thread walks its children in
 // order and starts a new pack where the next small child no longer fits
 // (the pack's particle count is taken later from the next group's start).
+// Also marks the first particle of each group.
 __global__ void k_regroup(DevState d) {
     const uint32_t nn = d.cnt->lvl_off[BH_NLEVELS];
     const uint32_t G = (uint32_t)d.n_grp;
@@ -448,6 +665,7 @@ __global__ void k_regroup(DevState d) {
         if (v < (uint32_t)d.n_sys) {
             const bool grp = c <= G || nch == 0;
             d.nd_meta[v] = make_meta(meta_level(meta), nch, grp ? 1u : 0u, meta_sys(meta));
+            if (grp) d.gmark[d.nd_begin[v]] = 1u;
         }
         const uint32_t f = d.nd_first[v];
         uint32_t run = 0;    // particles in the open pack, 0 when none is open
@@ -465,16 +683,11 @@ __global__ void k_regroup(DevState d) {
             } else {
                 run = 0;                     // a split child or an over-full leaf ends the run
             }
-            d.nd_meta[u] = make_meta(meta_level(mu), meta_nch(mu), grp ? 1u : 0u, meta_sys(mu));
+            if (grp != (meta_group(mu) != 0u))
+                d.nd_meta[u] = make_meta(meta_level(mu), meta_nch(mu), grp ? 1u : 0u, meta_sys(mu));
+            if (grp) d.gmark[d.nd_begin[u]] = 1u;
         }
     }
-}
-
-__global__ void k_group_mark(DevState d) {
-    const uint32_t nn = d.cnt->lvl_off[BH_NLEVELS];
-    uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nn; v += stride)
-        if (meta_group(d.nd_meta[v])) d.gmark[d.nd_begin[v]] = 1u;
 }
 
 __global__ void k_group_emit(DevState d) {
@@ -565,20 +778,36 @@ void permute(const DevState &d, hipStream_t s) {
     k_permute<<<grid_for(d.n), TPB, 0, s>>>(d);
 }
 
+uint32_t tree_tiles(uint32_t n) { return (n + TREE_TILE - 1) / TREE_TILE; }
+
+size_t tree_cnt_words(uint32_t n) { return (size_t)BH_NLEVELS * (tree_tiles(n) + 1); }
+
 void build_octree(const DevState &d, hipStream_t s) {
-    k_tree_init<<<(d.n_sys + TPB - 1) / TPB, TPB, 0, s>>>(d);
-    const unsigned g = grid_for(d.node_cap, 4096);
-    for (int l = 0; l < BH_MAXLEVEL; ++l) {
-        k_tree_count<<<g, TPB, 0, s>>>(d, l);
-        scan_u32(d.tmp_a, d.tmp_a, &d.cnt->pad[0], 0, &d.cnt->pad[1], d.scan_tmp, s);
-        k_tree_emit<<<g, TPB, 0, s>>>(d, l);
-    }
-    k_node_finalize<<<g, TPB, 0, s>>>(d);
+    const uint32_t tiles = tree_tiles(d.n);
+    k_tree_count<<<tiles, TPB, 0, s>>>(d, tiles);
+    k_tree_scan<<<BH_NLEVELS, 1024, 0, s>>>(d, tiles);
+    k_tree_emit<<<tiles, TPB, 0, s>>>(d, tiles);
+    k_node_finalize<<<grid_for(d.n, 4096), TPB, 0, s>>>(d);
+}
+
+// Levels of at most this many nodes share the single block of k_moments_top,
+// one node per thread: 1.2 us per level.  At 4096 nodes the one CU's loads took
+// 4 to 5 us per level, as much as a launch of its own.
+constexpr uint32_t MOM_TOP = 1024;
+
+void moment_plan(const uint32_t *lvl_off, uint32_t max_level, int *deep, int *top) {
+    int t = -1;
+    while (t + 1 < (int)max_level && lvl_off[t + 2] - lvl_off[t + 1] <= MOM_TOP) ++t;
+    // small trees: the one block takes every level, whatever the depth
+    const bool all = t + 1 >= (int)max_level;
+    *top = all ? BH_MAXLEVEL : t;
+    *deep = all ? 0 : (int)max_level;
 }
 
 void moments(const DevState &d, hipStream_t s) {
-    const unsigned g = grid_for(d.node_cap, 4096);
-    for (int l = BH_MAXLEVEL; l >= 0; --l) k_moments_level<<<g, TPB, 0, s>>>(d, l);
+    k_moments_leaf<<<grid_for(d.n, 4096), TPB, 0, s>>>(d);
+    for (int l = d.mom_deep - 1; l > d.mom_top; --l) k_moments_level<<<grid_for(d.n / 4, 2048), TPB, 0, s>>>(d, l);
+    if (d.mom_top >= 0) k_moments_top<<<1, 1024, 0, s>>>(d, d.mom_top);
 }
 
 __global__ void k_drift_snapshot(DevState d) {
@@ -602,15 +831,10 @@ void drift_clear(const DevState &d, hipStream_t s) {
     k_drift_clear<<<1, 64, 0, s>>>(d);
 }
 
-void regroup(const DevState &d, hipStream_t s) {
-    k_regroup<<<grid_for(d.node_cap, 4096), TPB, 0, s>>>(d);
-}
-
 void make_groups(const DevState &d, hipStream_t s) {
-    const unsigned g = grid_for(d.node_cap, 4096);
-    if (d.pack_groups) k_regroup<<<g, TPB, 0, s>>>(d);
+    const unsigned g = grid_for(d.n, 4096);
     fill_u32(d.gmark, 0u, d.n, s);
-    k_group_mark<<<g, TPB, 0, s>>>(d);
+    k_regroup<<<g, TPB, 0, s>>>(d);
     scan_u32(d.gmark, d.gmark, nullptr, d.n, &d.cnt->n_groups, d.scan_tmp, s);
     k_group_emit<<<g, TPB, 0, s>>>(d);
     if (d.pack_groups) k_group_count<<<grid_for(d.n, 4096), TPB, 0, s>>>(d);
