@@ -304,11 +304,13 @@ void scan_u32(const uint32_t *in, uint32_t *out, const uint32_t *n_dev, uint32_t
 // fill n words with v (graph-safe replacement for hipMemsetAsync)
 void fill_u32(uint32_t *p, uint32_t v, size_t n, hipStream_t s);
 
-// Stable LSD radix sort of (key, val) pairs by key bits [lo_bit, hi_bit),
+// Stable sort of (key, val) pairs by key, the keys being zero outside bits
+// [lo_bit, hi_bit) or, outside them, already ascending in input order within
+// equal keys of these bits;
 // then (when sys_off != nullptr and n_sys > 1) by the system owning input
 // index val (sys_off: device array of n_sys+1 offsets), so the result is in
 // (system, key, input order).  Result in key_a/val_a.  Scratch: key_b/val_b
-// of n, hist of radix_hist_words(n).
+// of n, hist of radix_hist_words(n) or of any larger count.
 size_t radix_hist_words(uint32_t n);
 void radix_sort(uint64_t *key_a, uint32_t *val_a, uint64_t *key_b, uint32_t *val_b,
                 uint32_t n, int lo_bit, int hi_bit, uint32_t *hist, uint32_t *tmp, hipStream_t s,

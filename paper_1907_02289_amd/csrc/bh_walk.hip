@@ -421,7 +421,8 @@ void order_groups(const DevState &d, uint32_t n_groups, uint64_t *key_a, uint32_
     unsigned blocks = (n_groups + 255) / 256;
     if (blocks > 4096) blocks = 4096;
     k_order_keys<<<blocks, 256, 0, s>>>(d, key_a, val_a);
-    radix_sort(key_a, val_a, key_b, val_b, n_groups, 0, 40, d.hist, d.scan_tmp, s, nullptr, 0);
+    // the low 32 bits, the group id, ascend already: a stable sort by the class is enough
+    radix_sort(key_a, val_a, key_b, val_b, n_groups, 32, 40, d.hist, d.scan_tmp, s, nullptr, 0);
     (void)hipMemcpyAsync(d.order, val_a, (size_t)n_groups * sizeof(uint32_t), hipMemcpyDeviceToDevice, s);
 }
 
