@@ -56,7 +56,7 @@ struct bh_ctx {
     DevBuf pos_in, vel_in, idx_in, pos, vel, acc, idx, inv;
     DevBuf key, key_tmp, val, val_tmp, hist, scan_tmp;
     DevBuf nd_prefix, nd_begin, nd_count, nd_first, nd_meta, nd_walk, nd_mom, nd_quad, tree_cnt;
-    DevBuf gmark, grp, g_lo, g_hi, g_cen, g_pc_off, g_pc_len, g_pp_off, g_pp_len, g_cost, order;
+    DevBuf gmark, grp, g_lo, g_hi, g_cen, g_pc_off, g_pc_len, g_pp_off, g_pp_len, g_cost, force_items;
     DevBuf gkey_a, gkey_b, gval_a, gval_b;
     DevBuf pc_pool, pp_pool, walk_scratch, counters;
     DevBuf pos_b, nd_mom_b, nd_drift;    // drift monitor: build snapshot and per-node drift
@@ -205,7 +205,7 @@ void refresh_state(bh_ctx *c) {
     d.g_pp_off = P<unsigned long long>(c->g_pp_off);
     d.g_pp_len = P<uint32_t>(c->g_pp_len);
     d.g_cost = P<unsigned long long>(c->g_cost);
-    d.order = P<uint32_t>(c->order);
+    d.force_items = P<ForceItem>(c->force_items);
     d.pc_pool = P<uint32_t>(c->pc_pool);
     d.pp_pool = P<uint32_t>(c->pp_pool);
     d.pc_cap = c->pc_cap;
@@ -356,7 +356,6 @@ bh_status ensure_particles(bh_ctx *c, uint32_t n) {
     HIPCHK(c, grow(c->g_pp_off, u8));
     HIPCHK(c, grow(c->g_pp_len, u4));
     HIPCHK(c, grow(c->g_cost, u8));
-    HIPCHK(c, grow(c->order, u4));
     HIPCHK(c, grow(c->gkey_a, u8));
     HIPCHK(c, grow(c->gkey_b, u8));
     HIPCHK(c, grow(c->gval_a, u4));
@@ -553,6 +552,11 @@ bh_status walk_until_fits(bh_ctx *c, hipStream_t s) {
 bh_status run_forces(bh_ctx *c, hipStream_t s, bool pot, double kick_h = 0.0);
 
 bh_status order_lists(bh_ctx *c, hipStream_t s) {
+    const size_t need = (size_t)c->n_groups * sizeof(ForceItem);
+    if (need > c->force_items.bytes || !c->force_items.p) {
+        HIPCHK(c, grow(c->force_items, need + need / 4 + 4096));
+        c->d.force_items = P<ForceItem>(c->force_items);
+    }
     bhk::order_groups(c->d, c->n_groups, P<uint64_t>(c->gkey_a), P<uint32_t>(c->gval_a), P<uint64_t>(c->gkey_b),
                       P<uint32_t>(c->gval_b), s);
     c->lists_valid = true;
@@ -713,7 +717,7 @@ bh_status bh_destroy(bh_ctx *c) {
                      &c->val, &c->val_tmp, &c->hist, &c->scan_tmp, &c->nd_prefix, &c->nd_begin, &c->nd_count,
                      &c->nd_first, &c->nd_meta, &c->nd_walk, &c->nd_mom, &c->nd_quad, &c->tree_cnt,
                      &c->gmark, &c->grp, &c->g_lo, &c->g_hi, &c->g_cen, &c->g_pc_off, &c->g_pc_len,
-                     &c->g_pp_off, &c->g_pp_len, &c->g_cost, &c->order, &c->gkey_a, &c->gkey_b, &c->gval_a,
+                     &c->g_pp_off, &c->g_pp_len, &c->g_cost, &c->force_items, &c->gkey_a, &c->gkey_b, &c->gval_a,
                      &c->gval_b, &c->pc_pool, &c->pp_pool, &c->walk_scratch, &c->counters, &c->direct_part,
                      &c->nd_qn, &c->amag, &c->amag_in, &c->g_amin, &c->g_rad, &c->cand, &c->mlp_w, &c->mlp_m,
                      &c->mlp_v, &c->mlp_scratch, &c->ds_x, &c->ds_y, &c->ds_pairs, &c->pk_a, &c->pk_b,
@@ -1054,12 +1058,17 @@ bh_status bh_autotune(bh_ctx *c, const int32_t *cand, int32_t n_cand, int32_t re
             double ms[EV_N];
             STCHK(bh_stage_times(c, ms));
             const double walk_ms = ms[EV_WALK];
+            // one evaluation before the timed ones: the first on new lists finds no
+            // sources in the caches, and would count against the tile tried first
+            refresh_state(c);
+            bhk::forces(c->d, c->n_groups, c->P.precision == BH_FP32_REL, false, force_blocks(c), 0.0, s);
             for (int tile : tiles) {
                 c->P.force_tile = tile;
                 refresh_state(c);
                 STCHK(run_forces(c, s, false));
                 STCHK(bh_stage_times(c, ms));
-                const double t = ms[EV_FORCE] + walk_ms / rebuild_every;
+                // the smaller tile wins by 2% or not at all: single timings differ by as much
+                const double t = (ms[EV_FORCE] + walk_ms / rebuild_every) * (tile == 256 && tiles.size() > 1 ? 1.02 : 1.0);
                 if (t < best) {
                     best = t;
                     best_g = cand[k];

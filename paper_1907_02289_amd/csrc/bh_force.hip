@@ -23,8 +23,8 @@
 // big level-21 leaves, searches the leaf offsets instead).  Inside a leapfrog
 // step these kernels also apply the closing half kick to each particle.
 //
-// Scheduling (Sec. 4.6): a persistent grid takes groups from an atomic
-// queue in order of decreasing interaction count, so the longest lists start
+// Scheduling (Sec. 4.6): a persistent grid takes groups, 256 particles at a
+// time, from an atomic queue in order of decreasing interaction count, so the longest lists start
 // first and the tail is made of short ones.  All four waves of a workgroup
 // share one LDS tile of sources (the paper's cores sharing a cache on one
 // list).  The waves take 64-particle chunks of the group, the waves left
@@ -52,6 +52,8 @@
 // use the sub-slice modes only (no tail or eighths mode, no id list, no
 // fused kick: their LDS and registers are at the six-workgroup limit, and the
 // dashpot reads other particles' velocities).
+#include <algorithm>
+
 #include "bh_internal.hpp"
 
 namespace {
@@ -96,6 +98,118 @@ __device__ __forceinline__ float fma_r<float>(float a, float b, float c) { retur
 template <>
 __device__ __forceinline__ double fma_r<double>(double a, double b, double c) { return fma(a, b, c); }
 
+// The FP32 gravity pair loop over 4 n4 sources from LDS address `addr` (per
+// lane), in the order and with the roundings of the C++ loops below.
+//
+// What bounds it is instruction issue (measured on gfx950, wave64, 24 waves per
+// CU; cycles per instruction and SIMD at 2.4 GHz):
+//   - A VALU instruction on VGPRs issues in 2.3 to 2.5 cycles, but registers
+//     lie in two banks, even and odd: instructions that keep reading one bank
+//     (fma x, x, y with both even) take 3.6 to 4.2.  An SGPR operand always
+//     costs 4.2 to 4.4.  v_rsq_f32 takes 8.2 and overlaps nothing.
+//   - In the compiler's loop four of eight sources wait for their LDS read in
+//     full, and a loop that starts away from a 64-byte line loses up to 10%.
+// So the loop is aligned, names its registers (the map is the best of 1500
+// tried) and reads the next two sources while it works on two.  What it gives
+// depends on the launch.  With few groups, where a CU holds few waves: 1.43 ms
+// with the compiler's loop, 1.07 with this one, at 1914 groups (5e5 particles,
+// items as below).  On a full chip the clock gives way instead (2.15 GHz with
+// the compiler's loop): the 2^24 ring's launch 78.0 -> 77.1 ms, 64 Plummer
+// spheres 1.79 -> 1.78.  The two sources' chains interleaved instruction by
+// instruction were no faster alone and 2% slower there (78.2 ms): the power
+// limit again.
+//
+// Registers, mass in the loop: ax, ay, az v57 v59 v61; xi, yi, zi v49 v51 v53;
+// eps2 v55; sources v32-35, v36-39, v40-43, v44-47; temporaries v48, v50 and
+// the odd ones up to v77.  Equal masses: ax, ay, az v40 v46 v52; xi, yi, zi v41
+// v47 v53; eps2 v59; sources v42-45, v48-51, v54-57, v60-63; temporaries v58
+// and v64 to v71.  Address v79.  The loop reads two sources past the last one
+// (the tile is padded by 16) and waits for them before it ends.
+#define SUB(d, a, b) "v_sub_f32 v" #d ", v" #a ", v" #b "\n\t"
+#define MUL(d, a, b) "v_mul_f32 v" #d ", v" #a ", v" #b "\n\t"
+#define FMA(d, a, b, c) "v_fma_f32 v" #d ", v" #a ", v" #b ", v" #c "\n\t"
+#define FMAC(d, a, b) "v_fmac_f32 v" #d ", v" #a ", v" #b "\n\t"
+#define RSQ(d, a) "v_rsq_f32 v" #d ", v" #a "\n\t"
+#define LDS4(a, b, addr, off) "ds_read_b128 v[" #a ":" #b "], v" #addr " offset:" #off "\n\t"
+// one source (x, y, z, m) with temporaries; the s_nop keeps v_rsq_f32 and its first use two instructions apart
+#define PAIR_MASS(x, y, z, m, dy, r, t, u, f)                                                                  \
+    SUB(z, z, 53) SUB(dy, y, 51) SUB(x, x, 49) FMA(r, z, z, 55) FMA(t, dy, dy, r) FMA(u, x, x, t) RSQ(r, u)    \
+    "s_nop 0\n\t" MUL(t, r, r) MUL(u, m, r) MUL(f, u, t) FMAC(57, f, x) FMAC(59, f, dy) FMAC(61, f, z)
+#define PAIR_EQM(x, y, z, r, t, f, u)                                                                          \
+    SUB(z, z, 53) SUB(y, y, 47) SUB(x, x, 41) FMA(r, z, z, 59) FMA(t, y, y, r) FMA(u, x, x, t) RSQ(r, u)       \
+    "s_nop 0\n\t" MUL(t, r, r) MUL(f, r, t) FMAC(40, f, x) FMAC(46, f, y) FMAC(52, f, z)
+// two, the second on other temporaries
+#define PAIR2_MASS(x, y, z, m, X, Y, Z, M)                                                                     \
+    PAIR_MASS(x, y, z, m, 48, 63, 67, 75, 71) PAIR_MASS(X, Y, Z, M, 50, 65, 69, 77, 73)
+#define PAIR2_EQM(x, y, z, X, Y, Z) PAIR_EQM(x, y, z, 58, 67, 69, 66) PAIR_EQM(X, Y, Z, 65, 64, 71, 68)
+
+template <bool EQM>
+__device__ __forceinline__ void pair_loop(uint32_t addr, int n4, float xi, float yi, float zi, float eps2, float &ax,
+                                          float &ay, float &az) {
+    if constexpr (EQM) {
+        asm volatile(LDS4(42, 45, 79, 0) LDS4(48, 51, 79, 16)
+                     ".p2align 6\n"
+                     "Lpair%=:\n\t"
+                     LDS4(54, 57, 79, 32) LDS4(60, 63, 79, 48)
+                     "s_waitcnt lgkmcnt(2)\n\t"
+                     PAIR2_EQM(42, 43, 44, 48, 49, 50)
+                     "v_add_u32 v79, 64, v79\n\t"
+                     LDS4(42, 45, 79, 0) LDS4(48, 51, 79, 16)
+                     "s_waitcnt lgkmcnt(2)\n\t"
+                     PAIR2_EQM(54, 55, 56, 60, 61, 62)
+                     "s_sub_u32 %[n], %[n], 1\n\t"
+                     "s_cmp_lg_u32 %[n], 0\n\t"
+                     "s_cbranch_scc1 Lpair%=\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "+{v40}"(ax), "+{v46}"(ay), "+{v52}"(az), "+{v79}"(addr), [n] "+s"(n4)
+                     : "{v41}"(xi), "{v47}"(yi), "{v53}"(zi), "{v59}"(eps2)
+                     : "memory", "scc", "v42", "v43", "v44", "v45", "v48", "v49", "v50", "v51", "v54", "v55", "v56",
+                       "v57", "v58", "v60", "v61", "v62", "v63", "v64", "v65", "v66", "v67", "v68", "v69", "v71");
+    } else {
+        asm volatile(LDS4(32, 35, 79, 0) LDS4(36, 39, 79, 16)
+                     ".p2align 6\n"
+                     "Lpair%=:\n\t"
+                     LDS4(40, 43, 79, 32) LDS4(44, 47, 79, 48)
+                     "s_waitcnt lgkmcnt(2)\n\t"
+                     PAIR2_MASS(32, 33, 34, 35, 36, 37, 38, 39)
+                     "v_add_u32 v79, 64, v79\n\t"
+                     LDS4(32, 35, 79, 0) LDS4(36, 39, 79, 16)
+                     "s_waitcnt lgkmcnt(2)\n\t"
+                     PAIR2_MASS(40, 41, 42, 43, 44, 45, 46, 47)
+                     "s_sub_u32 %[n], %[n], 1\n\t"
+                     "s_cmp_lg_u32 %[n], 0\n\t"
+                     "s_cbranch_scc1 Lpair%=\n\t"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "+{v57}"(ax), "+{v59}"(ay), "+{v61}"(az), "+{v79}"(addr), [n] "+s"(n4)
+                     : "{v49}"(xi), "{v51}"(yi), "{v53}"(zi), "{v55}"(eps2)
+                     : "memory", "scc", "v32", "v33", "v34", "v35", "v36", "v37", "v38", "v39", "v40", "v41", "v42",
+                       "v43", "v44", "v45", "v46", "v47", "v48", "v50", "v63", "v65", "v67", "v69", "v71", "v73",
+                       "v75", "v77");
+    }
+}
+#undef SUB
+#undef MUL
+#undef FMA
+#undef FMAC
+#undef RSQ
+#undef LDS4
+#undef PAIR_MASS
+#undef PAIR_EQM
+#undef PAIR2_MASS
+#undef PAIR2_EQM
+
+// byte address of an LDS object
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
+}
+
+// whether a pass has the hand-scheduled loop
+template <typename R, bool POT, bool ZERO_EPS, bool CLAMP>
+constexpr bool PAIR_LOOP = sizeof(R) == 4 && !POT && !ZERO_EPS && !CLAMP;
+// unrolling of the C++ loops: they take the last one to three sources after pair_loop
+template <bool TAIL_ONLY>
+constexpr int UNROLL = TAIL_ONLY ? 1 : 8;
+
 // One pass of a wave over sources [j0, j1) of the LDS tile.  The bounds are
 // the same for every lane of the wave; taking them through readfirstlane
 // keeps the loop control on the scalar unit, so the vector unit issues only
@@ -136,8 +250,14 @@ __device__ __forceinline__ void interact_lanes(const typename V4<R>::T *tile, in
                                                R eps2, R rce2, R &ax, R &ay, R &az, R &pot, R &cmin) {
     L = __builtin_amdgcn_readfirstlane(L);
     const typename V4<R>::T *t = tile + jb;
-#pragma unroll 8
-    for (int k = 0; k < L; ++k) {
+    int k0 = 0;
+    if constexpr (PAIR_LOOP<R, POT, ZERO_EPS, CLAMP>) {
+        const int n4 = L >> 2;
+        if (n4 > 0) pair_loop<EQM>(lds_address(t), n4, xi, yi, zi, eps2, ax, ay, az);
+        k0 = max(n4, 0) * 4;
+    }
+#pragma unroll UNROLL<PAIR_LOOP<R, POT, ZERO_EPS, CLAMP>>
+    for (int k = k0; k < L; ++k) {
         const typename V4<R>::T s = t[k];
         const R dx = s.x - xi, dy = s.y - yi, dz = s.z - zi;
         R r2 = fma_r<R>(dx, dx, fma_r<R>(dy, dy, fma_r<R>(dz, dz, eps2)));
@@ -161,7 +281,7 @@ __device__ __forceinline__ void interact_lanes(const typename V4<R>::T *tile, in
 template <typename R, bool POT, bool ZERO_EPS, bool CLAMP, bool EQM>
 __device__ __forceinline__ void tile_pass(const typename V4<R>::T *tile, int sub, int jl0, int L, R xi, R yi, R zi,
                                           R eps2, R rce2, R &ax, R &ay, R &az, R &pot, R &cmin) {
-    if (sub == 1)
+    if (!PAIR_LOOP<R, POT, ZERO_EPS, CLAMP> && sub == 1)
         interact<R, POT, ZERO_EPS, CLAMP, EQM>(tile, jl0, jl0 + L, xi, yi, zi, eps2, rce2, ax, ay, az, pot, cmin);
     else
         interact_lanes<R, POT, ZERO_EPS, CLAMP, EQM>(tile, jl0, L, xi, yi, zi, eps2, rce2, ax, ay, az, pot, cmin);
@@ -218,6 +338,33 @@ __device__ __forceinline__ void contact_pass(const typename V4<R>::T *tile, cons
     }
 }
 
+// Work items of the persistent blocks: an item is 256 particles of a group
+// (part p of a group: its blocks of 256 p, p + parts, ...; a group of more than
+// parts blocks, of coincident particles, wraps around), so a group's particles
+// are summed alike however many groups a launch has.  Items come in descending
+// cost and Morton order from one counter: blocks in flight then work on
+// neighbouring groups, whose sources stay in L2.  (Half of the items dealt to
+// the blocks in turn, without the counter, took the 2^24 ring's launch from 77
+// to 105 ms: the blocks drift apart.)  Whole groups as items left the chip
+// waiting for the last large ones when groups are few: 1.78 -> 1.43 ms at 1914
+// groups of up to 512.  A group of one item pops the counter once more for its
+// empty second part, 12 ns each over the whole chip: 0.390 -> 0.397 ms at 16077
+// groups of the 2^20 ring.
+struct ForceQueue {
+    uint32_t items, parts, pops;
+};
+
+ForceQueue force_queue(uint32_t n_groups, uint32_t n_grp, int &blocks) {
+    ForceQueue q;
+    // bounded so that items stay 32-bit (any number of parts covers a group)
+    const uint32_t most = 0x7fffffffu / n_groups;
+    q.parts = std::max(1u, std::min((n_grp + FT - 1) / FT, most));
+    q.items = n_groups * q.parts;
+    blocks = (int)std::min((uint32_t)blocks, q.items);
+    q.pops = q.items + (uint32_t)blocks;        // each block's last pop finds nothing
+    return q;
+}
+
 // FP32: registers capped so that 6 workgroups (24 waves) fit a CU; the
 // pair loop needs the occupancy to hide LDS and rsqrt latency (measured:
 // 100 VGPRs / 4 waves per SIMD ran 18% slower; the collision variant, at
@@ -234,7 +381,8 @@ template <typename R, bool POT, bool ZERO_EPS, bool COLL, int TJ>
 // leapfrog step to each particle, as a separate pass over v and a would (the
 // collision branch reads other particles' velocities, so it never fuses).
 // TJ: sources per LDS tile (512, or 256 in the FP32 gravity-only kernels).
-__global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevState d, uint32_t ng, double kick_h) {
+// q: the work items (see ForceQueue).
+__global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevState d, ForceQueue q, double kick_h) {
     static_assert(TJ == 256 || TJ == TJ_MAX, "tile of 256 or 512 sources");
     using T4 = typename V4<R>::T;
     __shared__ T4 tile[TJ + 16];
@@ -262,26 +410,30 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
     constexpr bool TAIL = sizeof(R) == 4 && !COLL;
 
     for (;;) {
-        if (tid == 0) s_item = atomicAdd(&d.cnt->work_counter2, 1u);
+        // the counter wraps to 0 with the launch's last pop.  An item popped one
+        // ahead, while the block works on its last, hides the atomic but binds the
+        // item to a block that may be late: 0.40 ms as without at 16077 groups,
+        // 1.27 instead of 1.09 ms at 1914.
+        if (tid == 0) s_item = atomicInc(&d.cnt->work_counter2, q.pops - 1);
         __syncthreads();
         // the work item is the same for the whole workgroup: keep it (and all
         // per-group values derived from it) in scalar registers
         const uint32_t item = __builtin_amdgcn_readfirstlane(s_item);
         __syncthreads();
-        if (item >= ng) break;
-        const uint32_t g = __builtin_amdgcn_readfirstlane(d.order[item]);
-        const GroupInfo gi = d.grp[g];
-        const double4 cen = d.g_cen[g];
+        if (item >= q.items) break;
+        const uint32_t gpart = item % q.parts;
+        const ForceItem gi = d.force_items[item / q.parts];
+        const double4 cen = make_double4(gi.cx, gi.cy, gi.cz, 0.0);
         // FP32: an equal-mass system's particles enter the pair loop with unit
         // mass, node masses in units of that mass, the sums scaled at the end
-        const double m0 = sizeof(R) == 4 ? d.sys_m0[gi.sys] : 0.0;
+        const double m0 = sizeof(R) == 4 ? gi.m0 : 0.0;
         const bool eqm = m0 > 0.0;
         const double gscale = eqm ? d.G * m0 : d.G;
         const double inv_m0 = eqm ? 1.0 / m0 : 1.0;
-        const unsigned long long pc0 = d.g_pc_off[g], pp0 = d.g_pp_off[g];
-        const uint32_t npc = d.g_pc_len[g], npp = d.g_pp_len[g];
+        const unsigned long long pc0 = gi.pc_off, pp0 = gi.pp_off;
+        const uint32_t npc = gi.npc, npp = gi.npp;
 
-        for (uint32_t ib = 0; ib < gi.count; ib += FT) {
+        for (uint32_t ib = gpart * FT; ib < gi.count; ib += q.parts * FT) {
             const uint32_t nb = min((uint32_t)FT, gi.count - ib);
             // Waves take 64-particle chunks of the block (n_ic of them), the
             // waves left over splitting the source range (split ways).  A chunk
@@ -458,6 +610,14 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
                 __syncthreads();
             };
 
+            // the first leaves of the particle list, loaded beside the first nodes
+            uint32_t lb = 0, lc = 0;
+            if ((uint32_t)tid < npp) {
+                const uint32_t leaf = d.pp_pool[pp0 + tid];
+                lb = d.nd_begin[leaf];
+                lc = d.nd_count[leaf];
+            }
+
             // ---- node list: centre of mass and mass of each accepted node
             for (uint32_t t0 = 0; t0 < npc; t0 += TJ) {
                 const uint32_t cntt = min((uint32_t)TJ, npc - t0);
@@ -471,11 +631,13 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
             // ---- particle list: the particles of each listed leaf
             for (uint32_t l0 = 0; l0 < npp; l0 += LC) {
                 const uint32_t nl = min((uint32_t)LC, npp - l0);
-                uint32_t lc = 0, lb = 0;
-                if ((uint32_t)tid < nl) {
-                    const uint32_t leaf = d.pp_pool[pp0 + l0 + tid];
-                    lb = d.nd_begin[leaf];
-                    lc = d.nd_count[leaf];
+                if (l0 != 0) {
+                    lc = 0;
+                    if ((uint32_t)tid < nl) {
+                        const uint32_t leaf = d.pp_pool[pp0 + l0 + tid];
+                        lb = d.nd_begin[leaf];
+                        lc = d.nd_count[leaf];
+                    }
                 }
                 // exclusive scan of leaf sizes over the workgroup
                 const uint32_t inc = wave_incl_scan(lc);
@@ -585,32 +747,28 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
     }
 }
 
-__global__ void k_force_reset(DevState d) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) d.cnt->work_counter2 = 0;
-}
-
 template <typename R, bool POT, bool ZERO_EPS>
-void launch_gravity(const DevState &d, uint32_t ng, int blocks, double kick_h, hipStream_t s) {
+void launch_gravity(const DevState &d, const ForceQueue &q, int blocks, double kick_h, hipStream_t s) {
     if constexpr (sizeof(R) == 4) {
         if (d.force_tile == 256) {
-            k_force<R, POT, ZERO_EPS, false, 256><<<blocks, FT, 0, s>>>(d, ng, kick_h);
+            k_force<R, POT, ZERO_EPS, false, 256><<<blocks, FT, 0, s>>>(d, q, kick_h);
             return;
         }
     }
-    k_force<R, POT, ZERO_EPS, false, TJ_MAX><<<blocks, FT, 0, s>>>(d, ng, kick_h);
+    k_force<R, POT, ZERO_EPS, false, TJ_MAX><<<blocks, FT, 0, s>>>(d, q, kick_h);
 }
 
 template <typename R, bool POT>
-void launch(const DevState &d, uint32_t ng, int blocks, double kick_h, hipStream_t s) {
+void launch(const DevState &d, const ForceQueue &q, int blocks, double kick_h, hipStream_t s) {
     if (d.rc > 0.0) {
         if (d.eps2 == 0.0)
-            k_force<R, POT, true, true, TJ_MAX><<<blocks, FT, 0, s>>>(d, ng, 0.0);
+            k_force<R, POT, true, true, TJ_MAX><<<blocks, FT, 0, s>>>(d, q, 0.0);
         else
-            k_force<R, POT, false, true, TJ_MAX><<<blocks, FT, 0, s>>>(d, ng, 0.0);
+            k_force<R, POT, false, true, TJ_MAX><<<blocks, FT, 0, s>>>(d, q, 0.0);
     } else if (d.eps2 == 0.0) {
-        launch_gravity<R, POT, true>(d, ng, blocks, kick_h, s);
+        launch_gravity<R, POT, true>(d, q, blocks, kick_h, s);
     } else {
-        launch_gravity<R, POT, false>(d, ng, blocks, kick_h, s);
+        launch_gravity<R, POT, false>(d, q, blocks, kick_h, s);
     }
 }
 
@@ -619,14 +777,14 @@ void launch(const DevState &d, uint32_t ng, int blocks, double kick_h, hipStream
 namespace bhk {
 
 void forces(const DevState &d, uint32_t n_groups, bool fp32, bool pot, int blocks, double kick_h, hipStream_t s) {
-    k_force_reset<<<1, 64, 0, s>>>(d);
     if (n_groups == 0) return;
+    const ForceQueue q = force_queue(n_groups, (uint32_t)d.n_grp, blocks);
     if (fp32) {
-        if (pot) launch<float, true>(d, n_groups, blocks, kick_h, s);
-        else launch<float, false>(d, n_groups, blocks, kick_h, s);
+        if (pot) launch<float, true>(d, q, blocks, kick_h, s);
+        else launch<float, false>(d, q, blocks, kick_h, s);
     } else {
-        if (pot) launch<double, true>(d, n_groups, blocks, kick_h, s);
-        else launch<double, false>(d, n_groups, blocks, kick_h, s);
+        if (pot) launch<double, true>(d, q, blocks, kick_h, s);
+        else launch<double, false>(d, q, blocks, kick_h, s);
     }
 }
 

@@ -127,6 +127,16 @@ struct GroupInfo {
     uint32_t node, begin, count, sys;
 };
 
+// What the force kernel needs of a group, in the order it takes them (one
+// load instead of a chain of three: position in the order, group, system).
+struct alignas(16) ForceItem {
+    double cx, cy, cz;                  // FP32 origin
+    double m0;                          // the system's common particle mass, 0 when masses differ
+    unsigned long long pc_off, pp_off;  // list starts in the pools
+    uint32_t npc, npp;
+    uint32_t begin, count;
+};
+
 // Raw device pointers of a context, passed by value to the launchers.
 struct DevState {
     // systems
@@ -164,7 +174,7 @@ struct DevState {
     unsigned long long *g_pc_off, *g_pp_off;   // list starts in the pools (64-bit: pools exceed 2^32)
     uint32_t *g_pc_len, *g_pp_len;
     unsigned long long *g_cost;    // interactions of the group
-    uint32_t *order;               // groups by descending cost
+    ForceItem *force_items;        // [groups] by descending cost class
     uint32_t *pc_pool, *pp_pool;
     unsigned long long pc_cap, pp_cap;
     uint32_t *walk_scratch;        // per walking wave: 2 frontiers + 2 lists

@@ -394,6 +394,17 @@ __global__ void k_order_keys(DevState d, uint64_t *key, uint32_t *val) {
     }
 }
 
+// The force kernel's records in work order.
+__global__ void k_force_items(DevState d, const uint32_t *order, uint32_t ng) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= ng) return;
+    const uint32_t g = order[i];
+    const GroupInfo gi = d.grp[g];
+    const double4 c = d.g_cen[g];
+    d.force_items[i] = ForceItem{c.x, c.y, c.z, d.sys_m0[gi.sys], d.g_pc_off[g], d.g_pp_off[g], d.g_pc_len[g],
+                                 d.g_pp_len[g], gi.begin, gi.count};
+}
+
 }  // namespace
 
 namespace bhk {
@@ -423,7 +434,7 @@ void order_groups(const DevState &d, uint32_t n_groups, uint64_t *key_a, uint32_
     k_order_keys<<<blocks, 256, 0, s>>>(d, key_a, val_a);
     // the low 32 bits, the group id, ascend already: a stable sort by the class is enough
     radix_sort(key_a, val_a, key_b, val_b, n_groups, 32, 40, d.hist, d.scan_tmp, s, nullptr, 0);
-    (void)hipMemcpyAsync(d.order, val_a, (size_t)n_groups * sizeof(uint32_t), hipMemcpyDeviceToDevice, s);
+    k_force_items<<<(n_groups + 255) / 256, 256, 0, s>>>(d, val_a, n_groups);
 }
 
 }  // namespace bhk
