@@ -325,17 +325,50 @@ __device__ __forceinline__ void contact_term(uint32_t i, uint32_t j, const DevSt
 // [jb, jb + L): entries whose FP32 squared distance (the pair loop's own
 // expression) is within rcd2, a bound that rounding of the relative
 // coordinates cannot cross.  jidx holds the sorted index of each entry.
+// A term costs two dependent rounds of global loads, and the lanes' candidates
+// lie at different entries: taken one by one they were serial, and each
+// particle is a candidate of its own (64 rounds per chunk).  So i itself needs
+// no loads, the others are noted and taken side by side, in the lane's own
+// order, and entries are looked at eight together, so that their LDS reads
+// overlap.  130003 particles in 841 groups: 0.198 -> 0.137 ms per evaluation
+// (0.093 without this pass); 2^22 in 54436 groups: 3.71 -> 3.26 ms.
 template <typename R, bool POT>
 __device__ __forceinline__ void contact_pass(const typename V4<R>::T *tile, const uint32_t *jidx, int jb, int L,
                                              R xi, R yi, R zi, R eps2, R rcd2, bool on, uint32_t i,
                                              const DevState &d, double *c) {
     if (!on) return;
-    for (int k = 0; k < L; ++k) {
+    uint64_t noted = 0;          // up to four entries, 16 bits each, the first one lowest
+    int n = 0;
+    auto take = [&] {
+        for (; n > 0; --n, noted >>= 16) contact_term<POT>(i, jidx[jb + (int)(noted & 0xffff)], d, c);
+    };
+    auto r2_of = [&](int k) {
         const typename V4<R>::T s = tile[jb + k];
         const R dx = s.x - xi, dy = s.y - yi, dz = s.z - zi;
-        const R r2 = fma_r<R>(dx, dx, fma_r<R>(dy, dy, fma_r<R>(dz, dz, eps2)));
-        if (r2 <= rcd2) contact_term<POT>(i, jidx[jb + k], d, c);
+        return fma_r<R>(dx, dx, fma_r<R>(dy, dy, fma_r<R>(dz, dz, eps2)));
+    };
+    auto note = [&](int k) {
+        if (r2_of(k) <= rcd2) {
+            if (jidx[jb + k] == i) {
+                if (POT) contact_term<POT>(i, i, d, c);
+            } else {
+                noted |= (uint64_t)k << (16 * n);
+                if (++n == 4) take();
+            }
+        }
+    };
+    int k = 0;
+    for (; k + 8 <= L; k += 8) {
+        R m = r2_of(k);
+#pragma unroll
+        for (int u = 1; u < 8; ++u) m = fmin(m, r2_of(k + u));
+        if (m <= rcd2)
+#pragma unroll 1
+            for (int u = 0; u < 8; ++u) note(k + u);
     }
+#pragma unroll 1
+    for (; k < L; ++k) note(k);
+    take();
 }
 
 // Work items of the persistent blocks: an item is 256 particles of a group
