@@ -373,15 +373,23 @@ __global__ void k_adam(AdamArgs ad, const float *g) {
 }
 
 // Squared error of the network over a set, summed in FP64: per block, in a fixed order.
-__global__ void __launch_bounds__(TPB) k_sq_error(const float *__restrict__ w, const float4 *X, const float *Y,
-                                                 uint64_t n, double *part) {
+__global__ void __launch_bounds__(TPB) k_sq_error(const float *w, const float4 *X, const float *Y, uint64_t n,
+                                                 double *part) {
     __shared__ double red[TPB / 64];
+    __shared__ alignas(16) float s_net[WNET_LDS];
+    const WaveNet net = wave_net_load(w);
+    for (int k = threadIdx.x; k < WNET_LDS; k += TPB) s_net[k] = wave_net_lds_entry(w, k);
+    __syncthreads();
     double s = 0.0;
-    for (uint64_t i = (uint64_t)blockIdx.x * TPB + threadIdx.x; i < n; i += (uint64_t)gridDim.x * TPB) {
-        const float4 x = X[i];
+    for (uint64_t b = (uint64_t)blockIdx.x * TPB; b < n; b += (uint64_t)gridDim.x * TPB) {
+        const uint64_t i = b + threadIdx.x;
+        const float4 x = i < n ? X[i] : make_float4(0.f, 0.f, 0.f, 0.f);
         const float f[4] = {x.x, x.y, x.z, x.w};
-        const double e = (double)mlp_forward(w, f) - (double)Y[i];
-        s += e * e;
+        const float y = wave_net_forward(net, s_net, f);
+        if (i < n) {
+            const double e = (double)y - (double)Y[i];
+            s += e * e;
+        }
     }
     s = wave_sum(s);
     if (__lane_id() == 0) red[threadIdx.x >> 6] = s;
@@ -389,12 +397,17 @@ __global__ void __launch_bounds__(TPB) k_sq_error(const float *__restrict__ w, c
     if (threadIdx.x == 0) part[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-__global__ void k_eval(const float *__restrict__ w, const float4 *X, uint64_t n, float *out) {
-    uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const float4 x = X[i];
+__global__ void __launch_bounds__(TPB) k_eval(const float *w, const float4 *X, uint64_t n, float *out) {
+    __shared__ alignas(16) float s_net[WNET_LDS];
+    const WaveNet net = wave_net_load(w);
+    for (int k = threadIdx.x; k < WNET_LDS; k += TPB) s_net[k] = wave_net_lds_entry(w, k);
+    __syncthreads();
+    for (uint64_t b = (uint64_t)blockIdx.x * TPB; b < n; b += (uint64_t)gridDim.x * TPB) {
+        const uint64_t i = b + threadIdx.x;
+        const float4 x = i < n ? X[i] : make_float4(0.f, 0.f, 0.f, 0.f);
         const float f[4] = {x.x, x.y, x.z, x.w};
-        out[i] = mlp_forward(w, f);
+        const float y = wave_net_forward(net, s_net, f);
+        if (i < n) out[i] = y;
     }
 }
 

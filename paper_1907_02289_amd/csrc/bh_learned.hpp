@@ -94,38 +94,116 @@ __device__ __forceinline__ PairGeom pair_features(double4 com, double r2, float 
     return p;
 }
 
-// Network output in label units (lg of the relative monopole error).
-__device__ __forceinline__ float mlp_forward(const float *__restrict__ w, const float f[MLP_NIN]) {
+// The value that the network's output is compared with, for a node in the band:
+// accepted when the output is below it.
+__device__ __forceinline__ double accept_below(const PairGeom &p, double M, double A_g, double tau, double G) {
+    return lg2p(((tau * A_g) * p.d2) / (G * M));
+}
+
+// Network output in label units (lg of the relative monopole error) for 64
+// inputs at once, one per lane of a full wave, on the matrix cores.  Each sum
+// is a chain of fmaf in ascending input from its bias:
+// v_mfma_f32_32x32x2_f32 adds its two products to the accumulator as two fused
+// multiply-adds in ascending k (checked bit for bit against fmaf, subnormals
+// included), so the output has the bits of that chain.  Layer weights sit in
+// registers, loaded once per wave (lane l holds row l % 32 and column
+// 2 s + l / 32 of step s); a D tile has its unit 8 q + 4 (l / 32) + i in
+// register 4 q + i, and v_permlane32_swap of registers with neighbouring units
+// gives the next layer's B operands, units in order.  One lane per input with
+// the weights from memory was bound by them: some 340 loads per 64 nodes of a walk,
+// 72% of the waves' time spent waiting.  Walk of 2^19 particles: 1581 -> 477
+// us in 1914 groups; whole steps 33.6 -> 13.4 ms with groups of up to 64, 47.7
+// -> 25.6 ms at 2^21 particles.
+struct WaveNet {
+    float w1[2], w2[MLP_NH / 2];
+};
+
+typedef float mlp_f16 __attribute__((ext_vector_type(16)));
+
+// The weights outside the matrix operands, as the walk's blocks keep them in
+// LDS: b1, b2, w3 (32 each), then b3, mean and 1/std of the inputs, of the label.
+#define WNET_B2 MLP_NH
+#define WNET_W3 (2 * MLP_NH)
+#define WNET_REST (3 * MLP_NH)
+#define WNET_LDS (WNET_REST + 1 + 2 * MLP_NIN + 2)
+
+__device__ __forceinline__ float wave_net_lds_entry(const float *w, int k) {
+    return k < WNET_B2     ? w[MLP_B1 + k]
+           : k < WNET_W3   ? w[MLP_B2 + (k - WNET_B2)]
+           : k < WNET_REST ? w[MLP_W3 + (k - WNET_W3)]
+                           : w[MLP_B3 + (k - WNET_REST)];
+}
+
+__device__ __forceinline__ WaveNet wave_net_load(const float *w) {
+    const int row = __lane_id() & 31, half = __lane_id() >> 5;
+    WaveNet n;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) n.w1[s] = w[MLP_W1 + row * MLP_NIN + 2 * s + half];
+#pragma unroll
+    for (int s = 0; s < MLP_NH / 2; ++s) n.w2[s] = w[MLP_W2 + row * MLP_NH + 2 * s + half];
+    return n;
+}
+
+// a's upper 32 lanes against b's lower 32: (a.lo, b.lo) and (a.hi, b.hi)
+__device__ __forceinline__ void swap_halves(float &a, float &b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+
+// All 64 lanes call it together (an unused lane may hold any input).  c: the block's LDS copy (WNET_LDS floats, 16-byte aligned).
+__device__ __forceinline__ float wave_net_forward(const WaveNet &n, const float *c, const float f[MLP_NIN]) {
+    const int half4 = 4 * (__lane_id() >> 5);
+    const float *rest = c + WNET_REST;
     float x[MLP_NIN];
 #pragma unroll
     for (int k = 0; k < MLP_NIN; ++k) {
-        const float t = f[k] - w[MLP_XMEAN + k];
-        x[k] = t * w[MLP_XISTD + k];
+        const float t = f[k] - rest[1 + k];
+        x[k] = t * rest[1 + MLP_NIN + k];
     }
-    float h1[MLP_NH];
+    // B operands: x[0], x[2] those of lanes 0..31 (tile 0), x[1], x[3] those of lanes 32..63 (tile 1)
+    swap_halves(x[0], x[1]);
+    swap_halves(x[2], x[3]);
+    mlp_f16 h[2], a[2];
 #pragma unroll
-    for (int j = 0; j < MLP_NH; ++j) {
-        float a = w[MLP_B1 + j];
+    for (int r = 0; r < 16; ++r) h[0][r] = h[1][r] = c[8 * (r >> 2) + half4 + (r & 3)];
 #pragma unroll
-        for (int k = 0; k < MLP_NIN; ++k) a = fmaf(w[MLP_W1 + j * MLP_NIN + k], x[k], a);
-        h1[j] = a > 0.0f ? a : 0.0f;
+    for (int r = 0; r < 16; ++r) a[0][r] = a[1][r] = c[WNET_B2 + 8 * (r >> 2) + half4 + (r & 3)];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        h[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(n.w1[0], x[t], h[t], 0, 0, 0);
+        h[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(n.w1[1], x[2 + t], h[t], 0, 0, 0);
     }
-    float out = w[MLP_B3];
-#pragma unroll 4
-    for (int j = 0; j < MLP_NH; ++j) {
-        float a = w[MLP_B2 + j];
 #pragma unroll
-        for (int k = 0; k < MLP_NH; ++k) a = fmaf(w[MLP_W2 + j * MLP_NH + k], h1[k], a);
-        const float h2 = a > 0.0f ? a : 0.0f;
-        out = fmaf(w[MLP_W3 + j], h2, out);
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = h[t][4 * q + i] > 0.0f ? h[t][4 * q + i] : 0.0f;
+            swap_halves(v[0], v[1]);
+            swap_halves(v[2], v[3]);
+            a[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(n.w2[4 * q + 0], v[0], a[t], 0, 0, 0);
+            a[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(n.w2[4 * q + 1], v[2], a[t], 0, 0, 0);
+            a[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(n.w2[4 * q + 2], v[1], a[t], 0, 0, 0);
+            a[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(n.w2[4 * q + 3], v[3], a[t], 0, 0, 0);
+        }
     }
-    return fmaf(out, w[MLP_YSTD], w[MLP_YMEAN]);
-}
-
-// The acceptance decision for a node in the band.
-__device__ __forceinline__ bool learned_accept(const float *__restrict__ w, const PairGeom &p, double M,
-                                               double A_g, double tau, double G) {
-    const float y = mlp_forward(w, p.f);
-    const double Z = ((tau * A_g) * p.d2) / (G * M);
-    return (double)y < lg2p(Z);
+    // a lane's own node: its units 8 q + i and 8 q + 4 + i
+    float out = rest[0];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float lo[4], hi[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            lo[i] = a[0][4 * q + i];
+            hi[i] = a[1][4 * q + i];
+            swap_halves(lo[i], hi[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out = fmaf(c[WNET_W3 + 8 * q + i], lo[i] > 0.0f ? lo[i] : 0.0f, out);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out = fmaf(c[WNET_W3 + 8 * q + 4 + i], hi[i] > 0.0f ? hi[i] : 0.0f, out);
+    }
+    return fmaf(out, rest[1 + 2 * MLP_NIN + 1], rest[1 + 2 * MLP_NIN]);
 }

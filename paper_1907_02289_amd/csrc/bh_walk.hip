@@ -23,66 +23,32 @@
 namespace {
 
 constexpr int WALK_TPB = 256;
-constexpr int WALK_LFRONT = 512;    // geometric walk: frontier entries kept in LDS per wave and buffer
+constexpr int WALK_LFRONT = 512;    // frontier entries kept in LDS per wave and buffer
 
-// doubled distance from the doubled coordinate C to [gl, gh]
-__device__ __forceinline__ int64_t gap2(int64_t C, int64_t gl, int64_t gh) {
-    int64_t da = 0;
-    da = (2 * gl - C > da) ? 2 * gl - C : da;
-    da = (C - 2 * gh > da) ? C - 2 * gh : da;
-    return da;
-}
+// The opening test, in 32-bit integers with the squared distance summed in
+// FP64: every doubled coordinate and gap is below 2^24 and every square below
+// 2^47, so each step is exact and the decision is that of 64-bit integers, bit
+// for bit, in about half the instructions.
+__device__ __forceinline__ int gap2(int C, int gl2, int gh2) { return max(0, max(gl2 - C, C - gh2)); }
 
 __device__ __forceinline__ bool accept_cell(int4 glo, int4 ghi, int Lx, int Ly, int Lz, int level, double th2,
-                                            bool periodic = false) {
-    const int64_t s = (int64_t)1 << (BH_MAXLEVEL - level);
-    const int64_t L[3] = {Lx, Ly, Lz};
-    const int64_t gl[3] = {glo.x, glo.y, glo.z}, gh[3] = {ghi.x, ghi.y, ghi.z};
-    constexpr int64_t TURN2 = (int64_t)2 << BH_MAXLEVEL;    // one turn of phi, doubled units
-    bool disjoint = false;
-    int64_t d2 = 0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        disjoint |= (L[a] + s <= gl[a]) || (L[a] >= gh[a]);
-        int64_t C = 2 * L[a] + s;
-        int64_t da = gap2(C, gl[a], gh[a]);
-        if (a == 0 && periodic) {
-            const int64_t dm = gap2(C - TURN2, gl[a], gh[a]), dp = gap2(C + TURN2, gl[a], gh[a]);
-            da = dm < da ? dm : da;
-            da = dp < da ? dp : da;
-        }
-        d2 += da * da;
-    }
-    const int64_t s2 = (2 * s) * (2 * s);
-    return disjoint && ((double)s2 < th2 * (double)d2);
-}
-
-// The same test for the geometric walk, in 32-bit integers with the squared
-// distance summed in FP64: every doubled coordinate and gap is below 2^24
-// and every square below 2^47, so each step is exact and the decision is
-// the one above, bit for bit, in about half the instructions.
-__device__ __forceinline__ int gap2_i32(int C, int gl2, int gh2) {
-    return max(0, max(gl2 - C, C - gh2));
-}
-
-__device__ __forceinline__ bool accept_cell_geo(int4 glo, int4 ghi, int Lx, int Ly, int Lz, int level, double th2,
-                                                bool periodic) {
+                                            bool periodic) {
     const int s = 1 << (BH_MAXLEVEL - level);
     const int L[3] = {Lx, Ly, Lz};
     const int gl[3] = {glo.x, glo.y, glo.z}, gh[3] = {ghi.x, ghi.y, ghi.z};
-    constexpr int TURN2 = 2 << BH_MAXLEVEL;
+    constexpr int TURN2 = 2 << BH_MAXLEVEL;                 // one turn of phi, doubled units
     bool disjoint = false;
     double d2 = 0.0;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         disjoint |= (L[a] + s <= gl[a]) || (L[a] >= gh[a]);
         const int C = 2 * L[a] + s;
-        int da = gap2_i32(C, 2 * gl[a], 2 * gh[a]);
+        int da = gap2(C, 2 * gl[a], 2 * gh[a]);
         if (a == 0 && periodic)
-            da = min(da, min(gap2_i32(C - TURN2, 2 * gl[a], 2 * gh[a]), gap2_i32(C + TURN2, 2 * gl[a], 2 * gh[a])));
+            da = min(da, min(gap2(C - TURN2, 2 * gl[a], 2 * gh[a]), gap2(C + TURN2, 2 * gl[a], 2 * gh[a])));
         d2 = fma((double)da, (double)da, d2);
     }
-    const double s2 = (double)(4 * s) * (double)s;      // (2 s)^2
+    const double s2 = (double)(4 * s) * (double)s;          // (2 s)^2
     return disjoint && (s2 < th2 * d2);
 }
 
@@ -109,37 +75,36 @@ __device__ __forceinline__ uint32_t wave_excl_small(uint32_t v, uint32_t &tot) {
 struct GroupCtx {
     int4 glo, ghi;
     double4 cen;
-    double rad, amin, Msys, S;
+    double rad, amin, Msys;
 };
 
-// Acceptance of node v for a group.  GEOMETRIC: the theta test.  LEARNED:
+// Node v for a group under the learned and the enumerating rule.  LEARNED:
 // below theta_min accept, at or above theta_max open, in between the network
 // (single-particle nodes accepted, nodes above the count cap: the theta test).
 // ENUMERATE: the theta_min test; *cand reports whether (group, v) lies in the
-// band and is a training candidate.
-// GEO: the kernel instance that serves only the geometric rule, without the
-// registers of the network inference (the other instance takes the rule from
-// d.walk_mode).
-template <bool GEO>
-__device__ __forceinline__ bool decide(const DevState &d, const GroupCtx &gc, uint32_t v, int4 wr, bool *cand) {
+// band and is a training candidate.  For NETWORK f and below are the network's
+// inputs and the value its output has to stay below.
+enum Verdict { OPEN, ACCEPT, NETWORK };
+
+__device__ __forceinline__ Verdict judge(const DevState &d, const GroupCtx &gc, uint32_t v, int4 wr, bool *cand,
+                                         float f[MLP_NIN], double *below) {
     const int level = (int)((uint32_t)wr.x >> 24);
     const int Lx = wr.x & 0xffffff, Ly = wr.y & 0xffffff, Lz = wr.z;
-    *cand = false;
-    if (GEO) return accept_cell_geo(gc.glo, gc.ghi, Lx, Ly, Lz, level, d.th2, d.cyl_r > 0.0);
-    if (d.walk_mode == WALK_GEOMETRIC) return accept_cell(gc.glo, gc.ghi, Lx, Ly, Lz, level, d.th2, d.cyl_r > 0.0);
-    if (accept_cell(gc.glo, gc.ghi, Lx, Ly, Lz, level, d.th2_min)) return true;
-    if (!accept_cell(gc.glo, gc.ghi, Lx, Ly, Lz, level, d.th2_max)) return false;
+    if (accept_cell(gc.glo, gc.ghi, Lx, Ly, Lz, level, d.th2_min, false)) return ACCEPT;
+    if (!accept_cell(gc.glo, gc.ghi, Lx, Ly, Lz, level, d.th2_max, false)) return OPEN;
     const uint32_t cnt = d.nd_count[v];
     if (d.walk_mode == WALK_ENUMERATE) {
         *cand = cnt >= 2 && cnt <= d.count_cap;
-        return false;
+        return OPEN;
     }
-    if (cnt == 1) return true;
-    if (cnt > d.count_cap) return accept_cell(gc.glo, gc.ghi, Lx, Ly, Lz, level, d.th2);
+    if (cnt == 1) return ACCEPT;
+    if (cnt > d.count_cap) return accept_cell(gc.glo, gc.ghi, Lx, Ly, Lz, level, d.th2, false) ? ACCEPT : OPEN;
     const double4 mom = d.nd_mom[v];
     const PairGeom pg =
         pair_features(mom, box_ratio2(gc.glo, gc.ghi, Lx, Ly, Lz, level), d.nd_qn[v], gc.cen, gc.rad, gc.Msys);
-    return learned_accept(d.mlp, pg, mom.w, gc.amin, d.tau, d.G);
+    for (int k = 0; k < MLP_NIN; ++k) f[k] = pg.f[k];
+    *below = accept_below(pg, mom.w, gc.amin, d.tau, d.G);
+    return NETWORK;
 }
 
 // Persistent blocks of four waves, one group per wave and round.  What
@@ -162,6 +127,9 @@ __device__ __forceinline__ bool decide(const DevState &d, const GroupCtx &gc, ui
 // 863 -> 100 us, 64 Plummer spheres 878 -> 230 us; with 60,426 groups of
 // 10^4-entry lists (2^24, theta 0.0865) the visits themselves take the time,
 // 5.2 -> 4.9 ms.
+// GEO: the instance of the geometric rule, without the registers of the
+// network.  The other one has 248 (two waves per SIMD): held to 168 or 128 its
+// walks took 3% and 10% longer.
 template <bool GEO>
 __global__ void __launch_bounds__(WALK_TPB, (GEO ? 8 : 1)) k_walk(DevState d) {
     constexpr uint32_t WPB = WALK_TPB / 64;
@@ -176,13 +144,19 @@ __global__ void __launch_bounds__(WALK_TPB, (GEO ? 8 : 1)) k_walk(DevState d) {
     uint32_t *ppb = pcb + P;
     const uint32_t ng = d.cnt->n_groups;
     const uint32_t n_nodes = d.cnt->lvl_off[BH_NLEVELS];
-    // geometric walk: the first WALK_LFRONT entries of each frontier live in
-    // LDS, the rest at the same index in the wave's global scratch
-    uint32_t *la = nullptr, *lb = nullptr;
-    if constexpr (GEO) {
-        __shared__ uint32_t lfront[WPB][2][WALK_LFRONT];
-        la = lfront[wib][0];
-        lb = lfront[wib][1];
+    // the first WALK_LFRONT entries of each frontier live in LDS, the rest at
+    // the same index in the wave's global scratch
+    __shared__ uint32_t lfront[WPB][2][WALK_LFRONT];
+    uint32_t *la = lfront[wib][0], *lb = lfront[wib][1];
+    const bool learned = !GEO && d.walk_mode == WALK_LEARNED;
+    WaveNet net;
+    __shared__ alignas(16) float s_net[GEO ? 1 : WNET_LDS];
+    if constexpr (!GEO) {
+        if (learned) {
+            net = wave_net_load(d.mlp);
+            for (int k = threadIdx.x; k < WNET_LDS; k += WALK_TPB) s_net[k] = wave_net_lds_entry(d.mlp, k);
+        }
+        __syncthreads();
     }
     __shared__ uint32_t s_len[WPB][2];             // list lengths of the block's four groups
     __shared__ unsigned long long s_at[2];         // the block's starts in the two pools
@@ -208,20 +182,16 @@ __global__ void __launch_bounds__(WALK_TPB, (GEO ? 8 : 1)) k_walk(DevState d) {
             GroupCtx gc;
             gc.glo = d.g_lo[g];
             gc.ghi = d.g_hi[g];
-            if (!GEO && d.walk_mode != WALK_GEOMETRIC) {
+            if constexpr (!GEO) {
                 gc.cen = d.g_cen[g];
                 gc.rad = d.g_rad[g];
-                gc.amin = d.walk_mode == WALK_LEARNED ? d.g_amin[g] : 0.0;
+                gc.amin = learned ? d.g_amin[g] : 0.0;
                 gc.Msys = d.nd_mom[gi.sys].w;
-                gc.S = (double)(1u << BH_MAXLEVEL) / d.box[gi.sys].w;
             }
             uint32_t *cur = fa, *nxt = fb;
             uint32_t *lcur = la, *lnxt = lb;
-            if (lane == 0) {
-                if constexpr (GEO) lcur[0] = gi.sys;  // root of the group's system
-                else cur[0] = gi.sys;
-            }
-            __threadfence_block();
+            if (lane == 0) lcur[0] = gi.sys;         // root of the group's system
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             uint32_t ncur = 1;
             unsigned long long pp_lane = 0;          // this lane's share, summed once per group
             bool ovf = false, bound = false;
@@ -239,8 +209,7 @@ __global__ void __launch_bounds__(WALK_TPB, (GEO ? 8 : 1)) k_walk(DevState d) {
                 }
                 uint32_t nnext = 0;
                 auto front = [&](uint32_t k) -> uint32_t {
-                    if constexpr (GEO) return k < (uint32_t)WALK_LFRONT ? lcur[k] : cur[k];
-                    else return cur[k];
+                    return k < (uint32_t)WALK_LFRONT ? lcur[k] : cur[k];
                 };
                 uint32_t v_next = (uint32_t)lane < ncur ? front(lane) : 0u;
                 int4 wr_next = (uint32_t)lane < ncur ? d.nd_walk[v_next] : make_int4(0, 0, 0, 0);
@@ -256,7 +225,20 @@ __global__ void __launch_bounds__(WALK_TPB, (GEO ? 8 : 1)) k_walk(DevState d) {
                     }
                     const int nch = (int)((uint32_t)wr.y >> 24);
                     bool is_cand = false;
-                    const bool acc = valid && decide<GEO>(d, gc, v, wr, &is_cand);
+                    bool acc;
+                    if constexpr (GEO) {
+                        acc = valid && accept_cell(gc.glo, gc.ghi, wr.x & 0xffffff, wr.y & 0xffffff, wr.z,
+                                                   (int)((uint32_t)wr.x >> 24), d.th2, d.cyl_r > 0.0);
+                    } else {
+                        float f[MLP_NIN] = {0.0f, 0.0f, 0.0f, 0.0f};
+                        double below = 0.0;
+                        const Verdict vd = valid ? judge(d, gc, v, wr, &is_cand, f, &below) : OPEN;
+                        acc = vd == ACCEPT;
+                        if (__ballot(vd == NETWORK)) {
+                            const float y = wave_net_forward(net, s_net, f);
+                            if (vd == NETWORK) acc = (double)y < below;
+                        }
+                    }
                     if constexpr (!GEO) {
                         is_cand = is_cand && valid && record;
                         const uint64_t mc = __ballot(is_cand);
@@ -281,23 +263,20 @@ __global__ void __launch_bounds__(WALK_TPB, (GEO ? 8 : 1)) k_walk(DevState d) {
                     npp += (uint32_t)__popcll(mpp);
                     uint32_t tot;
                     const uint32_t o = nnext + wave_excl_small(nopen, tot);
-                    for (uint32_t c = 0; c < nopen; ++c)
-                        if constexpr (GEO) {
-                            const uint32_t q = o + c;
-                            if (q < (uint32_t)WALK_LFRONT) lnxt[q] = (uint32_t)wr.w + c;
-                            else if (q < F) nxt[q] = (uint32_t)wr.w + c;
-                        } else if (o + c < F) {
-                            nxt[o + c] = (uint32_t)wr.w + c;
-                        }
+                    for (uint32_t c = 0; c < nopen; ++c) {
+                        const uint32_t q = o + c;
+                        if (q < (uint32_t)WALK_LFRONT) lnxt[q] = (uint32_t)wr.w + c;
+                        else if (q < F) nxt[q] = (uint32_t)wr.w + c;
+                    }
                     nnext += tot;
                 }
                 if (nnext > F || (!enumerate && (npc > P || npp > P))) ovf = true;
                 // the next frontier is read by other lanes of this wave than wrote it: LDS
                 // accesses of a wave complete in order; entries in global memory need the wait
-                if (!GEO || nnext > (uint32_t)WALK_LFRONT) __threadfence_block();
+                if (nnext > (uint32_t)WALK_LFRONT) __threadfence_block();
                 else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 uint32_t *t = cur; cur = nxt; nxt = t;
-                if constexpr (GEO) { t = lcur; lcur = lnxt; lnxt = t; }
+                t = lcur; lcur = lnxt; lnxt = t;
                 ncur = nnext;
             }
             if (bound) {
