@@ -184,145 +184,177 @@ __global__ void __launch_bounds__(TPB) k_stats_final(const double *part, uint64_
     }
 }
 
-// Gradient of a batch.  An earlier form wrote each sample's activations to
-// memory and gave each of the 1249 parameters one thread that read them all
-// in turn: 963 us for 4096 samples, a serial chain of 4096 dependent
-// multiply-adds on 20 wavefronts.  Here a block takes 64 samples at a time
-// through forward, backward and the sum over its samples without leaving the
-// CU: one sample per lane, an eighth of each hidden layer's units per wave
-// and half, activations in LDS (rows of 65 floats: lanes of one row and rows
-// of one lane both fall in distinct banks).  The 32 x 32 gradient of the
-// second layer is a contraction over samples and runs on the matrix cores
-// (v_mfma_f32_32x32x2_f32, FP32 products and sums, 16 samples per wave), the
-// other 225 sums take a thread each.  At most GRAD_BLOCKS blocks, so that
-// k_grad_final reads at most that many partial sums per parameter.
-// Forward and backward of a sample round exactly as the one-thread form did.
-// 4096 samples: 969 + 30 us before (gradient sums, forward and backward), 12 + 3.4 us now;
-// 100 training steps of 4096 rows 101.3 -> 1.85 ms.
+// Gradient of a batch.  A block takes 64 samples at a time through forward,
+// backward and the sum over its samples without leaving the CU.  What bounds
+// it is a chain of latencies: a batch of 4096 is 64 blocks, one per CU.  So
+// everything that is a contraction runs on the matrix cores
+// (v_mfma_f32_32x32x2_f32, 64 cycles for 2048 multiply-adds of one wave):
+// waves 0 and 1 take 32 samples each, units by samples, through both layers
+// forward and the second one backward, with the layouts of wave_net_forward;
+// then they sum the 32 x 32 gradient of the second layer over their samples,
+// while waves 2 and 3 take the other 225 sums, one or two per thread, from LDS
+// (rows of 65 floats: lanes of one row and rows of one lane both fall in
+// distinct banks).  At most GRAD_BLOCKS blocks, so that k_grad_final reads at
+// most that many partial sums per parameter.  Forward and backward of a sample
+// are chains of fmaf in ascending unit, as with one thread per sample.
+// 4096 samples: one thread per parameter over the batch 969 + 30 us (sums,
+// forward and backward); one lane per sample with scalar weight loads 12.6 us;
+// now 10.8 us, some 8 of them launch, loads of rows and weights, and stores.
+// 100 training steps of 4096 rows 101.3 -> 1.79 (lanes) -> 1.56 ms.
 constexpr int GS = 64;              // samples per block and round
 constexpr int GLD = GS + 1;         // LDS row of one unit over the samples
 constexpr int GRAD_BLOCKS = 256;
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-__global__ void __launch_bounds__(TPB) k_grad_part(const float *__restrict__ w, const float4 *X, const float *Y,
+__global__ void __launch_bounds__(TPB) k_grad_part(const float *w, const float4 *X, const float *Y,
                                                   const uint32_t *idx, uint32_t B, float *part, double *lossp) {
     __shared__ float xs[4][GLD], h1[MLP_NH][GLD], h2[MLP_NH][GLD], g1[MLP_NH][GLD], g2[MLP_NH][GLD], gos[GS];
-    __shared__ float red[4][MLP_NH * MLP_NH];
+    __shared__ float red[2][MLP_NH * MLP_NH];
+    __shared__ double lred[2];
+    __shared__ alignas(16) float s_net[WNET_LDS];
+    const int t = threadIdx.x;
     const int lane = __lane_id();
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    constexpr int U = MLP_NH / 4;   // units of a layer per wave
-    const int u0 = wv * U;
-    // this thread's share of the 225 sums outside W2: operand rows a * b (b null: a alone)
-    const int t = threadIdx.x;
+    const bool front = wv < 2;
+    const int col = lane & 31, half = lane >> 5;
+    const float *rest = s_net + WNET_REST;
+    WaveNet net;
+    float w2t[MLP_NH / 2];          // the second layer transposed, for the way back
+    if (front) {
+        net = wave_net_load(w);
+#pragma unroll
+        for (int s = 0; s < MLP_NH / 2; ++s) w2t[s] = w[MLP_W2 + (2 * s + half) * MLP_NH + col];
+    }
+    for (int k = t; k < WNET_LDS; k += TPB) s_net[k] = wave_net_lds_entry(w, k);
+    // the sums outside W2: thread k of waves 2 and 3 has W1's entry k and one of the rest, operand rows a * b
+    // (b null: a alone)
+    const int k2 = t - 128;
     const float *ra = gos, *rb = nullptr;
     int dst = -1;
-    if (t < 128) {
-        dst = MLP_W1 + t;
-        ra = g1[t >> 2];
-        rb = xs[t & 3];
-    } else if (t < 160) {
-        dst = MLP_B1 + (t - 128);
-        ra = g1[t - 128];
-    } else if (t < 192) {
-        dst = MLP_B2 + (t - 160);
-        ra = g2[t - 160];
-    } else if (t < 224) {
-        dst = MLP_W3 + (t - 192);
-        rb = h2[t - 192];
-    } else if (t == 224) {
-        dst = MLP_B3;
+    if (k2 >= 0) {
+        if (k2 < 32) {
+            dst = MLP_B1 + k2;
+            ra = g1[k2];
+        } else if (k2 < 64) {
+            dst = MLP_B2 + (k2 - 32);
+            ra = g2[k2 - 32];
+        } else if (k2 < 96) {
+            dst = MLP_W3 + (k2 - 64);
+            rb = h2[k2 - 64];
+        } else if (k2 == 96) {
+            dst = MLP_B3;
+        }
     }
-    float sum = 0.0f;
+    float sum = 0.0f, sum1 = 0.0f;
     double loss = 0.0;
-    floatx16 acc = {};
+    mlp_f16 acc = {};
     const uint32_t rounds = (B + GS - 1) / GS;
     for (uint32_t c = blockIdx.x; c < rounds; c += gridDim.x) {
-        const uint32_t b = c * GS + lane;
-        const bool valid = b < B;
+        const int n = 32 * wv + col;
+        const uint32_t b = c * GS + n;
+        const bool valid = front && b < B;
         const uint32_t i = valid ? (idx ? idx[b] : b) : 0u;
         const float4 xx = X[i];
-        const float f[4] = {xx.x, xx.y, xx.z, xx.w};
-        float x[4];
+        const float yy = Y[i];
+        __syncthreads();                // s_net is there; the last round's sums are done
+        if (front) {
+            const float f[4] = {xx.x, xx.y, xx.z, xx.w};
+            float x[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float tt = f[k] - w[MLP_XMEAN + k];
-            x[k] = valid ? tt * w[MLP_XISTD + k] : 0.0f;        // lanes past the batch add exact zeros
-            if (wv == 0) xs[k][lane] = x[k];
-        }
+            for (int k = 0; k < 4; ++k) {
+                const float tt = f[k] - rest[1 + k];
+                x[k] = valid ? tt * rest[1 + MLP_NIN + k] : 0.0f;   // columns past the batch add exact zeros
+                if (half == 0) xs[k][n] = x[k];
+            }
+            mlp_f16 h, a;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float a = w[MLP_B1 + u0 + u];
+            for (int r = 0; r < 16; ++r) {
+                const int u = 8 * (r >> 2) + 4 * half + (r & 3);
+                h[r] = s_net[u];
+                a[r] = s_net[WNET_B2 + u];
+            }
+            h = __builtin_amdgcn_mfma_f32_32x32x2f32(net.w1[0], half ? x[1] : x[0], h, 0, 0, 0);
+            h = __builtin_amdgcn_mfma_f32_32x32x2f32(net.w1[1], half ? x[3] : x[2], h, 0, 0, 0);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) a = fmaf(w[MLP_W1 + (u0 + u) * 4 + k], x[k], a);
-            h1[u0 + u][lane] = a > 0.0f ? a : 0.0f;
+            for (int r = 0; r < 16; ++r) {
+                h[r] = h[r] > 0.0f ? h[r] : 0.0f;
+                h1[8 * (r >> 2) + 4 * half + (r & 3)][n] = h[r];
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float v[4] = {h[4 * q], h[4 * q + 1], h[4 * q + 2], h[4 * q + 3]};
+                a = wave_net_steps(net.w2 + 4 * q, v, a);
+            }
+            float out = rest[0];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float lo[4], hi[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int r = 4 * q + k;
+                    a[r] = a[r] > 0.0f ? a[r] : 0.0f;
+                    h2[8 * q + 4 * half + k][n] = a[r];
+                    lo[k] = hi[k] = a[r];
+                    swap_halves(lo[k], hi[k]);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k) out = fmaf(s_net[WNET_W3 + 8 * q + k], lo[k], out);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) out = fmaf(s_net[WNET_W3 + 8 * q + 4 + k], hi[k], out);
+            }
+            // loss on the normalised label: (out - (y - mean) / sd)^2, averaged over the batch
+            const float yt = (yy - rest[1 + 2 * MLP_NIN]) / rest[2 + 2 * MLP_NIN];
+            const float r = out - yt;
+            const float go = valid ? 2.0f * r / (float)B : 0.0f;
+            if (half == 0) {
+                gos[n] = go;
+                const float r2 = r * r;
+                if (valid) loss += (double)r2;
+            }
+            mlp_f16 gk = {};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float v[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int u = 8 * q + 4 * half + k;
+                    v[k] = a[4 * q + k] > 0.0f ? go * s_net[WNET_W3 + u] : 0.0f;
+                    g2[u][n] = v[k];
+                }
+                gk = wave_net_steps(w2t + 4 * q, v, gk);
+            }
+#pragma unroll
+            for (int k = 0; k < 16; ++k) g1[8 * (k >> 2) + 4 * half + (k & 3)][n] = h[k] > 0.0f ? gk[k] : 0.0f;
         }
         __syncthreads();
-        float a2[U];
+        if (front) {
+            // W2: sum over this wave's 32 samples, two per instruction
 #pragma unroll
-        for (int u = 0; u < U; ++u) a2[u] = w[MLP_B2 + u0 + u];
-#pragma unroll 4
-        for (int k = 0; k < MLP_NH; ++k) {
-            const float hk = h1[k][lane];
-#pragma unroll
-            for (int u = 0; u < U; ++u) a2[u] = fmaf(w[MLP_W2 + (u0 + u) * MLP_NH + k], hk, a2[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            a2[u] = a2[u] > 0.0f ? a2[u] : 0.0f;
-            h2[u0 + u][lane] = a2[u];
-        }
-        __syncthreads();
-        float out = w[MLP_B3];
+            for (int st = 0; st < 16; ++st) {
+                const int sm = 32 * wv + 2 * st + half;
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(g2[col][sm], h1[col][sm], acc, 0, 0, 0);
+            }
+        } else {
+            const float *r1 = g1[k2 >> 2], *x1 = xs[k2 & 3];
 #pragma unroll 8
-        for (int j = 0; j < MLP_NH; ++j) out = fmaf(w[MLP_W3 + j], h2[j][lane], out);
-        // loss on the normalised label: (out - (y - mean) / sd)^2, averaged over the batch
-        const float yt = (Y[i] - w[MLP_YMEAN]) / w[MLP_YSTD];
-        const float r = out - yt;
-        const float go = valid ? 2.0f * r / (float)B : 0.0f;
-        if (wv == 0) {
-            gos[lane] = go;
-            const float r2 = r * r;
-            if (valid) loss += (double)r2;
+            for (int sm = 0; sm < GS; ++sm) {
+                sum1 = fmaf(r1[sm], x1[sm], sum1);
+                sum = rb ? fmaf(ra[sm], rb[sm], sum) : sum + ra[sm];
+            }
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) g2[u0 + u][lane] = a2[u] > 0.0f ? go * w[MLP_W3 + u0 + u] : 0.0f;
-        __syncthreads();
-        float gk[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) gk[u] = 0.0f;
-#pragma unroll 4
-        for (int j = 0; j < MLP_NH; ++j) {
-            const float gj = g2[j][lane];
-#pragma unroll
-            for (int u = 0; u < U; ++u) gk[u] = fmaf(w[MLP_W2 + j * MLP_NH + u0 + u], gj, gk[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) g1[u0 + u][lane] = h1[u0 + u][lane] > 0.0f ? gk[u] : 0.0f;
-        __syncthreads();
-        // W2: sum over this wave's 16 samples, two per instruction
-#pragma unroll
-        for (int st = 0; st < GS / 8; ++st) {
-            const int sm = 16 * wv + 2 * st + (lane >> 5);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(g2[lane & 31][sm], h1[lane & 31][sm], acc, 0, 0, 0);
-        }
-        if (dst >= 0) {
-#pragma unroll 8
-            for (int sm = 0; sm < GS; ++sm) sum = rb ? fmaf(ra[sm], rb[sm], sum) : sum + ra[sm];
-        }
-        __syncthreads();
     }
-    // matrix layout: element r of a lane is row 8 (r / 4) + r % 4 + 4 (lane / 32), column lane % 32
+    if (front) {
+        // matrix layout: element r of a lane is row 8 (r / 4) + r % 4 + 4 (lane / 32), column lane % 32
 #pragma unroll
-    for (int r = 0; r < 16; ++r) red[wv][(8 * (r >> 2) + (r & 3) + 4 * (lane >> 5)) * MLP_NH + (lane & 31)] = acc[r];
+        for (int r = 0; r < 16; ++r) red[wv][(8 * (r >> 2) + (r & 3) + 4 * half) * MLP_NH + col] = acc[r];
+        loss = wave_sum(loss);
+        if (lane == 0) lred[wv] = loss;
+    }
     __syncthreads();
     float *o = part + (size_t)blockIdx.x * MLP_NTRAIN;
-    for (int e = t; e < MLP_NH * MLP_NH; e += TPB) o[MLP_W2 + e] = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
+    for (int e = t; e < MLP_NH * MLP_NH; e += TPB) o[MLP_W2 + e] = red[0][e] + red[1][e];
+    if (!front) o[MLP_W1 + k2] = sum1;
     if (dst >= 0) o[dst] = sum;
-    if (wv == 0) {
-        loss = wave_sum(loss);
-        if (lane == 0) lossp[blockIdx.x] = loss;
-    }
+    if (t == 0) lossp[blockIdx.x] = lred[0] + lred[1];
 }
 
 // Adam step of one parameter (Kingma & Ba 2015); c1, c2 = 1 - beta^t.

@@ -151,6 +151,16 @@ __device__ __forceinline__ void swap_halves(float &a, float &b) {
     b = __uint_as_float(r[1]);
 }
 
+// Eight units of a D tile (registers 4 q .. 4 q + 3 of every lane) times their four steps of a layer.
+__device__ __forceinline__ mlp_f16 wave_net_steps(const float *w, float v[4], mlp_f16 a) {
+    swap_halves(v[0], v[1]);
+    swap_halves(v[2], v[3]);
+    a = __builtin_amdgcn_mfma_f32_32x32x2f32(w[0], v[0], a, 0, 0, 0);
+    a = __builtin_amdgcn_mfma_f32_32x32x2f32(w[1], v[2], a, 0, 0, 0);
+    a = __builtin_amdgcn_mfma_f32_32x32x2f32(w[2], v[1], a, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(w[3], v[3], a, 0, 0, 0);
+}
+
 // All 64 lanes call it together (an unused lane may hold any input).  c: the block's LDS copy (WNET_LDS floats, 16-byte aligned).
 __device__ __forceinline__ float wave_net_forward(const WaveNet &n, const float *c, const float f[MLP_NIN]) {
     const int half4 = 4 * (__lane_id() >> 5);
@@ -181,12 +191,7 @@ __device__ __forceinline__ float wave_net_forward(const WaveNet &n, const float 
             float v[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] = h[t][4 * q + i] > 0.0f ? h[t][4 * q + i] : 0.0f;
-            swap_halves(v[0], v[1]);
-            swap_halves(v[2], v[3]);
-            a[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(n.w2[4 * q + 0], v[0], a[t], 0, 0, 0);
-            a[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(n.w2[4 * q + 1], v[2], a[t], 0, 0, 0);
-            a[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(n.w2[4 * q + 2], v[1], a[t], 0, 0, 0);
-            a[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(n.w2[4 * q + 3], v[3], a[t], 0, 0, 0);
+            a[t] = wave_net_steps(n.w2 + 4 * q, v, a[t]);
         }
     }
     // a lane's own node: its units 8 q + i and 8 q + 4 + i
