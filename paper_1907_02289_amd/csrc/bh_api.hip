@@ -45,6 +45,7 @@ struct bh_ctx {
     int mom_deep = 0, mom_top = -1;      // launches of a moment pass on the current tree
     uint64_t n_pc = 0, n_pp = 0, interactions = 0;
     int n_grp_used = 64;
+    bool walk_reset = false;             // the walk's counters are clear (since the last build)
 
     // capacities
     uint32_t n_cap = 0, node_cap = 0, sys_cap = 0;
@@ -57,7 +58,6 @@ struct bh_ctx {
     DevBuf key, key_tmp, val, val_tmp, hist, scan_tmp;
     DevBuf nd_prefix, nd_begin, nd_count, nd_first, nd_meta, nd_walk, nd_mom, nd_quad, tree_cnt;
     DevBuf gmark, grp, g_lo, g_hi, g_cen, g_pc_off, g_pc_len, g_pp_off, g_pp_len, g_cost, force_items;
-    DevBuf gkey_a, gkey_b, gval_a, gval_b;
     DevBuf pc_pool, pp_pool, walk_scratch, counters;
     DevBuf pos_b, nd_mom_b, nd_drift;    // drift monitor: build snapshot and per-node drift
 
@@ -82,10 +82,11 @@ struct bh_ctx {
     DevBuf direct_part;
 
     // HIP graphs of the launch-bound part of a list-reusing step (kick-drift +
-    // the per-level moment refresh), replayed on an internal stream fenced
-    // with events against the caller's stream.  Two cached instances: the
-    // sorted buffers alternate between two allocations from one tree build to
-    // the next.
+    // the per-level moment refresh), captured on an internal stream, since the
+    // caller's may be the default one, and launched on the caller's (fenced
+    // into the internal stream with two events instead, a step of 3001 particles
+    // took 13 us longer).  Two cached instances: the sorted buffers alternate
+    // between two allocations from one tree build to the next.
     struct GraphEntry {
         DevState key;
         double h = 0, dt = 0;
@@ -103,7 +104,6 @@ struct bh_ctx {
     GraphEntry graphs[2];
     int graph_next = 0;
     hipStream_t gs = nullptr;
-    hipEvent_t fence_a = nullptr, fence_b = nullptr;
     int64_t graph_replays = 0, graph_captures = 0;
 
     DevState d{};
@@ -343,7 +343,7 @@ bh_status ensure_particles(bh_ctx *c, uint32_t n) {
     HIPCHK(c, grow(c->key_tmp, u8));
     HIPCHK(c, grow(c->val, u4));
     HIPCHK(c, grow(c->val_tmp, u4));
-    HIPCHK(c, grow(c->hist, bhk::radix_hist_words(cap) * 4));
+    HIPCHK(c, grow(c->hist, std::max(bhk::radix_hist_words(cap), bhk::ORDER_WORDS) * 4));
     HIPCHK(c, grow(c->scan_tmp, SCAN_TMP_WORDS * 4));
     HIPCHK(c, grow(c->tree_cnt, bhk::tree_cnt_words(cap) * 4));
     HIPCHK(c, grow(c->gmark, u4));
@@ -356,10 +356,6 @@ bh_status ensure_particles(bh_ctx *c, uint32_t n) {
     HIPCHK(c, grow(c->g_pp_off, u8));
     HIPCHK(c, grow(c->g_pp_len, u4));
     HIPCHK(c, grow(c->g_cost, u8));
-    HIPCHK(c, grow(c->gkey_a, u8));
-    HIPCHK(c, grow(c->gkey_b, u8));
-    HIPCHK(c, grow(c->gval_a, u4));
-    HIPCHK(c, grow(c->gval_b, u4));
     c->n_cap = cap;
     STCHK(ensure_drift(c));
     if (c->P.criterion == BH_OPEN_LEARNED) {
@@ -448,6 +444,7 @@ bh_status rebuild(bh_ctx *c, hipStream_t s, bool from_caller) {
     refresh_state(c);
     ev_begin(c, EV_KEYS, s);
     bhk::reset_flags(c->d, s);
+    c->walk_reset = true;
     if (from_caller) bhk::load_systems(c->d, s);
     bhk::root_box_keys(c->d, s);
     bhk::permute(c->d, s);
@@ -456,6 +453,9 @@ bh_status rebuild(bh_ctx *c, hipStream_t s, bool from_caller) {
         ev_begin(c, EV_TREE, s);
         bhk::build_octree(c->d, s);
         ev_end(c, EV_TREE, s);
+        ev_begin(c, EV_GROUPS, s);
+        bhk::make_groups(c->d, s);
+        ev_end(c, EV_GROUPS, s);
         STCHK(read_counters(c, s));
         if (c->h_cnt->flags[FLAG_NONFINITE]) {
             c->tree_valid = c->lists_valid = false;
@@ -476,6 +476,7 @@ bh_status rebuild(bh_ctx *c, hipStream_t s, bool from_caller) {
     }
     c->n_nodes = c->h_cnt->lvl_off[BH_NLEVELS];
     c->max_level = c->h_cnt->max_level;
+    c->n_groups = c->h_cnt->n_groups;
     bhk::moment_plan(c->h_cnt->lvl_off, c->max_level, &c->mom_deep, &c->mom_top);
     c->d.mom_deep = c->mom_deep;
     c->d.mom_top = c->mom_top;
@@ -483,11 +484,6 @@ bh_status rebuild(bh_ctx *c, hipStream_t s, bool from_caller) {
     bhk::moments(c->d, s);
     if (c->P.criterion == BH_OPEN_LEARNED) bhk::node_qn(c->d, s);
     ev_end(c, EV_MOM, s);
-    ev_begin(c, EV_GROUPS, s);
-    bhk::make_groups(c->d, s);
-    ev_end(c, EV_GROUPS, s);
-    STCHK(read_counters(c, s));
-    c->n_groups = c->h_cnt->n_groups;
     // the drift monitor measures motion from here
     if (c->P.reuse_drift > 0.0) bhk::drift_snapshot(c->d, s);
     c->tree_valid = true;
@@ -502,7 +498,8 @@ bh_status walk_until_fits(bh_ctx *c, hipStream_t s) {
     for (int attempt = 0;; ++attempt) {
         refresh_state(c);
         ev_begin(c, EV_WALK, s);
-        bhk::walk(c->d, c->n_groups, s);
+        bhk::walk(c->d, c->n_groups, !c->walk_reset, s);
+        c->walk_reset = false;
         ev_end(c, EV_WALK, s);
         STCHK(read_counters(c, s));
         const DevCounters &h = *c->h_cnt;
@@ -557,8 +554,7 @@ bh_status order_lists(bh_ctx *c, hipStream_t s) {
         HIPCHK(c, grow(c->force_items, need + need / 4 + 4096));
         c->d.force_items = P<ForceItem>(c->force_items);
     }
-    bhk::order_groups(c->d, c->n_groups, P<uint64_t>(c->gkey_a), P<uint32_t>(c->gval_a), P<uint64_t>(c->gkey_b),
-                      P<uint32_t>(c->gval_b), s);
+    bhk::order_groups(c->d, c->n_groups, s);
     c->lists_valid = true;
     return BH_OK;
 }
@@ -692,9 +688,7 @@ bh_status bh_create(bh_ctx **out, const bh_params *p) {
               grow(c->counters, sizeof(DevCounters)) == hipSuccess;
     for (int k = 0; ok && k < EV_N; ++k)
         ok = hipEventCreate(&c->ev0[k]) == hipSuccess && hipEventCreate(&c->ev1[k]) == hipSuccess;
-    ok = ok && hipStreamCreateWithFlags(&c->gs, hipStreamNonBlocking) == hipSuccess &&
-         hipEventCreateWithFlags(&c->fence_a, hipEventDisableTiming) == hipSuccess &&
-         hipEventCreateWithFlags(&c->fence_b, hipEventDisableTiming) == hipSuccess;
+    ok = ok && hipStreamCreateWithFlags(&c->gs, hipStreamNonBlocking) == hipSuccess;
     if (!ok || ensure_walk(c) != BH_OK || ensure_learned(c) != BH_OK) {
         bh_destroy(c);
         return BH_ENOMEM;
@@ -717,8 +711,8 @@ bh_status bh_destroy(bh_ctx *c) {
                      &c->val, &c->val_tmp, &c->hist, &c->scan_tmp, &c->nd_prefix, &c->nd_begin, &c->nd_count,
                      &c->nd_first, &c->nd_meta, &c->nd_walk, &c->nd_mom, &c->nd_quad, &c->tree_cnt,
                      &c->gmark, &c->grp, &c->g_lo, &c->g_hi, &c->g_cen, &c->g_pc_off, &c->g_pc_len,
-                     &c->g_pp_off, &c->g_pp_len, &c->g_cost, &c->force_items, &c->gkey_a, &c->gkey_b, &c->gval_a,
-                     &c->gval_b, &c->pc_pool, &c->pp_pool, &c->walk_scratch, &c->counters, &c->direct_part,
+                     &c->g_pp_off, &c->g_pp_len, &c->g_cost, &c->force_items, &c->pc_pool,
+                     &c->pp_pool, &c->walk_scratch, &c->counters, &c->direct_part,
                      &c->nd_qn, &c->amag, &c->amag_in, &c->g_amin, &c->g_rad, &c->cand, &c->mlp_w, &c->mlp_m,
                      &c->mlp_v, &c->mlp_scratch, &c->ds_x, &c->ds_y, &c->ds_pairs, &c->pk_a, &c->pk_b,
                      &c->pv_a, &c->pv_b, &c->phist, &c->pos_b, &c->nd_mom_b, &c->nd_drift};
@@ -737,8 +731,6 @@ bh_status bh_destroy(bh_ctx *c) {
     }
     for (auto &g : c->graphs)
         if (g.exec) (void)hipGraphExecDestroy(g.exec);
-    if (c->fence_a) (void)hipEventDestroy(c->fence_a);
-    if (c->fence_b) (void)hipEventDestroy(c->fence_b);
     if (c->gs) (void)hipStreamDestroy(c->gs);
     delete c;
     return BH_OK;
@@ -847,11 +839,7 @@ bh_status reuse_prefix_graph(bh_ctx *c, const DevState &dd, double h, double dt,
         hit->dt = dt;
         c->graph_captures += 1;
     }
-    HIPCHK(c, hipEventRecord(c->fence_a, s));
-    HIPCHK(c, hipStreamWaitEvent(c->gs, c->fence_a, 0));
-    HIPCHK(c, hipGraphLaunch(hit->exec, c->gs));
-    HIPCHK(c, hipEventRecord(c->fence_b, c->gs));
-    HIPCHK(c, hipStreamWaitEvent(s, c->fence_b, 0));
+    HIPCHK(c, hipGraphLaunch(hit->exec, s));
     c->graph_replays += 1;
     return BH_OK;
 }

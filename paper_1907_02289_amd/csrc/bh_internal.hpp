@@ -166,7 +166,7 @@ struct DevState {
     uint32_t *tree_cnt;            // [22 levels][tiles of particles] nodes per level and tile, then 22 totals
     int mom_deep, mom_top;         // moment launches: levels mom_deep-1 .. mom_top+1 one each, mom_top .. 0 together
     // groups
-    uint32_t *gmark;               // [n] particle marks, then group index
+    uint32_t *gmark;               // [n] node id + 1 at each group's first particle while groups are made, else 0
     GroupInfo *grp;                // [n] (capacity: one per particle)
     int4 *g_lo, *g_hi;             // grid box, half-open
     double4 *g_cen;
@@ -225,6 +225,19 @@ enum { WALK_GEOMETRIC = 0, WALK_LEARNED = 1, WALK_ENUMERATE = 2 };
 constexpr uint32_t BOX_BLOCKS_MAX = 1024, BOX_PER_BLOCK = 1024;
 
 // ---------------------------------------------------------------- host launchers
+__device__ __forceinline__ void reset_walk_counters(const DevState &d) {
+    d.cnt->pc_used = 0;
+    d.cnt->pp_used = 0;
+    d.cnt->interactions = 0;
+    d.cnt->walk_need_front = 0;
+    d.cnt->walk_need_list = 0;
+    d.cnt->flags[FLAG_WALK_OVF] = 0;
+    d.cnt->flags[FLAG_POOL_OVF] = 0;
+    d.cnt->flags[FLAG_WALK_BOUND] = 0;
+    d.cnt->flags[FLAG_CAND_BAD] = 0;
+    d.cnt->cand_used = 0;
+}
+
 namespace bhk {
 
 // tree build (bh_tree.hip)
@@ -244,9 +257,10 @@ void drift_clear(const DevState &d, hipStream_t s);
 void reset_flags(const DevState &d, hipStream_t s);
 
 // lists (bh_walk.hip)
-void walk(const DevState &d, uint32_t n_groups, hipStream_t s);
-void order_groups(const DevState &d, uint32_t n_groups, uint64_t *key_a, uint32_t *val_a, uint64_t *key_b,
-                  uint32_t *val_b, hipStream_t s);
+// reset: clear the walk's counters first (a build has cleared them already)
+void walk(const DevState &d, uint32_t n_groups, bool reset, hipStream_t s);
+constexpr size_t ORDER_WORDS = 64 * 128;      // d.hist holds at least as many
+void order_groups(const DevState &d, uint32_t n_groups, hipStream_t s);
 
 // forces (bh_force.hip): blocks = persistent workgroups
 // kick_h != 0 (no collision branch): the closing half kick v += kick_h a is
@@ -311,12 +325,8 @@ void direct_sum(const double *x, const double *y, const double *z, const double 
 void scan_u32(const uint32_t *in, uint32_t *out, const uint32_t *n_dev, uint32_t n_host,
               uint32_t *total, uint32_t *tmp, hipStream_t s);
 
-// fill n words with v (graph-safe replacement for hipMemsetAsync)
-void fill_u32(uint32_t *p, uint32_t v, size_t n, hipStream_t s);
-
 // Stable sort of (key, val) pairs by key, the keys being zero outside bits
-// [lo_bit, hi_bit) or, outside them, already ascending in input order within
-// equal keys of these bits;
+// [lo_bit, hi_bit);
 // then (when sys_off != nullptr and n_sys > 1) by the system owning input
 // index val (sys_off: device array of n_sys+1 offsets), so the result is in
 // (system, key, input order).  Result in key_a/val_a.  Scratch: key_b/val_b
@@ -325,5 +335,9 @@ size_t radix_hist_words(uint32_t n);
 void radix_sort(uint64_t *key_a, uint32_t *val_a, uint64_t *key_b, uint32_t *val_b,
                 uint32_t n, int lo_bit, int hi_bit, uint32_t *hist, uint32_t *tmp, hipStream_t s,
                 const uint32_t *sys_off, int n_sys);
+// The same for n up to sorts_small(n), from one pair of arrays into another.
+bool sorts_small(uint32_t n);
+void sort_small(const uint64_t *key, const uint32_t *val, uint64_t *key_out, uint32_t *val_out, uint32_t n,
+                hipStream_t s, const uint32_t *sys_off, int n_sys);
 
 }  // namespace bhk

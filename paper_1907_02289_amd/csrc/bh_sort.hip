@@ -9,7 +9,7 @@
 //     pairs into at most 1024 buckets of about 1000 to 2500, in one stable
 //     scatter, and a block sorts each bucket in LDS: eight launches, and two
 //     passes over memory instead of eight;
-//   above, and for keys of few bits: radix passes over memory with 8-bit
+//   above: radix passes over memory with 8-bit
 //     digits, per pass one histogram kernel, one scan of the (digit, block)
 //     counts and one scatter kernel whose ranks come from wave-level digit
 //     matching (eight ballots).  The scatter first orders its tile by digit in
@@ -100,12 +100,6 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_down(const uint32_t *in, 
         }
         carry += tot;
     }
-}
-
-__global__ void k_fill_u32(uint32_t *p, uint32_t v, size_t n) {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    size_t stride = (size_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) p[i] = v;
 }
 
 __global__ void k_copy_pairs(const uint64_t *kin, const uint32_t *vin, uint64_t *kout, uint32_t *vout, uint32_t n) {
@@ -831,13 +825,6 @@ void scan_u32(const uint32_t *in, uint32_t *out, const uint32_t *n_dev, uint32_t
     k_scan_down<<<SCAN_BLOCKS, SCAN_THREADS, 0, s>>>(in, out, n_dev, n_host, tmp);
 }
 
-void fill_u32(uint32_t *p, uint32_t v, size_t n, hipStream_t s) {
-    if (n == 0) return;
-    size_t blocks = (n + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    k_fill_u32<<<(unsigned)blocks, 256, 0, s>>>(p, v, n);
-}
-
 size_t radix_hist_words(uint32_t n) {
     size_t nb = (n + RS_TILE - 1) / RS_TILE;
     if (nb == 0) nb = 1;
@@ -845,21 +832,27 @@ size_t radix_hist_words(uint32_t n) {
     return nb * 256 > sample ? nb * 256 : sample;
 }
 
+bool sorts_small(uint32_t n) { return n <= SMALL_MAX; }
+
+void sort_small(const uint64_t *key, const uint32_t *val, uint64_t *key_out, uint32_t *val_out, uint32_t n,
+                hipStream_t s, const uint32_t *sys_off, int n_sys) {
+    const uint32_t rows = (n + RANK_ROWS - 1) / RANK_ROWS;
+    if (sys_off && n_sys > 1) k_sort_small<true><<<rows, RANK_THREADS, 0, s>>>(key, val, key_out, val_out, n, sys_off, n_sys);
+    else k_sort_small<false><<<rows, RANK_THREADS, 0, s>>>(key, val, key_out, val_out, n, sys_off, 1);
+}
+
 void radix_sort(uint64_t *key_a, uint32_t *val_a, uint64_t *key_b, uint32_t *val_b,
                 uint32_t n, int lo_bit, int hi_bit, uint32_t *hist, uint32_t *tmp, hipStream_t s,
                 const uint32_t *sys_off, int n_sys) {
     if (n == 0) return;
     if (!sys_off) n_sys = 1;
-    // one block up to SMALL_MAX; the sample sort up to SAMPLE_MAX unless a radix
-    // pass or two do
+    // ranks up to SMALL_MAX, the sample sort up to SAMPLE_MAX, radix passes above
     if (n <= SMALL_MAX) {
-        const uint32_t rows = (n + RANK_ROWS - 1) / RANK_ROWS;
-        if (n_sys > 1) k_sort_small<true><<<rows, RANK_THREADS, 0, s>>>(key_a, val_a, key_b, val_b, n, sys_off, n_sys);
-        else k_sort_small<false><<<rows, RANK_THREADS, 0, s>>>(key_a, val_a, key_b, val_b, n, sys_off, n_sys);
+        sort_small(key_a, val_a, key_b, val_b, n, s, sys_off, n_sys);
         k_copy_pairs<<<(n + 255) / 256, 256, 0, s>>>(key_b, val_b, key_a, val_a, n);
         return;
     }
-    if (n <= SAMPLE_MAX && hi_bit - lo_bit > 16) {
+    if (n <= SAMPLE_MAX) {
         const SampleLayout L = ss_layout(n, hist);
         const uint32_t rows = (L.buckets * L.per + RANK_ROWS - 1) / RANK_ROWS;
         const bool sys = n_sys > 1, wide = n > (1u << 20);

@@ -21,6 +21,8 @@
 // q = floor((v - min v) 2^21 / S).  phi comes from angle_of below, made of
 // correctly rounded operations only, so the keys do not depend on a math
 // library.
+#include <algorithm>
+
 #include "bh_internal.hpp"
 
 namespace {
@@ -186,7 +188,7 @@ __global__ void k_box_final(DevState d) {
 }
 
 // ---------------------------------------------------------------- keys
-__global__ void k_keys(DevState d) {
+__global__ void k_keys(DevState d, uint64_t *key, uint32_t *val) {
     uint32_t stride = gridDim.x * blockDim.x;
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < d.n; i += stride) {
         int s = sys_of(d.sys_off, d.n_sys, i);
@@ -203,13 +205,15 @@ __global__ void k_keys(DevState d) {
             double f = floor(t);
             q[a] = (f >= 2097151.0) ? 2097151u : (uint32_t)f;
         }
-        d.key[i] = (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2]);
-        d.val[i] = i;
+        key[i] = (spread3(q[0]) << 2) | (spread3(q[1]) << 1) | spread3(q[2]);
+        val[i] = i;
     }
 }
 
+// Flags of the build and the counters of the walk that follows it.
 __global__ void k_reset_flags(DevState d) {
     if (threadIdx.x < FLAG_COUNT) d.cnt->flags[threadIdx.x] = 0;
+    if (threadIdx.x == 0) reset_walk_counters(d);
 }
 
 // ---------------------------------------------------------------- permute
@@ -223,6 +227,7 @@ __global__ void k_permute(DevState d) {
         d.idx[j] = gi;
         d.inv[gi] = j;
         if (d.amag && d.amag_in) d.amag[j] = d.amag_in[src];
+        d.gmark[j] = 0;
     }
 }
 
@@ -655,8 +660,21 @@ __global__ void __launch_bounds__(1024) k_moments_top(DevState d, int top) {
 // the first node of each pack: the parent's thread walks its children in
 // order and starts a new pack where the next small child no longer fits
 // (the pack's particle count is taken later from the next group's start).
-// Also marks the first particle of each group.
+// Also marks the first particle of each group with the node's id plus one.
+//
+// Groups are numbered along the particles: marks per tile of particles, each
+// tile's start as the sum of those before it, groups written and marks cleared
+// tile by tile, then the boxes (and, with packing, the counts).  These four
+// launches follow the tree's before its counters are read, so that one read
+// serves both; a build that failed is left alone.  (With marks filled, three
+// scan launches, the nodes' groups looked up and packed counts in a launch of
+// their own it was 7 or 8, and a second read.)
+__device__ __forceinline__ bool build_failed(const DevState &d) {
+    return (d.cnt->flags[FLAG_NONFINITE] | d.cnt->flags[FLAG_EXTENT] | d.cnt->flags[FLAG_NODE_OVF]) != 0;
+}
+
 __global__ void k_regroup(DevState d) {
+    if (build_failed(d)) return;
     const uint32_t nn = d.cnt->lvl_off[BH_NLEVELS];
     const uint32_t G = (uint32_t)d.n_grp;
     uint32_t stride = gridDim.x * blockDim.x;
@@ -665,7 +683,7 @@ __global__ void k_regroup(DevState d) {
         if (v < (uint32_t)d.n_sys) {
             const bool grp = c <= G || nch == 0;
             d.nd_meta[v] = make_meta(meta_level(meta), nch, grp ? 1u : 0u, meta_sys(meta));
-            if (grp) d.gmark[d.nd_begin[v]] = 1u;
+            if (grp) d.gmark[d.nd_begin[v]] = v + 1;
         }
         const uint32_t f = d.nd_first[v];
         uint32_t run = 0;    // particles in the open pack, 0 when none is open
@@ -685,32 +703,58 @@ __global__ void k_regroup(DevState d) {
             }
             if (grp != (meta_group(mu) != 0u))
                 d.nd_meta[u] = make_meta(meta_level(mu), meta_nch(mu), grp ? 1u : 0u, meta_sys(mu));
-            if (grp) d.gmark[d.nd_begin[u]] = 1u;
+            if (grp) d.gmark[d.nd_begin[u]] = u + 1;
         }
     }
 }
 
-__global__ void k_group_emit(DevState d) {
-    const uint32_t nn = d.cnt->lvl_off[BH_NLEVELS];
-    uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < nn; v += stride) {
-        uint32_t meta = d.nd_meta[v];
-        if (!meta_group(meta)) continue;
-        uint32_t b = d.nd_begin[v];
-        uint32_t g = d.gmark[b];
-        d.grp[g] = GroupInfo{v, b, d.nd_count[v], meta_sys(meta)};
-    }
+// Particles per tile: at most 4096 tiles, whose counts a block adds up for itself.
+uint32_t group_tile(uint32_t n) { return std::max(1024u, ((n + 4095) / 4096 + TPB - 1) / TPB * TPB); }
+
+// d.tree_cnt, free once the octree is built, holds the tiles' counts.
+__global__ void __launch_bounds__(TPB) k_group_count(DevState d, uint32_t tile) {
+    __shared__ uint32_t red[TPB / 64];
+    const uint32_t b = blockIdx.x * tile, e = min(b + tile, d.n);
+    uint32_t c = 0;
+    if (!build_failed(d))
+        for (uint32_t i = b + threadIdx.x; i < e; i += TPB) c += d.gmark[i] != 0u;
+    c = wave_sum(c);
+    if (__lane_id() == 0) red[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) d.tree_cnt[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
-// Packed groups: the groups partition the sorted particles in order, so a
-// group ends where the next one starts.
-__global__ void k_group_count(DevState d) {
-    const uint32_t ng = d.cnt->n_groups;
-    uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < ng; g += stride) {
-        const uint32_t end = g + 1 < ng ? d.grp[g + 1].begin : (uint32_t)d.n;
-        d.grp[g].count = end - d.grp[g].begin;
+__global__ void __launch_bounds__(TPB) k_group_emit(DevState d, uint32_t tile) {
+    __shared__ uint32_t red[2][TPB / 64];
+    if (build_failed(d)) return;
+    const int w = threadIdx.x >> 6;
+    uint32_t g = 0;
+    for (uint32_t t = threadIdx.x; t < blockIdx.x; t += TPB) g += d.tree_cnt[t];
+    g = wave_sum(g);
+    if (__lane_id() == 0) red[0][w] = g;
+    __syncthreads();
+    g = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+    __syncthreads();
+    const uint32_t b = blockIdx.x * tile, e = min(b + tile, d.n);
+    int r = 0;
+    for (uint32_t i0 = b; i0 < e; i0 += TPB, r ^= 1) {
+        const uint32_t i = i0 + threadIdx.x;
+        const uint32_t mark = i < e ? d.gmark[i] : 0u;
+        const uint64_t m = __ballot(mark != 0u);
+        if (__lane_id() == 0) red[r][w] = (uint32_t)__popcll(m);
+        __syncthreads();
+        uint32_t at = g + (uint32_t)__popcll(m & lanemask_lt());
+        for (int k = 0; k < TPB / 64; ++k) {
+            at += k < w ? red[r][k] : 0u;
+            g += red[r][k];
+        }
+        if (mark) {
+            const uint32_t v = mark - 1;
+            d.grp[at] = GroupInfo{v, i, d.nd_count[v], meta_sys(d.nd_meta[v])};
+            d.gmark[i] = 0;
+        }
     }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) d.cnt->n_groups = g;
 }
 
 // One wave per group: integer grid box from the keys, centre = midpoint of
@@ -720,6 +764,11 @@ __global__ void __launch_bounds__(TPB) k_group_box(DevState d) {
     const uint32_t wpb = TPB / 64;
     for (uint32_t g = blockIdx.x * wpb + (threadIdx.x >> 6); g < ng; g += gridDim.x * wpb) {
         GroupInfo gi = d.grp[g];
+        if (d.pack_groups) {
+            // the groups partition the sorted particles in order: a pack ends where the next group starts
+            gi.count = (g + 1 < ng ? d.grp[g + 1].begin : (uint32_t)d.n) - gi.begin;
+            if (__lane_id() == 0) d.grp[g].count = gi.count;
+        }
         uint32_t qlo[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu}, qhi[3] = {0, 0, 0};
         double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
         for (uint32_t i = gi.begin + __lane_id(); i < gi.begin + gi.count; i += 64) {
@@ -766,8 +815,13 @@ void load_systems(const DevState &d, hipStream_t s) {
 void root_box_keys(const DevState &d, hipStream_t s) {
     k_box_partial<<<dim3(d.box_blocks, d.n_sys), TPB, 0, s>>>(d);
     k_box_final<<<d.n_sys, 64, 0, s>>>(d);
-    k_keys<<<grid_for(d.n), TPB, 0, s>>>(d);
-    radix_sort(d.key, d.val, d.key_tmp, d.val_tmp, d.n, 0, 63, d.hist, d.scan_tmp, s, d.sys_off, d.n_sys);
+    if (sorts_small(d.n)) {
+        k_keys<<<grid_for(d.n), TPB, 0, s>>>(d, d.key_tmp, d.val_tmp);
+        sort_small(d.key_tmp, d.val_tmp, d.key, d.val, d.n, s, d.sys_off, d.n_sys);
+    } else {
+        k_keys<<<grid_for(d.n), TPB, 0, s>>>(d, d.key, d.val);
+        radix_sort(d.key, d.val, d.key_tmp, d.val_tmp, d.n, 0, 63, d.hist, d.scan_tmp, s, d.sys_off, d.n_sys);
+    }
 }
 
 void reset_flags(const DevState &d, hipStream_t s) {
@@ -832,12 +886,10 @@ void drift_clear(const DevState &d, hipStream_t s) {
 }
 
 void make_groups(const DevState &d, hipStream_t s) {
-    const unsigned g = grid_for(d.n, 4096);
-    fill_u32(d.gmark, 0u, d.n, s);
-    k_regroup<<<g, TPB, 0, s>>>(d);
-    scan_u32(d.gmark, d.gmark, nullptr, d.n, &d.cnt->n_groups, d.scan_tmp, s);
-    k_group_emit<<<g, TPB, 0, s>>>(d);
-    if (d.pack_groups) k_group_count<<<grid_for(d.n, 4096), TPB, 0, s>>>(d);
+    const uint32_t tile = group_tile(d.n), tiles = (d.n + tile - 1) / tile;
+    k_regroup<<<grid_for(d.n, 4096), TPB, 0, s>>>(d);
+    k_group_count<<<tiles, TPB, 0, s>>>(d, tile);
+    k_group_emit<<<tiles, TPB, 0, s>>>(d, tile);
     k_group_box<<<grid_for((size_t)d.n * 64 / 8, 8192), TPB, 0, s>>>(d);
 }
 
