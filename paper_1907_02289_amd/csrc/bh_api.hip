@@ -549,7 +549,7 @@ bh_status walk_until_fits(bh_ctx *c, hipStream_t s) {
 bh_status run_forces(bh_ctx *c, hipStream_t s, bool pot, double kick_h = 0.0);
 
 bh_status order_lists(bh_ctx *c, hipStream_t s) {
-    const size_t need = (size_t)c->n_groups * sizeof(ForceItem);
+    const size_t need = bhk::max_items(c->n_groups, c->n) * sizeof(ForceItem);
     if (need > c->force_items.bytes || !c->force_items.p) {
         HIPCHK(c, grow(c->force_items, need + need / 4 + 4096));
         c->d.force_items = P<ForceItem>(c->force_items);

@@ -59,6 +59,7 @@
 namespace {
 
 constexpr int FT = 256;      // threads per workgroup (4 waves)
+static_assert(FT == ITEM_PARTICLES, "a workgroup takes an item's particles at once");
 constexpr int TJ_MAX = 512;  // sources per LDS tile at most (two per thread); 256 is the other tile
 constexpr int LC = FT;       // particle-list leaves per chunk (one per thread)
 constexpr int PIDX = 2048;   // particle ids of a leaf chunk listed in LDS (FP32 gravity-only kernels)
@@ -371,31 +372,35 @@ __device__ __forceinline__ void contact_pass(const typename V4<R>::T *tile, cons
     take();
 }
 
-// Work items of the persistent blocks: an item is 256 particles of a group
-// (part p of a group: its blocks of 256 p, p + parts, ...; a group of more than
-// parts blocks, of coincident particles, wraps around), so a group's particles
-// are summed alike however many groups a launch has.  Items come in descending
-// cost and Morton order from one counter: blocks in flight then work on
-// neighbouring groups, whose sources stay in L2.  (Half of the items dealt to
-// the blocks in turn, without the counter, took the 2^24 ring's launch from 77
-// to 105 ms: the blocks drift apart.)  Whole groups as items left the chip
-// waiting for the last large ones when groups are few: 1.78 -> 1.43 ms at 1914
-// groups of up to 512.  A group of one item pops the counter once more for its
-// empty second part, 12 ns each over the whole chip: 0.390 -> 0.397 ms at 16077
-// groups of the 2^20 ring.
-struct ForceQueue {
-    uint32_t items, parts, pops;
-};
+// Work items of the persistent blocks: an item is 256 particles of a group (or
+// what it has), so a group's particles are summed alike however many groups a
+// launch has.  Items come in descending cost and Morton order: a block starts
+// with the item of its number and goes on from one counter, so that blocks in
+// flight work on neighbouring groups, whose sources stay in L2.  (Half of the
+// items dealt to the blocks in turn, without the counter, took the 2^24 ring's
+// launch from 77 to 105 ms: the blocks drift apart.)  Whole groups as items left
+// the chip waiting for the last large ones when groups are few: 1.78 -> 1.43 ms
+// at 1914 groups of up to 512.  The counter serves one pop per 12 ns, which is
+// why the first items need none and empty ones do not exist (0.396 -> 0.364 ms at
+// 16077 groups of the 2^20 ring, 77.1 -> 75.9 at 2^24, with the pop beside the
+// results' writes).  A pop before the last sums, or a whole item ahead, gave
+// nothing or bound the item to a block that was late (1.27 ms at 1914 groups).
 
-ForceQueue force_queue(uint32_t n_groups, uint32_t n_grp, int &blocks) {
-    ForceQueue q;
-    // bounded so that items stay 32-bit (any number of parts covers a group)
-    const uint32_t most = 0x7fffffffu / n_groups;
-    q.parts = std::max(1u, std::min((n_grp + FT - 1) / FT, most));
-    q.items = n_groups * q.parts;
-    blocks = (int)std::min((uint32_t)blocks, q.items);
-    q.pops = q.items + (uint32_t)blocks;        // each block's last pop finds nothing
-    return q;
+// A work item's record in scalar registers: one load, a word per lane.  Read
+// as a struct it went to vector registers (the kernel writes memory, so the
+// compiler takes no scalar loads).
+__device__ __forceinline__ ForceItem uniform_item(const ForceItem *p) {
+    constexpr int W = sizeof(ForceItem) / 4;
+    static_assert(W <= 64, "one word per lane");
+    const int lane = __lane_id();
+    const uint32_t v = reinterpret_cast<const uint32_t *>(p)[lane < W ? lane : 0];
+    union {
+        ForceItem item;
+        uint32_t word[W];
+    } u;
+#pragma unroll
+    for (int k = 0; k < W; ++k) u.word[k] = __builtin_amdgcn_readlane(v, k);
+    return u.item;
 }
 
 // FP32: registers capped so that 6 workgroups (24 waves) fit a CU; the
@@ -414,8 +419,7 @@ template <typename R, bool POT, bool ZERO_EPS, bool COLL, int TJ>
 // leapfrog step to each particle, as a separate pass over v and a would (the
 // collision branch reads other particles' velocities, so it never fuses).
 // TJ: sources per LDS tile (512, or 256 in the FP32 gravity-only kernels).
-// q: the work items (see ForceQueue).
-__global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevState d, ForceQueue q, double kick_h) {
+__global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevState d, double kick_h) {
     static_assert(TJ == 256 || TJ == TJ_MAX, "tile of 256 or 512 sources");
     using T4 = typename V4<R>::T;
     __shared__ T4 tile[TJ + 16];
@@ -442,366 +446,359 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
     // tail mode (below) in the FP32 kernels without the collision branch
     constexpr bool TAIL = sizeof(R) == 4 && !COLL;
 
-    for (;;) {
-        // the counter wraps to 0 with the launch's last pop.  An item popped one
-        // ahead, while the block works on its last, hides the atomic but binds the
-        // item to a block that may be late: 0.40 ms as without at 16077 groups,
-        // 1.27 instead of 1.09 ms at 1914.
-        if (tid == 0) s_item = atomicInc(&d.cnt->work_counter2, q.pops - 1);
-        __syncthreads();
-        // the work item is the same for the whole workgroup: keep it (and all
-        // per-group values derived from it) in scalar registers
-        const uint32_t item = __builtin_amdgcn_readfirstlane(s_item);
-        __syncthreads();
-        if (item >= q.items) break;
-        const uint32_t gpart = item % q.parts;
-        const ForceItem gi = d.force_items[item / q.parts];
+    const uint32_t items = __builtin_amdgcn_readfirstlane(d.cnt->n_items);
+    // the item is the same for the whole workgroup: keep it (and all values
+    // derived from it) in scalar registers
+    for (uint32_t item = blockIdx.x; item < items;) {
+        const ForceItem gi = uniform_item(d.force_items + item);
         const double4 cen = make_double4(gi.cx, gi.cy, gi.cz, 0.0);
         // FP32: an equal-mass system's particles enter the pair loop with unit
         // mass, node masses in units of that mass, the sums scaled at the end
         const double m0 = sizeof(R) == 4 ? gi.m0 : 0.0;
         const bool eqm = m0 > 0.0;
         const double gscale = eqm ? d.G * m0 : d.G;
-        const double inv_m0 = eqm ? 1.0 / m0 : 1.0;
+        const double inv_m0 = eqm ? gi.inv_m0 : 1.0;
         const unsigned long long pc0 = gi.pc_off, pp0 = gi.pp_off;
         const uint32_t npc = gi.npc, npp = gi.npp;
 
-        for (uint32_t ib = gpart * FT; ib < gi.count; ib += q.parts * FT) {
-            const uint32_t nb = min((uint32_t)FT, gi.count - ib);
-            // Waves take 64-particle chunks of the block (n_ic of them), the
-            // waves left over splitting the source range (split ways).  A chunk
-            // of at most 32 (16, 8) particles -- a small group, or the last chunk
-            // of a larger one -- spreads its wave over 2 (4, 8) sub-slices of its
-            // source range: cw lanes per particle, sub = 64 / cw parts.
-            // split, sub and cw are powers of two: their divisions are shifts
-            const int n_ic = (int)((nb + 63) >> 6);
-            const int split_sh = n_ic == 1 ? 2 : (n_ic == 2 ? 1 : 0);
-            const int split = 1 << split_sh;                         // 4 / n_ic
-            const int ichunk = w % n_ic;
-            const int jslice = w / n_ic;
-            const bool wave_on = jslice < split;
-            const int cnt_w = min(64, (int)nb - 64 * ichunk);
-            // Slices of 8 particles in the chunk.  With 3, 5 or 7 of them the
-            // chunk runs in eighths mode: lanes 0..8S-1 hold the particles and
-            // take the first S eighths of the wave's source range; each of the
-            // 8-S other groups of 8 lanes takes one of the last eighths for the
-            // S slices in turn and hands each slice's partial sums to the lanes
-            // that own them.  Every lane then runs S/8 of the range.
-            const int s8 = (cnt_w + 7) >> 3;
-            const bool e8 = TAIL && (s8 == 3 || s8 == 5 || s8 == 7);
-            const int cw_sh = e8 ? 6 : (cnt_w <= 8 ? 3 : (cnt_w <= 16 ? 4 : (cnt_w <= 32 ? 5 : 6)));
-            const int cw = 1 << cw_sh;
-            const int sub_sh = 6 - cw_sh;
-            const int sub = 1 << sub_sh;                             // 64 / cw
-            const int part = lane >> cw_sh;
-            // A chunk of 41 to 48 particles runs in tail mode: lanes 0..47 hold
-            // the particles and take the first three quarters of the wave's
-            // source range; lanes 48..63 take the last quarter for the three
-            // 16-particle slices in turn and hand each slice's partial sums to
-            // the lanes that own them.  Every lane then runs 3/4 of the range
-            // instead of a full wave running all of it.
-            const bool tailm = TAIL && cnt_w > 40 && cnt_w <= 48;
-            const int last_cnt = (int)nb - 64 * (n_ic - 1);
-            // the block's last chunk is sub-sliced, tailed or in eighths
-            const bool any_sub = last_cnt <= (TAIL ? 56 : 32);
-            const uint32_t il = 64 * ichunk + (lane & (cw - 1));
-            const bool ion = wave_on && il < nb;
-            const uint32_t i = gi.begin + ib + il;
-            R xi = 0, yi = 0, zi = 0;
-            if (ion) {
-                const double4 p = d.pos[i];
-                xi = (R)(p.x - cen.x);
-                yi = (R)(p.y - cen.y);
-                zi = (R)(p.z - cen.z);
-            }
-            R ax = 0, ay = 0, az = 0, pot = 0;
-            R rcd2 = 0, cmin = 0;
-            if (COLL) {
-                const double n1 = fabs((double)xi) + fabs((double)yi) + fabs((double)zi);
-                const double rcd = d.rc * (1.0 + U) + 0.5 * U * n1;
-                rcd2 = (R)((rcd * rcd) * (1.0 + U) + d.eps2 * (1.0 + U));
+        const uint32_t nb = gi.count;
+        // Waves take 64-particle chunks of the block (n_ic of them), the
+        // waves left over splitting the source range (split ways).  A chunk
+        // of at most 32 (16, 8) particles -- a small group, or the last chunk
+        // of a larger one -- spreads its wave over 2 (4, 8) sub-slices of its
+        // source range: cw lanes per particle, sub = 64 / cw parts.
+        // split, sub and cw are powers of two: their divisions are shifts
+        const int n_ic = (int)((nb + 63) >> 6);
+        const int split_sh = n_ic == 1 ? 2 : (n_ic == 2 ? 1 : 0);
+        const int split = 1 << split_sh;                         // 4 / n_ic
+        const int ichunk = w % n_ic;
+        const int jslice = w / n_ic;
+        const bool wave_on = jslice < split;
+        const int cnt_w = min(64, (int)nb - 64 * ichunk);
+        // Slices of 8 particles in the chunk.  With 3, 5 or 7 of them the
+        // chunk runs in eighths mode: lanes 0..8S-1 hold the particles and
+        // take the first S eighths of the wave's source range; each of the
+        // 8-S other groups of 8 lanes takes one of the last eighths for the
+        // S slices in turn and hands each slice's partial sums to the lanes
+        // that own them.  Every lane then runs S/8 of the range.
+        const int s8 = (cnt_w + 7) >> 3;
+        const bool e8 = TAIL && (s8 == 3 || s8 == 5 || s8 == 7);
+        const int cw_sh = e8 ? 6 : (cnt_w <= 8 ? 3 : (cnt_w <= 16 ? 4 : (cnt_w <= 32 ? 5 : 6)));
+        const int cw = 1 << cw_sh;
+        const int sub_sh = 6 - cw_sh;
+        const int sub = 1 << sub_sh;                             // 64 / cw
+        const int part = lane >> cw_sh;
+        // A chunk of 41 to 48 particles runs in tail mode: lanes 0..47 hold
+        // the particles and take the first three quarters of the wave's
+        // source range; lanes 48..63 take the last quarter for the three
+        // 16-particle slices in turn and hand each slice's partial sums to
+        // the lanes that own them.  Every lane then runs 3/4 of the range
+        // instead of a full wave running all of it.
+        const bool tailm = TAIL && cnt_w > 40 && cnt_w <= 48;
+        const int last_cnt = (int)nb - 64 * (n_ic - 1);
+        // the block's last chunk is sub-sliced, tailed or in eighths
+        const bool any_sub = last_cnt <= (TAIL ? 56 : 32);
+        const uint32_t il = 64 * ichunk + (lane & (cw - 1));
+        const bool ion = wave_on && il < nb;
+        const uint32_t i = gi.begin + il;
+        R xi = 0, yi = 0, zi = 0;
+        if (ion) {
+            const double4 p = d.pos[i];
+            xi = (R)(p.x - cen.x);
+            yi = (R)(p.y - cen.y);
+            zi = (R)(p.z - cen.z);
+        }
+        R ax = 0, ay = 0, az = 0, pot = 0;
+        R rcd2 = 0, cmin = 0;
+        if (COLL) {
+            const double n1 = fabs((double)xi) + fabs((double)yi) + fabs((double)zi);
+            const double rcd = d.rc * (1.0 + U) + 0.5 * U * n1;
+            rcd2 = (R)((rcd * rcd) * (1.0 + U) + d.eps2 * (1.0 + U));
 #pragma unroll
-                for (int a = 0; a < 4; ++a) cacc[a][tid] = 0.0;
-            }
+            for (int a = 0; a < 4; ++a) cacc[a][tid] = 0.0;
+        }
 
-            // The staged tile holds cntt sources.  With a sub-sliced chunk in the
-            // block the tile is padded with massless far sources to a multiple of
-            // 8 split entries and cut at multiples of 8, so that every part has
-            // the same length; full chunks still stop at the last real entry.
-            // particles: whether the tile holds particle sources (the only ones
-            // the collision branch applies to).
-            auto compute_tile = [&](uint32_t cntt, bool particles) {
-                const int ct = (int)cntt;
-                const int cntp = any_sub ? ((ct + (8 << split_sh) - 1) >> (3 + split_sh)) << (3 + split_sh) : ct;
-                for (int t = ct + tid; t < cntp; t += FT) tile[t] = mk4<R>((R)1e18, (R)1e18, (R)1e18, (R)0);
-                __syncthreads();
-                if (wave_on) {
-                    int jb, je;
-                    if (any_sub) {
-                        const int q = cntp >> 3;
-                        jb = 8 * ((q * jslice) >> split_sh);
-                        je = 8 * ((q * (jslice + 1)) >> split_sh);
-                    } else {
-                        jb = (ct * jslice) >> split_sh;
-                        je = (ct * (jslice + 1)) >> split_sh;
-                    }
-                    // this lane's part of the range: [jl0, jl0 + L)
-                    int jl0, L;
-                    if (sub == 1) {
-                        jl0 = jb;
-                        L = max(0, min(je, ct) - jb);
-                    } else {
-                        L = (je - jb) >> sub_sh;
-                        jl0 = jb + part * L;
-                    }
-                    bool clamp = false;
-                    if constexpr (COLL) clamp = particles;
-                    const bool eq = particles && eqm;
-                    if (clamp) {
-                        cmin = (R)1e30;
-                        if (eq)
-                            tile_pass<R, POT, ZERO_EPS, true, true>(tile, sub, jl0, L, xi, yi, zi, eps2, rce2, ax, ay,
-                                                                    az, pot, cmin);
-                        else
-                            tile_pass<R, POT, ZERO_EPS, true, false>(tile, sub, jl0, L, xi, yi, zi, eps2, rce2, ax,
-                                                                     ay, az, pot, cmin);
-                        if (__ballot(ion && cmin <= rcd2) != 0)
-                            contact_pass<R, POT>(tile, jidx, jl0, L, xi, yi, zi, eps2, rcd2, ion, i, d,
-                                                 &cacc[0][tid]);
-                    } else if (e8) {
-                        const int Q = (je - jb) >> 3;
-                        const int lg = lane >> 3;
-                        const bool tail_lane = lg >= s8;
+        // The staged tile holds cntt sources.  With a sub-sliced chunk in the
+        // block the tile is padded with massless far sources to a multiple of
+        // 8 split entries and cut at multiples of 8, so that every part has
+        // the same length; full chunks still stop at the last real entry.
+        // particles: whether the tile holds particle sources (the only ones
+        // the collision branch applies to).
+        auto compute_tile = [&](uint32_t cntt, bool particles) {
+            const int ct = (int)cntt;
+            const int cntp = any_sub ? ((ct + (8 << split_sh) - 1) >> (3 + split_sh)) << (3 + split_sh) : ct;
+            for (int t = ct + tid; t < cntp; t += FT) tile[t] = mk4<R>((R)1e18, (R)1e18, (R)1e18, (R)0);
+            __syncthreads();
+            if (wave_on) {
+                int jb, je;
+                if (any_sub) {
+                    const int q = cntp >> 3;
+                    jb = 8 * ((q * jslice) >> split_sh);
+                    je = 8 * ((q * (jslice + 1)) >> split_sh);
+                } else {
+                    jb = (ct * jslice) >> split_sh;
+                    je = (ct * (jslice + 1)) >> split_sh;
+                }
+                // this lane's part of the range: [jl0, jl0 + L)
+                int jl0, L;
+                if (sub == 1) {
+                    jl0 = jb;
+                    L = max(0, min(je, ct) - jb);
+                } else {
+                    L = (je - jb) >> sub_sh;
+                    jl0 = jb + part * L;
+                }
+                bool clamp = false;
+                if constexpr (COLL) clamp = particles;
+                const bool eq = particles && eqm;
+                if (clamp) {
+                    cmin = (R)1e30;
+                    if (eq)
+                        tile_pass<R, POT, ZERO_EPS, true, true>(tile, sub, jl0, L, xi, yi, zi, eps2, rce2, ax, ay,
+                                                                az, pot, cmin);
+                    else
+                        tile_pass<R, POT, ZERO_EPS, true, false>(tile, sub, jl0, L, xi, yi, zi, eps2, rce2, ax,
+                                                                 ay, az, pot, cmin);
+                    if (__ballot(ion && cmin <= rcd2) != 0)
+                        contact_pass<R, POT>(tile, jidx, jl0, L, xi, yi, zi, eps2, rcd2, ion, i, d,
+                                             &cacc[0][tid]);
+                } else if (e8) {
+                    const int Q = (je - jb) >> 3;
+                    const int lg = lane >> 3;
+                    const bool tail_lane = lg >= s8;
 #pragma unroll 1
-                        for (int pq = 0; pq < s8; ++pq) {
-                            const int src = 8 * pq + (lane & 7);
-                            const R tx = __shfl(xi, src, 64), ty = __shfl(yi, src, 64), tz = __shfl(zi, src, 64);
-                            if (tail_lane) {
-                                xi = tx;
-                                yi = ty;
-                                zi = tz;
-                                ax = ay = az = pot = (R)0;
-                            }
-                            // owners: eighth pq of their own slice; others: their own eighth
-                            const int j0 = jb + (tail_lane ? lg : pq) * Q;
-                            if (eq)
-                                interact_lanes<R, POT, ZERO_EPS, false, true>(tile, j0, Q, xi, yi, zi, eps2, rce2,
-                                                                              ax, ay, az, pot, cmin);
-                            else
-                                interact_lanes<R, POT, ZERO_EPS, false, false>(tile, j0, Q, xi, yi, zi, eps2, rce2,
-                                                                               ax, ay, az, pot, cmin);
-                            for (int t = s8; t < 8; ++t) {
-                                const int tl = 8 * t + (lane & 7);
-                                const R sx = __shfl(ax, tl, 64), sy = __shfl(ay, tl, 64), sz = __shfl(az, tl, 64),
-                                        sp = __shfl(pot, tl, 64);
-                                if (lg == pq) {
-                                    ax += sx;
-                                    ay += sy;
-                                    az += sz;
-                                    pot += sp;
-                                }
-                            }
+                    for (int pq = 0; pq < s8; ++pq) {
+                        const int src = 8 * pq + (lane & 7);
+                        const R tx = __shfl(xi, src, 64), ty = __shfl(yi, src, 64), tz = __shfl(zi, src, 64);
+                        if (tail_lane) {
+                            xi = tx;
+                            yi = ty;
+                            zi = tz;
+                            ax = ay = az = pot = (R)0;
                         }
-                    } else if (tailm) {
-                        const int Q = (je - jb) >> 2;
-                        const bool tail_lane = lane >= 48;
-#pragma unroll 1
-                        for (int pq = 0; pq < 3; ++pq) {
-                            const int src = 16 * pq + (lane & 15);
-                            const R tx = __shfl(xi, src, 64), ty = __shfl(yi, src, 64), tz = __shfl(zi, src, 64);
-                            if (tail_lane) {
-                                xi = tx;
-                                yi = ty;
-                                zi = tz;
-                                ax = ay = az = pot = (R)0;
-                            }
-                            const int j0 = tail_lane ? jb + 3 * Q : jb + pq * Q;
-                            if (eq)
-                                interact_lanes<R, POT, ZERO_EPS, false, true>(tile, j0, Q, xi, yi, zi, eps2, rce2,
-                                                                              ax, ay, az, pot, cmin);
-                            else
-                                interact_lanes<R, POT, ZERO_EPS, false, false>(tile, j0, Q, xi, yi, zi, eps2, rce2,
-                                                                               ax, ay, az, pot, cmin);
-                            const int tl = 48 + (lane & 15);
+                        // owners: eighth pq of their own slice; others: their own eighth
+                        const int j0 = jb + (tail_lane ? lg : pq) * Q;
+                        if (eq)
+                            interact_lanes<R, POT, ZERO_EPS, false, true>(tile, j0, Q, xi, yi, zi, eps2, rce2,
+                                                                          ax, ay, az, pot, cmin);
+                        else
+                            interact_lanes<R, POT, ZERO_EPS, false, false>(tile, j0, Q, xi, yi, zi, eps2, rce2,
+                                                                           ax, ay, az, pot, cmin);
+                        for (int t = s8; t < 8; ++t) {
+                            const int tl = 8 * t + (lane & 7);
                             const R sx = __shfl(ax, tl, 64), sy = __shfl(ay, tl, 64), sz = __shfl(az, tl, 64),
                                     sp = __shfl(pot, tl, 64);
-                            if ((lane >> 4) == pq) {
+                            if (lg == pq) {
                                 ax += sx;
                                 ay += sy;
                                 az += sz;
                                 pot += sp;
                             }
                         }
-                    } else if (eq) {
-                        tile_pass<R, POT, ZERO_EPS, false, true>(tile, sub, jl0, L, xi, yi, zi, eps2, rce2, ax, ay,
-                                                                 az, pot, cmin);
-                    } else {
-                        tile_pass<R, POT, ZERO_EPS, false, false>(tile, sub, jl0, L, xi, yi, zi, eps2, rce2, ax, ay,
-                                                                  az, pot, cmin);
                     }
-                }
-                __syncthreads();
-            };
-
-            // the first leaves of the particle list, loaded beside the first nodes
-            uint32_t lb = 0, lc = 0;
-            if ((uint32_t)tid < npp) {
-                const uint32_t leaf = d.pp_pool[pp0 + tid];
-                lb = d.nd_begin[leaf];
-                lc = d.nd_count[leaf];
-            }
-
-            // ---- node list: centre of mass and mass of each accepted node
-            for (uint32_t t0 = 0; t0 < npc; t0 += TJ) {
-                const uint32_t cntt = min((uint32_t)TJ, npc - t0);
-                for (uint32_t e = tid; e < cntt; e += FT) {
-                    const double4 m = d.nd_mom[d.pc_pool[pc0 + t0 + e]];
-                    tile[e] = mk4<R>((R)(m.x - cen.x), (R)(m.y - cen.y), (R)(m.z - cen.z), (R)(m.w * inv_m0));
-                }
-                compute_tile(cntt, false);
-            }
-
-            // ---- particle list: the particles of each listed leaf
-            for (uint32_t l0 = 0; l0 < npp; l0 += LC) {
-                const uint32_t nl = min((uint32_t)LC, npp - l0);
-                if (l0 != 0) {
-                    lc = 0;
-                    if ((uint32_t)tid < nl) {
-                        const uint32_t leaf = d.pp_pool[pp0 + l0 + tid];
-                        lb = d.nd_begin[leaf];
-                        lc = d.nd_count[leaf];
-                    }
-                }
-                // exclusive scan of leaf sizes over the workgroup
-                const uint32_t inc = wave_incl_scan(lc);
-                if (lane == 63) wsum[w] = inc;
-                __syncthreads();
-                uint32_t off = 0, tot = 0;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    off += (k < w) ? wsum[k] : 0u;
-                    tot += wsum[k];
-                }
-                lbeg[tid] = lb;
-                lscan[tid] = off + inc - lc;
-                // a chunk of at most PIDX particles lists them all (each thread its
-                // leaf's); a larger one (a few big level-21 leaves) searches
-                const bool ids = LIST_IDS && tot <= (uint32_t)PIDX;
-                if (ids)
-                    for (uint32_t k = 0; k < lc; ++k) pid[off + inc - lc + k] = lb + k;
-                __syncthreads();
-                for (uint32_t p0 = 0; p0 < tot; p0 += TJ) {
-                    const uint32_t cntt = min((uint32_t)TJ, tot - p0);
-                    for (uint32_t e = tid; e < cntt; e += FT) {
-                        const uint32_t f = p0 + e;
-                        uint32_t j;
-                        if (ids) {
-                            j = pid[f];
-                        } else {
-                            uint32_t lo = 0, hi = nl - 1;          // last k with lscan[k] <= f
-                            while (lo < hi) {
-                                const uint32_t mid = (lo + hi + 1) >> 1;
-                                if (lscan[mid] <= f) lo = mid; else hi = mid - 1;
-                            }
-                            j = lbeg[lo] + (f - lscan[lo]);
+                } else if (tailm) {
+                    const int Q = (je - jb) >> 2;
+                    const bool tail_lane = lane >= 48;
+#pragma unroll 1
+                    for (int pq = 0; pq < 3; ++pq) {
+                        const int src = 16 * pq + (lane & 15);
+                        const R tx = __shfl(xi, src, 64), ty = __shfl(yi, src, 64), tz = __shfl(zi, src, 64);
+                        if (tail_lane) {
+                            xi = tx;
+                            yi = ty;
+                            zi = tz;
+                            ax = ay = az = pot = (R)0;
                         }
-                        const double4 q = d.pos[j];
-                        tile[e] = mk4<R>((R)(q.x - cen.x), (R)(q.y - cen.y), (R)(q.z - cen.z), (R)q.w);
-                        if (COLL) jidx[e] = j;
-                    }
-                    compute_tile(cntt, true);
-                }
-            }
-
-            // ---- add the j-slices in a fixed order and write FP64 results
-            if (cw < 64) {
-#pragma unroll
-                for (int off = 32; off >= 8; off >>= 1) {
-                    if (off < cw) break;
-                    ax += __shfl_xor(ax, off, 64);
-                    ay += __shfl_xor(ay, off, 64);
-                    az += __shfl_xor(az, off, 64);
-                    pot += __shfl_xor(pot, off, 64);
-                }
-            }
-            red[0][w][lane] = ax;
-            red[1][w][lane] = ay;
-            red[2][w][lane] = az;
-            red[3][w][lane] = pot;
-            __syncthreads();
-            if (ion && jslice == 0 && lane < cw) {
-                R sx = 0, sy = 0, sz = 0, sp = 0;
-                for (int k = 0; k < split; ++k) {
-                    const int ww = k * n_ic + ichunk;
-                    sx += red[0][ww][lane];
-                    sy += red[1][ww][lane];
-                    sz += red[2][ww][lane];
-                    sp += red[3][ww][lane];
-                }
-                double gx = gscale * (double)sx, gy = gscale * (double)sy, gz = gscale * (double)sz;
-                if (d.amag) d.amag[i] = sqrt(gx * gx + gy * gy + gz * gz);
-                if (d.central_mass != 0.0) {
-                    const double4 p = d.pos[i];
-                    const double r2 = p.x * p.x + p.y * p.y + p.z * p.z;
-                    const double r = sqrt(r2);
-                    const double f = -d.G * d.central_mass / (r2 * r);
-                    gx += f * p.x;
-                    gy += f * p.y;
-                    gz += f * p.z;
-                }
-                double gp = POT ? gscale * (double)sp : 0.0;
-                if (COLL) {
-                    // contact sums of the threads that worked on particle i, in a fixed order
-                    double cx = 0, cy = 0, cz = 0, cp = 0;
-                    for (int k = 0; k < split; ++k)
-                        for (int sb = 0; sb < sub; ++sb) {
-                            const int th = (k * n_ic + ichunk) * 64 + sb * cw + lane;
-                            cx += cacc[0][th];
-                            cy += cacc[1][th];
-                            cz += cacc[2][th];
-                            cp += cacc[3][th];
+                        const int j0 = tail_lane ? jb + 3 * Q : jb + pq * Q;
+                        if (eq)
+                            interact_lanes<R, POT, ZERO_EPS, false, true>(tile, j0, Q, xi, yi, zi, eps2, rce2,
+                                                                          ax, ay, az, pot, cmin);
+                        else
+                            interact_lanes<R, POT, ZERO_EPS, false, false>(tile, j0, Q, xi, yi, zi, eps2, rce2,
+                                                                           ax, ay, az, pot, cmin);
+                        const int tl = 48 + (lane & 15);
+                        const R sx = __shfl(ax, tl, 64), sy = __shfl(ay, tl, 64), sz = __shfl(az, tl, 64),
+                                sp = __shfl(pot, tl, 64);
+                        if ((lane >> 4) == pq) {
+                            ax += sx;
+                            ay += sy;
+                            az += sz;
+                            pot += sp;
                         }
-                    gx += cx;
-                    gy += cy;
-                    gz += cz;
-                    gp += cp;
-                }
-                d.acc[i] = make_double4(gx, gy, gz, POT ? gp : 0.0);
-                if (!COLL && kick_h != 0.0) {
-                    double4 v = d.vel[i];
-                    v.x = v.x + kick_h * gx;
-                    v.y = v.y + kick_h * gy;
-                    v.z = v.z + kick_h * gz;
-                    d.vel[i] = v;
+                    }
+                } else if (eq) {
+                    tile_pass<R, POT, ZERO_EPS, false, true>(tile, sub, jl0, L, xi, yi, zi, eps2, rce2, ax, ay,
+                                                             az, pot, cmin);
+                } else {
+                    tile_pass<R, POT, ZERO_EPS, false, false>(tile, sub, jl0, L, xi, yi, zi, eps2, rce2, ax, ay,
+                                                              az, pot, cmin);
                 }
             }
             __syncthreads();
+        };
+
+        // the first leaves of the particle list, loaded beside the first nodes
+        uint32_t lb = 0, lc = 0;
+        if ((uint32_t)tid < npp) {
+            const uint32_t leaf = d.pp_pool[pp0 + tid];
+            lb = d.nd_begin[leaf];
+            lc = d.nd_count[leaf];
         }
+
+        // ---- node list: centre of mass and mass of each accepted node
+        for (uint32_t t0 = 0; t0 < npc; t0 += TJ) {
+            const uint32_t cntt = min((uint32_t)TJ, npc - t0);
+            for (uint32_t e = tid; e < cntt; e += FT) {
+                const double4 m = d.nd_mom[d.pc_pool[pc0 + t0 + e]];
+                tile[e] = mk4<R>((R)(m.x - cen.x), (R)(m.y - cen.y), (R)(m.z - cen.z), (R)(m.w * inv_m0));
+            }
+            compute_tile(cntt, false);
+        }
+
+        // ---- particle list: the particles of each listed leaf
+        for (uint32_t l0 = 0; l0 < npp; l0 += LC) {
+            const uint32_t nl = min((uint32_t)LC, npp - l0);
+            if (l0 != 0) {
+                lc = 0;
+                if ((uint32_t)tid < nl) {
+                    const uint32_t leaf = d.pp_pool[pp0 + l0 + tid];
+                    lb = d.nd_begin[leaf];
+                    lc = d.nd_count[leaf];
+                }
+            }
+            // exclusive scan of leaf sizes over the workgroup
+            const uint32_t inc = wave_incl_scan(lc);
+            if (lane == 63) wsum[w] = inc;
+            __syncthreads();
+            uint32_t off = 0, tot = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                off += (k < w) ? wsum[k] : 0u;
+                tot += wsum[k];
+            }
+            lbeg[tid] = lb;
+            lscan[tid] = off + inc - lc;
+            // a chunk of at most PIDX particles lists them all (each thread its
+            // leaf's); a larger one (a few big level-21 leaves) searches
+            const bool ids = LIST_IDS && tot <= (uint32_t)PIDX;
+            if (ids)
+                for (uint32_t k = 0; k < lc; ++k) pid[off + inc - lc + k] = lb + k;
+            __syncthreads();
+            for (uint32_t p0 = 0; p0 < tot; p0 += TJ) {
+                const uint32_t cntt = min((uint32_t)TJ, tot - p0);
+                for (uint32_t e = tid; e < cntt; e += FT) {
+                    const uint32_t f = p0 + e;
+                    uint32_t j;
+                    if (ids) {
+                        j = pid[f];
+                    } else {
+                        uint32_t lo = 0, hi = nl - 1;          // last k with lscan[k] <= f
+                        while (lo < hi) {
+                            const uint32_t mid = (lo + hi + 1) >> 1;
+                            if (lscan[mid] <= f) lo = mid; else hi = mid - 1;
+                        }
+                        j = lbeg[lo] + (f - lscan[lo]);
+                    }
+                    const double4 q = d.pos[j];
+                    tile[e] = mk4<R>((R)(q.x - cen.x), (R)(q.y - cen.y), (R)(q.z - cen.z), (R)q.w);
+                    if (COLL) jidx[e] = j;
+                }
+                compute_tile(cntt, true);
+            }
+        }
+
+        // ---- add the j-slices in a fixed order and write FP64 results
+        if (cw < 64) {
+#pragma unroll
+            for (int off = 32; off >= 8; off >>= 1) {
+                if (off < cw) break;
+                ax += __shfl_xor(ax, off, 64);
+                ay += __shfl_xor(ay, off, 64);
+                az += __shfl_xor(az, off, 64);
+                pot += __shfl_xor(pot, off, 64);
+            }
+        }
+        red[0][w][lane] = ax;
+        red[1][w][lane] = ay;
+        red[2][w][lane] = az;
+        red[3][w][lane] = pot;
+        __syncthreads();
+        if (ion && jslice == 0 && lane < cw) {
+            R sx = 0, sy = 0, sz = 0, sp = 0;
+            for (int k = 0; k < split; ++k) {
+                const int ww = k * n_ic + ichunk;
+                sx += red[0][ww][lane];
+                sy += red[1][ww][lane];
+                sz += red[2][ww][lane];
+                sp += red[3][ww][lane];
+            }
+            double gx = gscale * (double)sx, gy = gscale * (double)sy, gz = gscale * (double)sz;
+            if (d.amag) d.amag[i] = sqrt(gx * gx + gy * gy + gz * gz);
+            if (d.central_mass != 0.0) {
+                const double4 p = d.pos[i];
+                const double r2 = p.x * p.x + p.y * p.y + p.z * p.z;
+                const double r = sqrt(r2);
+                const double f = -d.G * d.central_mass / (r2 * r);
+                gx += f * p.x;
+                gy += f * p.y;
+                gz += f * p.z;
+            }
+            double gp = POT ? gscale * (double)sp : 0.0;
+            if (COLL) {
+                // contact sums of the threads that worked on particle i, in a fixed order
+                double cx = 0, cy = 0, cz = 0, cp = 0;
+                for (int k = 0; k < split; ++k)
+                    for (int sb = 0; sb < sub; ++sb) {
+                        const int th = (k * n_ic + ichunk) * 64 + sb * cw + lane;
+                        cx += cacc[0][th];
+                        cy += cacc[1][th];
+                        cz += cacc[2][th];
+                        cp += cacc[3][th];
+                    }
+                gx += cx;
+                gy += cy;
+                gz += cz;
+                gp += cp;
+            }
+            d.acc[i] = make_double4(gx, gy, gz, POT ? gp : 0.0);
+            if (!COLL && kick_h != 0.0) {
+                double4 v = d.vel[i];
+                v.x = v.x + kick_h * gx;
+                v.y = v.y + kick_h * gy;
+                v.z = v.z + kick_h * gz;
+                d.vel[i] = v;
+            }
+        }
+        // the next item, popped while the first wave writes its results; the
+        // counter wraps to 0 with the launch's last pop (every item pops once)
+        if (tid == FT - 1) s_item = atomicInc(&d.cnt->item_head, items - 1) + gridDim.x;
+        __syncthreads();
+        item = __builtin_amdgcn_readfirstlane(s_item);
     }
 }
 
 template <typename R, bool POT, bool ZERO_EPS>
-void launch_gravity(const DevState &d, const ForceQueue &q, int blocks, double kick_h, hipStream_t s) {
+void launch_gravity(const DevState &d, int blocks, double kick_h, hipStream_t s) {
     if constexpr (sizeof(R) == 4) {
         if (d.force_tile == 256) {
-            k_force<R, POT, ZERO_EPS, false, 256><<<blocks, FT, 0, s>>>(d, q, kick_h);
+            k_force<R, POT, ZERO_EPS, false, 256><<<blocks, FT, 0, s>>>(d, kick_h);
             return;
         }
     }
-    k_force<R, POT, ZERO_EPS, false, TJ_MAX><<<blocks, FT, 0, s>>>(d, q, kick_h);
+    k_force<R, POT, ZERO_EPS, false, TJ_MAX><<<blocks, FT, 0, s>>>(d, kick_h);
 }
 
 template <typename R, bool POT>
-void launch(const DevState &d, const ForceQueue &q, int blocks, double kick_h, hipStream_t s) {
+void launch(const DevState &d, int blocks, double kick_h, hipStream_t s) {
     if (d.rc > 0.0) {
         if (d.eps2 == 0.0)
-            k_force<R, POT, true, true, TJ_MAX><<<blocks, FT, 0, s>>>(d, q, 0.0);
+            k_force<R, POT, true, true, TJ_MAX><<<blocks, FT, 0, s>>>(d, 0.0);
         else
-            k_force<R, POT, false, true, TJ_MAX><<<blocks, FT, 0, s>>>(d, q, 0.0);
+            k_force<R, POT, false, true, TJ_MAX><<<blocks, FT, 0, s>>>(d, 0.0);
     } else if (d.eps2 == 0.0) {
-        launch_gravity<R, POT, true>(d, q, blocks, kick_h, s);
+        launch_gravity<R, POT, true>(d, blocks, kick_h, s);
     } else {
-        launch_gravity<R, POT, false>(d, q, blocks, kick_h, s);
+        launch_gravity<R, POT, false>(d, blocks, kick_h, s);
     }
 }
 
@@ -811,13 +808,13 @@ namespace bhk {
 
 void forces(const DevState &d, uint32_t n_groups, bool fp32, bool pot, int blocks, double kick_h, hipStream_t s) {
     if (n_groups == 0) return;
-    const ForceQueue q = force_queue(n_groups, (uint32_t)d.n_grp, blocks);
+    blocks = (int)std::min<size_t>((size_t)blocks, max_items(n_groups, d.n));
     if (fp32) {
-        if (pot) launch<float, true>(d, q, blocks, kick_h, s);
-        else launch<float, false>(d, q, blocks, kick_h, s);
+        if (pot) launch<float, true>(d, blocks, kick_h, s);
+        else launch<float, false>(d, blocks, kick_h, s);
     } else {
-        if (pot) launch<double, true>(d, q, blocks, kick_h, s);
-        else launch<double, false>(d, q, blocks, kick_h, s);
+        if (pot) launch<double, true>(d, blocks, kick_h, s);
+        else launch<double, false>(d, blocks, kick_h, s);
     }
 }
 

@@ -29,7 +29,8 @@ struct DevCounters {
     uint32_t max_level;
     uint32_t walk_need_front;           // largest frontier seen
     uint32_t walk_need_list;            // longest list seen
-    uint32_t work_counter2;             // force kernel's work queue head
+    uint32_t n_items;                   // force kernel's work items, and its queue head
+    uint32_t item_head;
     // the walk's totals, on cache lines of their own: their atomics go in parallel
     alignas(128) unsigned long long pc_used;    // list-pool fill (may exceed capacity: overflow)
     alignas(128) unsigned long long pp_used;
@@ -127,14 +128,16 @@ struct GroupInfo {
     uint32_t node, begin, count, sys;
 };
 
-// What the force kernel needs of a group, in the order it takes them (one
-// load instead of a chain of three: position in the order, group, system).
+// A work item of the force kernel: up to ITEM_PARTICLES particles of a group and the
+// group's lists (one record instead of a chain of loads over position in the
+// order, group and system).
+constexpr uint32_t ITEM_PARTICLES = 256;
 struct alignas(16) ForceItem {
     double cx, cy, cz;                  // FP32 origin
-    double m0;                          // the system's common particle mass, 0 when masses differ
+    double m0, inv_m0;                  // the system's common particle mass and its inverse, 0 and 1 when masses differ
     unsigned long long pc_off, pp_off;  // list starts in the pools
     uint32_t npc, npp;
-    uint32_t begin, count;
+    uint32_t begin, count;              // this item's particles
 };
 
 // Raw device pointers of a context, passed by value to the launchers.
@@ -174,7 +177,7 @@ struct DevState {
     unsigned long long *g_pc_off, *g_pp_off;   // list starts in the pools (64-bit: pools exceed 2^32)
     uint32_t *g_pc_len, *g_pp_len;
     unsigned long long *g_cost;    // interactions of the group
-    ForceItem *force_items;        // [groups] by descending cost class
+    ForceItem *force_items;        // [cnt->n_items] by descending cost class of their groups
     uint32_t *pc_pool, *pp_pool;
     unsigned long long pc_cap, pp_cap;
     uint32_t *walk_scratch;        // per walking wave: 2 frontiers + 2 lists
@@ -266,6 +269,8 @@ void order_groups(const DevState &d, uint32_t n_groups, hipStream_t s);
 // kick_h != 0 (no collision branch): the closing half kick v += kick_h a is
 // applied in the same launch; with the collision branch it is ignored.
 void forces(const DevState &d, uint32_t n_groups, bool fp32, bool pot, int blocks, double kick_h, hipStream_t s);
+// items of n_groups groups of n particles, at most
+inline size_t max_items(uint32_t n_groups, uint32_t n) { return (size_t)n_groups + n / ITEM_PARTICLES; }
 
 // integration and caller-order output (bh_integrate.hip)
 struct AccPtr {

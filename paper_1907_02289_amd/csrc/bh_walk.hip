@@ -348,8 +348,8 @@ __global__ void k_walk_reset(DevState d) {
 // (the list-length ordering of the paper's load balance, Sec. 4.6), in
 // classes of half an octave of cost; inside a class, ascending group id,
 // i.e. along the Morton curve, so that the groups in flight at one time are
-// neighbours whose lists share most of their sources in L2.  A counting sort:
-// groups of each class per tile, then every tile's block sums the table up to
+// neighbours whose lists share most of their sources in L2.  A counting sort of
+// the groups' work items: items of each class per tile of groups, then every tile's block sums the table up to
 // itself and writes the force kernel's records in place.  At most ORDER_TILES
 // tiles keep the table at 32 KB.  (A radix pass over (class, id) keys and the
 // records were 7 launches, 4 below 8192 groups.)  What bounds these sizes is
@@ -367,12 +367,16 @@ __device__ __forceinline__ uint32_t order_class(const DevState &d, uint32_t g) {
     return 127u - (cls < 127u ? cls : 127u);              // largest cost first
 }
 
+__device__ __forceinline__ uint32_t item_count(const GroupInfo &gi) {
+    return (gi.count + ITEM_PARTICLES - 1) / ITEM_PARTICLES;
+}
+
 __global__ void __launch_bounds__(ORDER_TPB) k_order_count(DevState d, uint32_t ng, uint32_t tile) {
     __shared__ uint32_t cnt[ORDER_CLASSES];
     if (threadIdx.x < ORDER_CLASSES) cnt[threadIdx.x] = 0;
     __syncthreads();
     const uint32_t b = blockIdx.x * tile, e = min(b + tile, ng);
-    for (uint32_t g = b + threadIdx.x; g < e; g += ORDER_TPB) atomicAdd(&cnt[order_class(d, g)], 1u);
+    for (uint32_t g = b + threadIdx.x; g < e; g += ORDER_TPB) atomicAdd(&cnt[order_class(d, g)], item_count(d.grp[g]));
     __syncthreads();
     if (threadIdx.x < ORDER_CLASSES) d.hist[threadIdx.x * gridDim.x + blockIdx.x] = cnt[threadIdx.x];
 }
@@ -380,7 +384,7 @@ __global__ void __launch_bounds__(ORDER_TPB) k_order_count(DevState d, uint32_t 
 __global__ void __launch_bounds__(ORDER_TPB) k_order_place(DevState d, uint32_t ng, uint32_t tile) {
     __shared__ uint32_t start[ORDER_CLASSES], total[ORDER_CLASSES], cnt[ORDER_TPB / 64][ORDER_CLASSES];
     const int lane = __lane_id(), w = threadIdx.x >> 6;
-    // this tile's start in each class: the smaller classes' groups and those of the tiles before
+    // this tile's start in each class: the smaller classes' items and those of the tiles before
     if (threadIdx.x < ORDER_CLASSES) {
         uint32_t before = 0, all = 0;
 #pragma unroll 8
@@ -390,11 +394,13 @@ __global__ void __launch_bounds__(ORDER_TPB) k_order_place(DevState d, uint32_t 
             all += c;
         }
         start[threadIdx.x] = before;
-        total[threadIdx.x] = wave_incl_scan(all) - all;
-        if (threadIdx.x == 63) cnt[0][0] = total[63] + all;
+        const uint32_t inc = wave_incl_scan(all);
+        total[threadIdx.x] = inc - all;
+        if (lane == 63) cnt[w][0] = inc;
     }
     __syncthreads();
-    if (threadIdx.x < ORDER_CLASSES) start[threadIdx.x] += total[threadIdx.x] + (threadIdx.x >= 64 ? cnt[0][0] : 0u);
+    if (threadIdx.x < ORDER_CLASSES) start[threadIdx.x] += total[threadIdx.x] + (w ? cnt[0][0] : 0u);
+    if (blockIdx.x == 0 && threadIdx.x == 0) d.cnt->n_items = cnt[0][0] + cnt[1][0];
     const uint32_t b = blockIdx.x * tile, e = min(b + tile, ng);
     for (uint32_t g0 = b; g0 < e; g0 += ORDER_TPB) {
         __syncthreads();
@@ -402,23 +408,30 @@ __global__ void __launch_bounds__(ORDER_TPB) k_order_place(DevState d, uint32_t 
         __syncthreads();
         const uint32_t g = g0 + threadIdx.x;
         const bool on = g < e;
-        const uint32_t o = on ? order_class(d, g) : 0u;
-        uint64_t same = __ballot(on);                     // lanes of the same class
-#pragma unroll
-        for (int k = 0; k < 7; ++k) {
-            const uint64_t bit = __ballot((o >> k) & 1u);
-            same &= (o >> k) & 1u ? bit : ~bit;
+        const GroupInfo gi = on ? d.grp[g] : GroupInfo{0, 0, 0, 0};
+        const uint32_t o = on ? order_class(d, g) : 0u, items = on ? item_count(gi) : 0u;
+        // items of the same class in the lanes below: class after class
+        uint32_t rank = 0;
+        for (uint64_t left = __ballot(on); left;) {
+            const uint32_t cls = __shfl(o, __ffsll((unsigned long long)left) - 1, 64);
+            const bool mine = on && o == cls;
+            const uint32_t inc = wave_incl_scan(mine ? items : 0u);
+            if (mine) rank = inc - items;
+            if (lane == 63) cnt[w][cls] = inc;
+            left &= ~__ballot(mine);
         }
-        const uint32_t rank = (uint32_t)__popcll(same & lanemask_lt());
-        if (on && rank == 0) cnt[w][o] = (uint32_t)__popcll(same);
         __syncthreads();
         if (on) {
             uint32_t at = start[o] + rank;
             for (int k = 0; k < w; ++k) at += cnt[k][o];
-            const GroupInfo gi = d.grp[g];
             const double4 c = d.g_cen[g];
-            d.force_items[at] = ForceItem{c.x, c.y, c.z, d.sys_m0[gi.sys], d.g_pc_off[g], d.g_pp_off[g], d.g_pc_len[g],
-                                          d.g_pp_len[g], gi.begin, gi.count};
+            const double m0 = d.sys_m0[gi.sys];
+            ForceItem it{c.x, c.y, c.z, m0, m0 > 0.0 ? 1.0 / m0 : 1.0, d.g_pc_off[g], d.g_pp_off[g], d.g_pc_len[g],
+                         d.g_pp_len[g], gi.begin, 0};
+            for (uint32_t k = 0; k < items; ++k, it.begin += ITEM_PARTICLES) {
+                it.count = min(ITEM_PARTICLES, gi.count - k * ITEM_PARTICLES);
+                d.force_items[at + k] = it;
+            }
         }
         __syncthreads();
         if (threadIdx.x < ORDER_CLASSES)
