@@ -68,7 +68,10 @@ struct bh_ctx {
     hipEvent_t tab_ev = nullptr;      // last copy out of the pinned tables
     bool tab_ev_pending = false;
 
-    hipEvent_t ev0[EV_N] = {}, ev1[EV_N] = {};
+    // ends of the timed stages; a stage that starts where another ended shares
+    // its event (an event costs the host a few us, a step of 3001 particles
+    // had nine), and an evaluation's stage is its pair in force_ev
+    hipEvent_t ev0[EV_N] = {}, ev1[EV_N] = {}, ev_from[EV_N] = {}, ev_to[EV_N] = {};
     bool ev_used[EV_N] = {};
     std::vector<std::pair<hipEvent_t, hipEvent_t>> force_ev;   // one pair per force launch
     size_t force_ev_used = 0;
@@ -276,10 +279,17 @@ bh_status check_params(const bh_params *p) {
 
 void ev_begin(bh_ctx *c, int k, hipStream_t s) {
     (void)hipEventRecord(c->ev0[k], s);
+    c->ev_from[k] = c->ev0[k];
 }
 void ev_end(bh_ctx *c, int k, hipStream_t s) {
     (void)hipEventRecord(c->ev1[k], s);
+    c->ev_to[k] = c->ev1[k];
     c->ev_used[k] = true;
+}
+// stage k ends and stage next, always run after it, begins
+void ev_next(bh_ctx *c, int k, int next, hipStream_t s) {
+    ev_end(c, k, s);
+    c->ev_from[next] = c->ev1[k];
 }
 
 bh_status wait_tables(bh_ctx *c) {
@@ -448,12 +458,10 @@ bh_status rebuild(bh_ctx *c, hipStream_t s, bool from_caller) {
     if (from_caller) bhk::load_systems(c->d, s);
     bhk::root_box_keys(c->d, s);
     bhk::permute(c->d, s);
-    ev_end(c, EV_KEYS, s);
+    ev_next(c, EV_KEYS, EV_TREE, s);
     for (;;) {
-        ev_begin(c, EV_TREE, s);
         bhk::build_octree(c->d, s);
-        ev_end(c, EV_TREE, s);
-        ev_begin(c, EV_GROUPS, s);
+        ev_next(c, EV_TREE, EV_GROUPS, s);
         bhk::make_groups(c->d, s);
         ev_end(c, EV_GROUPS, s);
         STCHK(read_counters(c, s));
@@ -470,6 +478,7 @@ bh_status rebuild(bh_ctx *c, hipStream_t s, bool from_caller) {
             if (c->node_cap >= 0x80000000u) return fail(c, BH_ECAPACITY, "tree node capacity cannot grow further");
             STCHK(ensure_nodes(c, c->node_cap * 2));
             refresh_state(c);
+            ev_begin(c, EV_TREE, s);
             continue;
         }
         break;
@@ -604,11 +613,12 @@ bh_status run_forces(bh_ctx *c, hipStream_t s, bool pot, double kick_h) {
         }
     }
     auto &pr = c->force_ev[c->force_ev_used++];
-    ev_begin(c, EV_FORCE, s);
     HIPCHK(c, hipEventRecord(pr.first, s));
     bhk::forces(c->d, c->n_groups, c->P.precision == BH_FP32_REL, pot, force_blocks(c), kick_h, s);
     HIPCHK(c, hipEventRecord(pr.second, s));
-    ev_end(c, EV_FORCE, s);
+    c->ev_from[EV_FORCE] = pr.first;
+    c->ev_to[EV_FORCE] = pr.second;
+    c->ev_used[EV_FORCE] = true;
     c->interactions_evaluated += (int64_t)c->interactions;
     c->force_evaluations += 1;
     c->age += 1;
@@ -864,8 +874,7 @@ bh_status integrate(bh_ctx *c, double dt, int32_t n_steps, int32_t rebuild_every
             } else {
                 ev_begin(c, EV_INTEG, s);
                 bhk::kick_drift(dd, h, dt, s);
-                ev_end(c, EV_INTEG, s);
-                ev_begin(c, EV_MOM, s);
+                ev_next(c, EV_INTEG, EV_MOM, s);
                 if (monitor) bhk::drift_clear(dd, s);
                 bhk::moments(dd, s);
                 ev_end(c, EV_MOM, s);
@@ -1488,9 +1497,9 @@ bh_status bh_stage_times(bh_ctx *c, double *ms) {
     for (int k = 0; k < EV_N; ++k) {
         ms[k] = 0.0;
         if (!c->ev_used[k]) continue;
-        HIPCHK(c, hipEventSynchronize(c->ev1[k]));
+        HIPCHK(c, hipEventSynchronize(c->ev_to[k]));
         float t = 0.f;
-        HIPCHK(c, hipEventElapsedTime(&t, c->ev0[k], c->ev1[k]));
+        HIPCHK(c, hipEventElapsedTime(&t, c->ev_from[k], c->ev_to[k]));
         ms[k] = t;
     }
     return BH_OK;
