@@ -42,7 +42,7 @@ struct bh_ctx {
     std::vector<uint32_t> sys_off;
     bool tree_valid = false, lists_valid = false;
     uint32_t n_nodes = 0, n_groups = 0, max_level = 0;
-    int mom_deep = 0, mom_top = -1;      // launches of a moment pass on the current tree
+    int mom_small = 0, mom_deep = 0, mom_top = -1;      // launches of a moment pass on the current tree
     uint64_t n_pc = 0, n_pp = 0, interactions = 0;
     int n_grp_used = 64;
     bool walk_reset = false;             // the walk's counters are clear (since the last build)
@@ -198,6 +198,7 @@ void refresh_state(bh_ctx *c) {
     d.tree_cnt = P<uint32_t>(c->tree_cnt);
     d.mom_deep = c->mom_deep;
     d.mom_top = c->mom_top;
+    d.mom_small = c->mom_small;
     d.gmark = P<uint32_t>(c->gmark);
     d.grp = P<GroupInfo>(c->grp);
     d.g_lo = P<int4>(c->g_lo);
@@ -486,9 +487,10 @@ bh_status rebuild(bh_ctx *c, hipStream_t s, bool from_caller) {
     c->n_nodes = c->h_cnt->lvl_off[BH_NLEVELS];
     c->max_level = c->h_cnt->max_level;
     c->n_groups = c->h_cnt->n_groups;
-    bhk::moment_plan(c->h_cnt->lvl_off, c->max_level, &c->mom_deep, &c->mom_top);
+    bhk::moment_plan(c->h_cnt->lvl_off, c->max_level, c->n, &c->mom_deep, &c->mom_top, &c->mom_small);
     c->d.mom_deep = c->mom_deep;
     c->d.mom_top = c->mom_top;
+    c->d.mom_small = c->mom_small;
     ev_begin(c, EV_MOM, s);
     bhk::moments(c->d, s);
     if (c->P.criterion == BH_OPEN_LEARNED) bhk::node_qn(c->d, s);

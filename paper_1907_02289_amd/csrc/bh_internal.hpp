@@ -168,6 +168,7 @@ struct DevState {
     double *nd_quad;               // [node_cap][6] second moments (learned rule only), may be null
     uint32_t *tree_cnt;            // [22 levels][tiles of particles] nodes per level and tile, then 22 totals
     int mom_deep, mom_top;         // moment launches: levels mom_deep-1 .. mom_top+1 one each, mom_top .. 0 together
+    int mom_small;                 // != 0: all of them and the leaves in one block
     // groups
     uint32_t *gmark;               // [n] node id + 1 at each group's first particle while groups are made, else 0
     GroupInfo *grp;                // [n] (capacity: one per particle)
@@ -249,8 +250,8 @@ void root_box_keys(const DevState &d, hipStream_t s);
 void permute(const DevState &d, hipStream_t s);
 void build_octree(const DevState &d, hipStream_t s);
 void moments(const DevState &d, hipStream_t s);
-// d.mom_deep and d.mom_top for a tree with these level offsets
-void moment_plan(const uint32_t *lvl_off, uint32_t max_level, int *deep, int *top);
+// d.mom_deep, d.mom_top and d.mom_small for a tree of n particles with these level offsets
+void moment_plan(const uint32_t *lvl_off, uint32_t max_level, uint32_t n, int *deep, int *top, int *small);
 size_t tree_cnt_words(uint32_t n);
 void make_groups(const DevState &d, hipStream_t s);
 // drift monitor: keep the build's positions and moments (after a build) and

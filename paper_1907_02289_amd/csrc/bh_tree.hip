@@ -503,7 +503,7 @@ __global__ void k_node_finalize(DevState d) {
 // in a single launch of one block with a
 // barrier between levels.  One launch per level of the deepest possible tree
 // was 22 launches of 2.4 to 31 us per refresh: 55 us at 4096 particles, 88 at
-// 2^20; now 16 and 50 us.
+// 2^20; now 13 and 45 us.
 
 // Adds n particles to the drift monitor's count of level l, for the lanes with
 // on: one atomic per wave and level (lanes of a wave hold one level or two).
@@ -522,31 +522,56 @@ __device__ __forceinline__ bool has_drifted(const DevState &d, double dr, uint32
     return dr > d.drift_kappa * side;
 }
 
+// Mass and centre of mass of particles [b, e): eight in flight at once, summed in order.
+__device__ __forceinline__ double4 leaf_sum(const DevState &d, uint32_t b, uint32_t e) {
+    double M = 0, sx = 0, sy = 0, sz = 0;
+    for (uint32_t i = b; i < e; i += 8) {
+        double4 p[8];
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k)
+            if (i + k < e) p[k] = d.pos[i + k];
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k)
+            if (i + k < e) {
+                M += p[k].w;
+                sx += p[k].w * p[k].x;
+                sy += p[k].w * p[k].y;
+                sz += p[k].w * p[k].z;
+            }
+    }
+    return make_double4(sx / M, sy / M, sz / M, M);
+}
+
+// Those of a node's children, in order.
+__device__ __forceinline__ double4 child_sum(const double4 q[8], uint32_t nch) {
+    double M = 0, sx = 0, sy = 0, sz = 0;
+#pragma unroll
+    for (uint32_t c = 0; c < 8; ++c)
+        if (c < nch) {
+            M += q[c].w;
+            sx += q[c].w * q[c].x;
+            sy += q[c].w * q[c].y;
+            sz += q[c].w * q[c].z;
+        }
+    return make_double4(sx / M, sy / M, sz / M, M);
+}
+
 // Drift since the build: the largest distance by which a particle of
 // the node has moved relative to the node's centre of mass,
 //   leaf:     max_i |(x_i - x_i^b) - (c - c^b)|,
 //   internal: max_k (drift_k + |(c_k - c_k^b) - (c - c^b)|),
 // an upper bound of the leaf form over the node's particles.
-__global__ void __launch_bounds__(TPB) k_moments_leaf(DevState d) {
+__device__ __forceinline__ void leaf_moments(const DevState &d, uint32_t t0, uint32_t stride) {
     const uint32_t nn = d.cnt->lvl_off[BH_NLEVELS];
-    const uint32_t stride = gridDim.x * blockDim.x;
     const uint32_t end = (nn + 63u) & ~63u;          // whole waves: count_stale needs every lane
-    for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < end; v += stride) {
+    for (uint32_t v = t0; v < end; v += stride) {
         const int4 wr = v < nn ? d.nd_walk[v] : make_int4(0, 1 << 24, 0, 0);
         const bool leaf = ((uint32_t)wr.y >> 24) == 0;
         const int l = (int)((uint32_t)wr.x >> 24);
         bool stale = false;
         if (leaf) {
             const uint32_t b = d.nd_begin[v], e = b + (uint32_t)wr.w;
-            double M = 0, sx = 0, sy = 0, sz = 0;
-            for (uint32_t i = b; i < e; ++i) {
-                double4 p = d.pos[i];
-                M += p.w;
-                sx += p.w * p.x;
-                sy += p.w * p.y;
-                sz += p.w * p.z;
-            }
-            const double4 r = make_double4(sx / M, sy / M, sz / M, M);
+            const double4 r = leaf_sum(d, b, e);
             d.nd_mom[v] = r;
             if (d.nd_drift) {
                 const double4 rb = d.nd_mom_b[v];
@@ -576,6 +601,10 @@ __global__ void __launch_bounds__(TPB) k_moments_leaf(DevState d) {
     }
 }
 
+__global__ void __launch_bounds__(TPB) k_moments_leaf(DevState d) {
+    leaf_moments(d, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+}
+
 // One internal node of level l; returns whether it has drifted.
 __device__ __forceinline__ bool node_moments(const DevState &d, uint32_t v, int4 wr, int l) {
     const uint32_t nch = (uint32_t)wr.y >> 24, f = (uint32_t)wr.w;
@@ -583,16 +612,7 @@ __device__ __forceinline__ bool node_moments(const DevState &d, uint32_t v, int4
 #pragma unroll
     for (uint32_t c = 0; c < 8; ++c)
         if (c < nch) q[c] = d.nd_mom[f + c];        // all in flight at once, summed in order
-    double M = 0, sx = 0, sy = 0, sz = 0;
-#pragma unroll
-    for (uint32_t c = 0; c < 8; ++c)
-        if (c < nch) {
-            M += q[c].w;
-            sx += q[c].w * q[c].x;
-            sy += q[c].w * q[c].y;
-            sz += q[c].w * q[c].z;
-        }
-    const double4 r = make_double4(sx / M, sy / M, sz / M, M);
+    const double4 r = child_sum(q, nch);
     d.nd_mom[v] = r;
     bool stale = false;
     if (d.nd_drift) {
@@ -649,6 +669,53 @@ __global__ void __launch_bounds__(1024) k_moments_top(DevState d, int top) {
     for (int l = min(top, (int)d.cnt->max_level - 1); l >= 0; --l) {
         level_moments(d, l, threadIdx.x, 1024);
         __syncthreads();
+    }
+}
+
+// A whole tree of at most MOM_SMALL nodes in one block, without drift and second
+// moments: its nodes' records loaded at once, the moments passed from level to
+// level in LDS.  Through memory a level waited 1.2 us for its children, and the
+// leaves were a launch of their own: 4.5 + 10.3 us at 3001 particles, now 10.5,
+// at 4096 4.7 + 11 and 13.
+constexpr uint32_t MOM_SMALL = 4096;
+
+__global__ void __launch_bounds__(1024) k_moments_small(DevState d) {
+    __shared__ double4 mom[MOM_SMALL];
+    constexpr int K = MOM_SMALL / 1024;
+    const uint32_t nn = d.cnt->lvl_off[BH_NLEVELS];
+    int4 wr[K];
+    uint32_t begin[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const uint32_t v = threadIdx.x + 1024 * k;
+        wr[k] = v < nn ? d.nd_walk[v] : make_int4(0, 0, 0, 0);
+        begin[k] = v < nn ? d.nd_begin[v] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const uint32_t v = threadIdx.x + 1024 * k;
+        if (v < nn && ((uint32_t)wr[k].y >> 24) == 0) {
+            const double4 r = leaf_sum(d, begin[k], begin[k] + (uint32_t)wr[k].w);
+            mom[v] = r;
+            d.nd_mom[v] = r;
+        }
+    }
+    for (int l = (int)d.cnt->max_level - 1; l >= 0; --l) {
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const uint32_t v = threadIdx.x + 1024 * k;
+            const uint32_t nch = (uint32_t)wr[k].y >> 24, f = (uint32_t)wr[k].w;
+            if (v < nn && nch != 0 && (int)((uint32_t)wr[k].x >> 24) == l) {
+                double4 q[8];
+#pragma unroll
+                for (uint32_t c = 0; c < 8; ++c)
+                    if (c < nch) q[c] = mom[f + c];
+                const double4 r = child_sum(q, nch);
+                mom[v] = r;
+                d.nd_mom[v] = r;
+            }
+        }
     }
 }
 
@@ -849,7 +916,9 @@ void build_octree(const DevState &d, hipStream_t s) {
 // 4 to 5 us per level, as much as a launch of its own.
 constexpr uint32_t MOM_TOP = 1024;
 
-void moment_plan(const uint32_t *lvl_off, uint32_t max_level, int *deep, int *top) {
+void moment_plan(const uint32_t *lvl_off, uint32_t max_level, uint32_t n, int *deep, int *top, int *small) {
+    // one block also sums the leaves: not when they hold many particles each
+    *small = lvl_off[BH_NLEVELS] <= MOM_SMALL && n <= 4 * MOM_SMALL;
     int t = -1;
     while (t + 1 < (int)max_level && lvl_off[t + 2] - lvl_off[t + 1] <= MOM_TOP) ++t;
     // small trees: the one block takes every level, whatever the depth
@@ -859,6 +928,10 @@ void moment_plan(const uint32_t *lvl_off, uint32_t max_level, int *deep, int *to
 }
 
 void moments(const DevState &d, hipStream_t s) {
+    if (d.mom_small && !d.nd_drift && !d.nd_quad) {
+        k_moments_small<<<1, 1024, 0, s>>>(d);
+        return;
+    }
     k_moments_leaf<<<grid_for(d.n, 4096), TPB, 0, s>>>(d);
     for (int l = d.mom_deep - 1; l > d.mom_top; --l) k_moments_level<<<grid_for(d.n / 4, 2048), TPB, 0, s>>>(d, l);
     if (d.mom_top >= 0) k_moments_top<<<1, 1024, 0, s>>>(d, d.mom_top);
