@@ -29,7 +29,9 @@
 // share one LDS tile of sources (the paper's cores sharing a cache on one
 // list).  The waves take 64-particle chunks of the group, the waves left
 // over splitting the source range.  A partial chunk -- a small group, or the
-// last chunk of a larger one -- keeps most of its lanes busy: at most 8, 16 or
+// last chunk of a larger one -- keeps most of its lanes busy.  In FP64 the
+// wave takes as many sub-slices of the source range as the chunk's particles
+// fit into it, up to 8.  In FP32 at most 8, 16 or
 // 25..32 particles spread the wave over 8, 4 or 2 sub-slices of the source
 // range; 17..24, 33..40 and 49..56 particles (3, 5, 7 slices of 8) run in
 // eighths mode and 41..48 in tail mode, where the lanes without particles
@@ -49,7 +51,7 @@
 // in FP64 from the absolute positions and velocities, and summed in FP64
 // apart from the gravity sums.  Particle tiles thus run the 13-instruction
 // body plus a max and a min; node tiles run the plain loop.  These kernels
-// use the sub-slice modes only (no tail or eighths mode, no id list, no
+// use the sub-slices only (no tail or eighths mode, no id list, no
 // fused kick: their LDS and registers are at the six-workgroup limit, and the
 // dashpot reads other particles' velocities).
 #include <algorithm>
@@ -422,7 +424,12 @@ template <typename R, bool POT, bool ZERO_EPS, bool COLL, int TJ>
 __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevState d, double kick_h) {
     static_assert(TJ == 256 || TJ == TJ_MAX, "tile of 256 or 512 sources");
     using T4 = typename V4<R>::T;
-    __shared__ T4 tile[TJ + 16];
+    // tail and eighths mode (below) in the FP32 kernels without the collision branch
+    constexpr bool TAIL = sizeof(R) == 4 && !COLL;
+    // FP32: sub-slices of 8, 16 or 32 lanes (below)
+    constexpr bool POW2 = sizeof(R) == 4;
+    constexpr int PAD = POW2 ? 16 : 64;
+    __shared__ T4 tile[TJ + PAD];
     __shared__ uint32_t lbeg[LC];
     __shared__ uint32_t lscan[LC + 1];
     __shared__ R red[4][4][64];
@@ -443,8 +450,6 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
     // detection margin: a bound on how far FP32 (FP64) rounding of the
     // group-relative coordinates can move a squared distance
     constexpr double U = sizeof(R) == 4 ? 0x1p-20 : 0x1p-49;
-    // tail mode (below) in the FP32 kernels without the collision branch
-    constexpr bool TAIL = sizeof(R) == 4 && !COLL;
 
     const uint32_t items = __builtin_amdgcn_readfirstlane(d.cnt->n_items);
     // the item is the same for the whole workgroup: keep it (and all values
@@ -464,10 +469,15 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
         const uint32_t nb = gi.count;
         // Waves take 64-particle chunks of the block (n_ic of them), the
         // waves left over splitting the source range (split ways).  A chunk
-        // of at most 32 (16, 8) particles -- a small group, or the last chunk
-        // of a larger one -- spreads its wave over 2 (4, 8) sub-slices of its
-        // source range: cw lanes per particle, sub = 64 / cw parts.
-        // split, sub and cw are powers of two: their divisions are shifts
+        // of at most 32 particles -- a small group, or the last chunk of a
+        // larger one -- spreads its wave over sub sub-slices of its source
+        // range, cw lanes each.  FP32: 2, 4 or 8 of 32, 16 or 8 lanes (powers of
+        // two, their divisions are shifts), with TAIL the sizes between in the
+        // modes below.  FP64 (there tail and eighths mode hand sums over at twice
+        // the cost: 0.335 -> 0.385 ms at 9311 groups of 21): as many as fit up to
+        // 8, of exactly the chunk's particles: 3 for 17 to 21 instead of 2
+        // (0.324 -> 0.298 ms at those groups).  With FP32 collisions that would
+        // save 5% of the kernel and change its sums by their rounding.
         const int n_ic = (int)((nb + 63) >> 6);
         const int split_sh = n_ic == 1 ? 2 : (n_ic == 2 ? 1 : 0);
         const int split = 1 << split_sh;                         // 4 / n_ic
@@ -484,10 +494,12 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
         const int s8 = (cnt_w + 7) >> 3;
         const bool e8 = TAIL && (s8 == 3 || s8 == 5 || s8 == 7);
         const int cw_sh = e8 ? 6 : (cnt_w <= 8 ? 3 : (cnt_w <= 16 ? 4 : (cnt_w <= 32 ? 5 : 6)));
-        const int cw = 1 << cw_sh;
         const int sub_sh = 6 - cw_sh;
-        const int sub = 1 << sub_sh;                             // 64 / cw
-        const int part = lane >> cw_sh;
+        const int fit = 64 / max(cnt_w, 8);
+        const int sub = POW2 ? 1 << sub_sh : fit;
+        const int cw = POW2 ? 1 << cw_sh : (fit == 1 ? 64 : cnt_w);
+        // lane / cw: exact, as 64 / 65536 is below 1 / cw
+        const int part = POW2 ? lane >> cw_sh : lane * ((65536 + cw - 1) / cw) >> 16;
         // A chunk of 41 to 48 particles runs in tail mode: lanes 0..47 hold
         // the particles and take the first three quarters of the wave's
         // source range; lanes 48..63 take the last quarter for the three
@@ -498,8 +510,8 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
         const int last_cnt = (int)nb - 64 * (n_ic - 1);
         // the block's last chunk is sub-sliced, tailed or in eighths
         const bool any_sub = last_cnt <= (TAIL ? 56 : 32);
-        const uint32_t il = 64 * ichunk + (lane & (cw - 1));
-        const bool ion = wave_on && il < nb;
+        const uint32_t il = 64 * ichunk + (lane - part * cw);
+        const bool ion = wave_on && il < nb && (POW2 || part < sub);
         const uint32_t i = gi.begin + il;
         R xi = 0, yi = 0, zi = 0;
         if (ion) {
@@ -518,35 +530,51 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
             for (int a = 0; a < 4; ++a) cacc[a][tid] = 0.0;
         }
 
-        // The staged tile holds cntt sources.  With a sub-sliced chunk in the
-        // block the tile is padded with massless far sources to a multiple of
+        // The staged tile holds cntt sources.  FP32: with a sub-sliced chunk in
+        // the block the tile is padded with massless far sources to a multiple of
         // 8 split entries and cut at multiples of 8, so that every part has
         // the same length; full chunks still stop at the last real entry.
+        // FP64: it is padded with 64 of them, each wave cuts it into split
+        // sub parts of one length, an odd one when its lanes read several parts
+        // at once (they then lie in different banks).
         // particles: whether the tile holds particle sources (the only ones
         // the collision branch applies to).
         auto compute_tile = [&](uint32_t cntt, bool particles) {
             const int ct = (int)cntt;
-            const int cntp = any_sub ? ((ct + (8 << split_sh) - 1) >> (3 + split_sh)) << (3 + split_sh) : ct;
+            const int cntp = !POW2 ? ct + PAD
+                             : any_sub ? ((ct + (8 << split_sh) - 1) >> (3 + split_sh)) << (3 + split_sh)
+                                       : ct;
             for (int t = ct + tid; t < cntp; t += FT) tile[t] = mk4<R>((R)1e18, (R)1e18, (R)1e18, (R)0);
             __syncthreads();
             if (wave_on) {
-                int jb, je;
-                if (any_sub) {
-                    const int q = cntp >> 3;
-                    jb = 8 * ((q * jslice) >> split_sh);
-                    je = 8 * ((q * (jslice + 1)) >> split_sh);
+                // this lane's part of the range, [jl0, jl0 + L); the wave's, [jb, je)
+                int jb = 0, je = 0, jl0, L;
+                if constexpr (!POW2) {
+                    const int parts = split * sub;
+                    L = (ct + parts - 1) / parts;
+                    if (sub == 1) {
+                        jl0 = jslice * L;
+                        L = max(0, min(L, ct - jl0));
+                    } else {
+                        L |= 1;
+                        jl0 = (jslice * sub + min(part, sub - 1)) * L;
+                    }
                 } else {
-                    jb = (ct * jslice) >> split_sh;
-                    je = (ct * (jslice + 1)) >> split_sh;
-                }
-                // this lane's part of the range: [jl0, jl0 + L)
-                int jl0, L;
-                if (sub == 1) {
-                    jl0 = jb;
-                    L = max(0, min(je, ct) - jb);
-                } else {
-                    L = (je - jb) >> sub_sh;
-                    jl0 = jb + part * L;
+                    if (any_sub) {
+                        const int q = cntp >> 3;
+                        jb = 8 * ((q * jslice) >> split_sh);
+                        je = 8 * ((q * (jslice + 1)) >> split_sh);
+                    } else {
+                        jb = (ct * jslice) >> split_sh;
+                        je = (ct * (jslice + 1)) >> split_sh;
+                    }
+                    if (sub == 1) {
+                        jl0 = jb;
+                        L = max(0, min(je, ct) - jb);
+                    } else {
+                        L = (je - jb) >> sub_sh;
+                        jl0 = jb + part * L;
+                    }
                 }
                 bool clamp = false;
                 if constexpr (COLL) clamp = particles;
@@ -708,7 +736,7 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
         }
 
         // ---- add the j-slices in a fixed order and write FP64 results
-        if (cw < 64) {
+        if (POW2 && cw < 64) {
 #pragma unroll
             for (int off = 32; off >= 8; off >>= 1) {
                 if (off < cw) break;
@@ -727,10 +755,12 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
             R sx = 0, sy = 0, sz = 0, sp = 0;
             for (int k = 0; k < split; ++k) {
                 const int ww = k * n_ic + ichunk;
-                sx += red[0][ww][lane];
-                sy += red[1][ww][lane];
-                sz += red[2][ww][lane];
-                sp += red[3][ww][lane];
+                for (int l = lane; l < (POW2 ? lane + 1 : sub * cw); l += cw) {
+                    sx += red[0][ww][l];
+                    sy += red[1][ww][l];
+                    sz += red[2][ww][l];
+                    sp += red[3][ww][l];
+                }
             }
             double gx = gscale * (double)sx, gy = gscale * (double)sy, gz = gscale * (double)sz;
             if (d.amag) d.amag[i] = sqrt(gx * gx + gy * gy + gz * gz);
