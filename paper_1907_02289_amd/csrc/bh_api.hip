@@ -53,7 +53,7 @@ struct bh_ctx {
     uint32_t walk_waves = 0, walk_waves_net = 0, walk_front = 4096, walk_list = 8192;
 
     // device buffers
-    DevBuf sys_off_b, sys_tab_b, acc_tab_b, box_b, box_part_b, sys_m0_b;
+    DevBuf sys_tab_b, acc_tab_b, box_b, box_part_b, sys_m0_b;
     DevBuf pos_in, vel_in, idx_in, pos, vel, acc, idx, inv;
     DevBuf key, key_tmp, val, val_tmp, hist, scan_tmp;
     DevBuf nd_prefix, nd_begin, nd_count, nd_first, nd_meta, nd_walk, nd_mom, nd_quad, tree_cnt;
@@ -63,7 +63,7 @@ struct bh_ctx {
 
     // pinned host staging
     DevCounters *h_cnt = nullptr;
-    SysPtr *h_systab = nullptr;
+    char *h_systab = nullptr;            // offsets, then the systems' arrays: sys_tab_b's contents
     bhk::AccPtr *h_acctab = nullptr;
     hipEvent_t tab_ev = nullptr;      // last copy out of the pinned tables
     bool tab_ev_pending = false;
@@ -162,12 +162,15 @@ T *P(DevBuf &b) {
     return reinterpret_cast<T *>(b.p);
 }
 
+// bytes of n_sys + 1 particle offsets, padded for the pointers that follow them
+size_t off_bytes(int n_sys) { return ((size_t)(n_sys + 1) * sizeof(uint32_t) + 15) & ~(size_t)15; }
+
 void refresh_state(bh_ctx *c) {
     DevState &d = c->d;
     d.n_sys = c->n_sys;
     d.n = c->n;
-    d.sys_off = P<uint32_t>(c->sys_off_b);
-    d.sys_tab = P<SysPtr>(c->sys_tab_b);
+    d.sys_off = P<uint32_t>(c->sys_tab_b);
+    d.sys_tab = reinterpret_cast<SysPtr *>(P<char>(c->sys_tab_b) + off_bytes(c->n_sys));
     d.box = P<double4>(c->box_b);
     d.box_part = P<double>(c->box_part_b);
     d.box_blocks = c->box_blocks;
@@ -323,8 +326,7 @@ bh_status ensure_systems(bh_ctx *c, int n_sys) {
     if ((uint32_t)n_sys <= c->sys_cap && c->h_systab) return BH_OK;
     uint32_t cap = std::max<uint32_t>(n_sys, 16);
     STCHK(wait_tables(c));
-    HIPCHK(c, grow(c->sys_off_b, (cap + 1) * sizeof(uint32_t)));
-    HIPCHK(c, grow(c->sys_tab_b, cap * sizeof(SysPtr)));
+    HIPCHK(c, grow(c->sys_tab_b, off_bytes(cap) + cap * sizeof(SysPtr)));
     HIPCHK(c, grow(c->acc_tab_b, cap * sizeof(bhk::AccPtr)));
     HIPCHK(c, grow(c->box_b, cap * sizeof(double4)));
     HIPCHK(c, grow(c->sys_m0_b, cap * sizeof(double)));
@@ -332,7 +334,7 @@ bh_status ensure_systems(bh_ctx *c, int n_sys) {
     if (c->h_acctab) (void)hipHostFree(c->h_acctab);
     c->h_systab = nullptr;
     c->h_acctab = nullptr;
-    HIPCHK(c, hipHostMalloc((void **)&c->h_systab, (cap + 1) * sizeof(SysPtr) + (cap + 1) * sizeof(uint32_t)));
+    HIPCHK(c, hipHostMalloc((void **)&c->h_systab, off_bytes(cap) + cap * sizeof(SysPtr)));
     HIPCHK(c, hipHostMalloc((void **)&c->h_acctab, cap * sizeof(bhk::AccPtr)));
     c->sys_cap = cap;
     return BH_OK;
@@ -456,8 +458,7 @@ bh_status rebuild(bh_ctx *c, hipStream_t s, bool from_caller) {
     ev_begin(c, EV_KEYS, s);
     bhk::reset_flags(c->d, s);
     c->walk_reset = true;
-    if (from_caller) bhk::load_systems(c->d, s);
-    bhk::root_box_keys(c->d, s);
+    bhk::root_box_keys(c->d, from_caller, s);
     bhk::permute(c->d, s);
     ev_next(c, EV_KEYS, EV_TREE, s);
     for (;;) {
@@ -644,9 +645,10 @@ bh_status set_systems(bh_ctx *c, const bh_system *sys, int32_t n_sys, hipStream_
     c->n_sys = n_sys;
     c->n = (uint32_t)total;
     c->sys_off.assign(n_sys + 1, 0);
+    SysPtr *tab = reinterpret_cast<SysPtr *>(c->h_systab + off_bytes(n_sys));
     for (int k = 0; k < n_sys; ++k) {
         c->sys_off[k + 1] = c->sys_off[k] + (uint32_t)sys[k].n;
-        SysPtr &t = c->h_systab[k];
+        SysPtr &t = tab[k];
         t.x = sys[k].x;
         t.y = sys[k].y;
         t.z = sys[k].z;
@@ -656,10 +658,9 @@ bh_status set_systems(bh_ctx *c, const bh_system *sys, int32_t n_sys, hipStream_
         t.m = sys[k].m;
         t.n = sys[k].n;
     }
-    uint32_t *h_off = reinterpret_cast<uint32_t *>(c->h_systab + c->sys_cap + 1);
-    std::copy(c->sys_off.begin(), c->sys_off.end(), h_off);
-    HIPCHK(c, hipMemcpyAsync(c->sys_tab_b.p, c->h_systab, n_sys * sizeof(SysPtr), hipMemcpyHostToDevice, s));
-    HIPCHK(c, hipMemcpyAsync(c->sys_off_b.p, h_off, (n_sys + 1) * sizeof(uint32_t), hipMemcpyHostToDevice, s));
+    std::copy(c->sys_off.begin(), c->sys_off.end(), reinterpret_cast<uint32_t *>(c->h_systab));
+    HIPCHK(c, hipMemcpyAsync(c->sys_tab_b.p, c->h_systab, off_bytes(n_sys) + n_sys * sizeof(SysPtr),
+                             hipMemcpyHostToDevice, s));
     HIPCHK(c, hipEventRecord(c->tab_ev, s));
     c->tab_ev_pending = true;
     // root-box partials: one system alone fills the chip, and the partials
@@ -718,7 +719,7 @@ bh_status bh_create(bh_ctx **out, const bh_params *p) {
 bh_status bh_destroy(bh_ctx *c) {
     if (!c) return BH_EINVAL;
     (void)hipDeviceSynchronize();
-    DevBuf *all[] = {&c->sys_off_b, &c->sys_tab_b, &c->acc_tab_b, &c->box_b, &c->box_part_b, &c->sys_m0_b, &c->pos_in,
+    DevBuf *all[] = {&c->sys_tab_b, &c->acc_tab_b, &c->box_b, &c->box_part_b, &c->sys_m0_b, &c->pos_in,
                      &c->vel_in, &c->idx_in, &c->pos, &c->vel, &c->acc, &c->idx, &c->inv, &c->key, &c->key_tmp,
                      &c->val, &c->val_tmp, &c->hist, &c->scan_tmp, &c->nd_prefix, &c->nd_begin, &c->nd_count,
                      &c->nd_first, &c->nd_meta, &c->nd_walk, &c->nd_mom, &c->nd_quad, &c->tree_cnt,

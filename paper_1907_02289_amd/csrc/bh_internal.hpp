@@ -245,8 +245,8 @@ __device__ __forceinline__ void reset_walk_counters(const DevState &d) {
 namespace bhk {
 
 // tree build (bh_tree.hip)
-void load_systems(const DevState &d, hipStream_t s);
-void root_box_keys(const DevState &d, hipStream_t s);
+// load: from the caller's arrays
+void root_box_keys(const DevState &d, bool load, hipStream_t s);
 void permute(const DevState &d, hipStream_t s);
 void build_octree(const DevState &d, hipStream_t s);
 void moments(const DevState &d, hipStream_t s);

@@ -92,29 +92,30 @@ __device__ __forceinline__ void tree_coords(const DevState &d, double4 p, double
     }
 }
 
-// ---------------------------------------------------------------- load
-__global__ void k_load(DevState d) {
-    uint32_t stride = gridDim.x * blockDim.x;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < d.n; i += stride) {
-        int s = sys_of(d.sys_off, d.n_sys, i);
-        uint32_t j = i - d.sys_off[s];
-        SysPtr p = d.sys_tab[s];
-        d.pos_in[i] = make_double4(p.x[j], p.y[j], p.z[j], p.m[j]);
-        d.vel_in[i] = p.vx ? make_double4(p.vx[j], p.vy[j], p.vz[j], 0.0) : make_double4(0.0, 0.0, 0.0, 0.0);
-        d.idx_in[i] = i;
-        if (d.amag_in) d.amag_in[i] = INFINITY;      // unknown until a force evaluation
-    }
-}
-
 // ---------------------------------------------------------------- root box
+// LOAD: from the caller's arrays, which the same pass copies into the library's
+// records (a launch and 32 bytes per particle less than two passes).
+template <bool LOAD>
 __global__ void __launch_bounds__(TPB) k_box_partial(DevState d) {
     const int s = blockIdx.y;
     const uint32_t b0 = d.sys_off[s], b1 = d.sys_off[s + 1];
     // per axis 0..2 the tree coordinates, axis 3 the mass
     double lo[4] = {INFINITY, INFINITY, INFINITY, INFINITY}, hi[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
     bool bad = false;
+    SysPtr sp;
+    if (LOAD) sp = d.sys_tab[s];
     for (uint32_t i = b0 + blockIdx.x * TPB + threadIdx.x; i < b1; i += d.box_blocks * TPB) {
-        const double4 p = d.pos_in[i];
+        double4 p;
+        if (LOAD) {
+            const uint32_t j = i - b0;
+            p = make_double4(sp.x[j], sp.y[j], sp.z[j], sp.m[j]);
+            d.pos_in[i] = p;
+            d.vel_in[i] = sp.vx ? make_double4(sp.vx[j], sp.vy[j], sp.vz[j], 0.0) : make_double4(0.0, 0.0, 0.0, 0.0);
+            d.idx_in[i] = i;
+            if (d.amag_in) d.amag_in[i] = INFINITY;      // unknown until a force evaluation
+        } else {
+            p = d.pos_in[i];
+        }
         bad |= !isfinite(p.x) || !isfinite(p.y) || !isfinite(p.z);
         double c[4];
         tree_coords(d, p, c);
@@ -409,6 +410,10 @@ __device__ __forceinline__ uint32_t cell_end(const TileKeys &key, bool on, uint3
     return hi;
 }
 
+// Up to this many tiles (16384 particles) a block adds up its level rows itself:
+// some 2 us in place of the scan's launch and 3.
+constexpr uint32_t TREE_FEW = 64;
+
 __global__ void __launch_bounds__(TPB) k_tree_emit(DevState d, uint32_t tiles) {
     __shared__ uint64_t lkey[TREE_TILE + 2 * TREE_PAD + 1];
     __shared__ uint32_t rank[TREE_ROWS][BH_NLEVELS];   // nodes of a row, then its first id, per level
@@ -417,8 +422,20 @@ __global__ void __launch_bounds__(TPB) k_tree_emit(DevState d, uint32_t tiles) {
     unsigned long long total = 0, end = 0;
     uint32_t before = 0;
     if (threadIdx.x < BH_NLEVELS) {
-        total = d.tree_cnt[(size_t)BH_NLEVELS * tiles + threadIdx.x];
-        before = d.tree_cnt[(size_t)threadIdx.x * tiles + blockIdx.x];
+        const uint32_t *cnt = d.tree_cnt + (size_t)threadIdx.x * tiles;
+        if (tiles <= TREE_FEW) {
+            uint32_t all = 0;
+#pragma unroll 8
+            for (uint32_t t = 0; t < tiles; ++t) {
+                const uint32_t c = cnt[t];
+                before += t < blockIdx.x ? c : 0u;
+                all += c;
+            }
+            total = all;
+        } else {
+            total = d.tree_cnt[(size_t)BH_NLEVELS * tiles + threadIdx.x];
+            before = cnt[blockIdx.x];
+        }
     }
     if (threadIdx.x < TREE_ROWS * BH_NLEVELS) (&rank[0][0])[threadIdx.x] = 0;
     const TileKeys key = tile_keys(d, lkey);
@@ -875,12 +892,10 @@ __global__ void __launch_bounds__(TPB) k_group_box(DevState d) {
 
 namespace bhk {
 
-void load_systems(const DevState &d, hipStream_t s) {
-    k_load<<<grid_for(d.n), TPB, 0, s>>>(d);
-}
-
-void root_box_keys(const DevState &d, hipStream_t s) {
-    k_box_partial<<<dim3(d.box_blocks, d.n_sys), TPB, 0, s>>>(d);
+void root_box_keys(const DevState &d, bool load, hipStream_t s) {
+    const dim3 boxes(d.box_blocks, d.n_sys);
+    if (load) k_box_partial<true><<<boxes, TPB, 0, s>>>(d);
+    else k_box_partial<false><<<boxes, TPB, 0, s>>>(d);
     k_box_final<<<d.n_sys, 64, 0, s>>>(d);
     if (sorts_small(d.n)) {
         k_keys<<<grid_for(d.n), TPB, 0, s>>>(d, d.key_tmp, d.val_tmp);
@@ -906,7 +921,7 @@ size_t tree_cnt_words(uint32_t n) { return (size_t)BH_NLEVELS * (tree_tiles(n) +
 void build_octree(const DevState &d, hipStream_t s) {
     const uint32_t tiles = tree_tiles(d.n);
     k_tree_count<<<tiles, TPB, 0, s>>>(d, tiles);
-    k_tree_scan<<<BH_NLEVELS, 1024, 0, s>>>(d, tiles);
+    if (tiles > TREE_FEW) k_tree_scan<<<BH_NLEVELS, 1024, 0, s>>>(d, tiles);
     k_tree_emit<<<tiles, TPB, 0, s>>>(d, tiles);
     k_node_finalize<<<grid_for(d.n, 4096), TPB, 0, s>>>(d);
 }
