@@ -326,10 +326,8 @@ void direct_sum(const double *x, const double *y, const double *z, const double 
                 const int64_t *targets, int64_t nt, double eps2, double G, const Contact *contact, double *ax,
                 double *ay, double *az, double *scratch, hipStream_t s);
 
-// exclusive scan of n uint32 (n from *n_dev when n_dev != nullptr, else n_host);
-// out may alias in.  *total (if non-null) receives the sum.  tmp: >= 1024 words.
-void scan_u32(const uint32_t *in, uint32_t *out, const uint32_t *n_dev, uint32_t n_host,
-              uint32_t *total, uint32_t *tmp, hipStream_t s);
+// exclusive scan of n uint32; out may alias in.  tmp: >= 256 words.
+void scan_u32(const uint32_t *in, uint32_t *out, uint32_t n, uint32_t *tmp, hipStream_t s);
 
 // Stable sort of (key, val) pairs by key, the keys being zero outside bits
 // [lo_bit, hi_bit);

@@ -7,7 +7,7 @@
 //   up to SMALL_MAX pairs: places counted by comparison over the whole chip;
 //   up to SAMPLE_MAX: a sample sort.  Splitters from a sorted sample cut the
 //     pairs into at most 1024 buckets of about 1000 to 2500, in one stable
-//     scatter, and a block sorts each bucket in LDS: eight launches, and two
+//     scatter, and a block sorts each bucket in LDS: seven launches, and two
 //     passes over memory instead of eight;
 //   above: radix passes over memory with 8-bit
 //     digits, per pass one histogram kernel, one scan of the (digit, block)
@@ -49,10 +49,8 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t *wsum, 
     return off + inc - v;
 }
 
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_reduce(const uint32_t *in, const uint32_t *n_dev,
-                                                             uint32_t n_host, uint32_t *part) {
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan_reduce(const uint32_t *in, uint32_t n, uint32_t *part) {
     __shared__ uint32_t wsum[4];
-    uint32_t n = n_dev ? *n_dev : n_host;
     uint32_t chunk = (n + SCAN_BLOCKS - 1) / SCAN_BLOCKS;
     uint32_t b0 = blockIdx.x * chunk;
     uint32_t b1 = min(n, b0 + chunk);
@@ -64,24 +62,17 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_reduce(const uint32_t *in
     if (threadIdx.x == 0) part[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
 }
 
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_top(uint32_t *part, uint32_t *total) {
-    __shared__ uint32_t wsum[4];
-    uint32_t v = part[threadIdx.x];
-    uint32_t tot;
-    uint32_t ex = block_excl_scan(v, wsum, &tot);
-    part[threadIdx.x] = ex;
-    if (threadIdx.x == 0 && total) *total = tot;
-}
-
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_down(const uint32_t *in, uint32_t *out,
-                                                           const uint32_t *n_dev, uint32_t n_host,
+// Every block adds up the partial sums before its own (a launch less than
+// scanning them apart).
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan_down(const uint32_t *in, uint32_t *out, uint32_t n,
                                                            const uint32_t *part) {
+    static_assert(SCAN_BLOCKS == SCAN_THREADS, "one partial sum per thread");
     __shared__ uint32_t wsum[4];
-    uint32_t n = n_dev ? *n_dev : n_host;
     uint32_t chunk = (n + SCAN_BLOCKS - 1) / SCAN_BLOCKS;
     uint32_t b0 = blockIdx.x * chunk;
     uint32_t b1 = min(n, b0 + chunk);
-    uint32_t carry = part[blockIdx.x];
+    uint32_t carry;
+    (void)block_excl_scan(threadIdx.x < blockIdx.x ? part[threadIdx.x] : 0u, wsum, &carry);
     for (uint32_t t0 = b0; t0 < b1; t0 += SCAN_THREADS * SCAN_ITEMS) {
         uint32_t v[SCAN_ITEMS];
         uint32_t base = t0 + threadIdx.x * SCAN_ITEMS;
@@ -818,11 +809,9 @@ __global__ void __launch_bounds__(SS_SORT) k_ss_sort(uint64_t *kin, uint32_t *vi
 
 namespace bhk {
 
-void scan_u32(const uint32_t *in, uint32_t *out, const uint32_t *n_dev, uint32_t n_host,
-              uint32_t *total, uint32_t *tmp, hipStream_t s) {
-    k_scan_reduce<<<SCAN_BLOCKS, SCAN_THREADS, 0, s>>>(in, n_dev, n_host, tmp);
-    k_scan_top<<<1, SCAN_THREADS, 0, s>>>(tmp, total);
-    k_scan_down<<<SCAN_BLOCKS, SCAN_THREADS, 0, s>>>(in, out, n_dev, n_host, tmp);
+void scan_u32(const uint32_t *in, uint32_t *out, uint32_t n, uint32_t *tmp, hipStream_t s) {
+    k_scan_reduce<<<SCAN_BLOCKS, SCAN_THREADS, 0, s>>>(in, n, tmp);
+    k_scan_down<<<SCAN_BLOCKS, SCAN_THREADS, 0, s>>>(in, out, n, tmp);
 }
 
 size_t radix_hist_words(uint32_t n) {
@@ -860,7 +849,7 @@ void radix_sort(uint64_t *key_a, uint32_t *val_a, uint64_t *key_b, uint32_t *val
         if (sys) k_ss_rank<true><<<rows, RANK_THREADS, 0, s>>>(key_b, val_b, L);
         else k_ss_rank<false><<<rows, RANK_THREADS, 0, s>>>(key_b, val_b, L);
         k_ss_hist<<<L.tiles, SS_THREADS, 0, s>>>(key_a, val_a, n, sys_off, n_sys, L);
-        scan_u32(L.hist, L.hist, nullptr, L.buckets * L.tiles, nullptr, tmp, s);
+        scan_u32(L.hist, L.hist, L.buckets * L.tiles, tmp, s);
         k_ss_scatter<<<L.tiles, SS_THREADS, 0, s>>>(key_a, val_a, key_b, val_b, n, L);
         auto last = [&](auto kernel) {
             kernel<<<L.buckets, SS_SORT, 0, s>>>(key_b, val_b, key_a, val_a, n, sys_off, n_sys, L);
@@ -879,7 +868,7 @@ void radix_sort(uint64_t *key_a, uint32_t *val_a, uint64_t *key_b, uint32_t *val
         } else {
             k_radix_hist<false><<<nb, RS_THREADS, 0, s>>>(ki, vi, n, sh, hist, nb, sys_off, n_sys);
         }
-        scan_u32(hist, hist, nullptr, nb * 256, nullptr, tmp, s);
+        scan_u32(hist, hist, nb * 256, tmp, s);
         if (sys) {
             k_radix_scatter<true><<<nb, RS_THREADS, 0, s>>>(ki, vi, ko, vo, n, sh, hist, nb, sys_off, n_sys);
         } else {
