@@ -15,7 +15,8 @@
 // v_rsq_f64 (sixteen); a correctly rounded square root and division were 15
 // more.  cube_inverse() below has none of their range handling, so every tile
 // is checked while it is staged, and one that could leave its range (a
-// coordinate or mass of 2^400 or more, infinite or NaN) takes them as before.
+// coordinate or mass of 2^339 or more, infinite or NaN), or a softening length
+// of 2^340 or more, takes them as before.
 // 4096 targets against 2^20 sources: 7.45 -> 2.95 ms; loops unrolled 1 to 8
 // times at 5 to 8 waves per SIMD are within 1%.  1000 targets of 60000: 2.70
 // -> 0.073 ms, by the smaller chunks (chosen in launch()).  Each tile's 64
@@ -46,10 +47,12 @@ constexpr int MAX_DEVICES = 64;
 std::mutex scratch_mu;
 double *scratch_dev[MAX_DEVICES] = {};
 
-constexpr double WIDE = 0x1p400;         // coordinates and masses from here on take the exact pair
+// coordinates and masses from WIDE on, and any eps^2 from WIDE_EPS2 on, take the exact pair: below them
+// r^2 < 2^682 and the exact pair's r^3 is finite, so that both pairs give a term or none alike
+constexpr double WIDE = 0x1p339, WIDE_EPS2 = 0x1p680;
 constexpr double TIGHT = 0x1p-300;       // and so do squared distances below
 
-// m x^(-3/2) for TIGHT <= x < 3 * 2^802: the hardware estimate y of x^(-1/2) (relative
+// m x^(-3/2) for TIGHT <= x < 2^682: the hardware estimate y of x^(-1/2) (relative
 // error below 2^-24) and e = 1 - x y^2 give it as m y^3 (1 + 3/2 e + 15/8 e^2 + ...),
 // the next term below 2^-67.  A rounding d of y^2 enters y^3 as d and the
 // correction as -3/2 d: four roundings, one of them halved, against the three
@@ -96,7 +99,7 @@ __global__ void __launch_bounds__(DT) k_direct_part(const double *x, const doubl
     double ax = 0, ay = 0, az = 0, cx = 0, cy = 0, cz = 0;
     for (int64_t b = j0; b < j1; b += DT) {
         const int64_t j = b + threadIdx.x;
-        bool wide = far_i;
+        bool wide = far_i || !(eps2 < WIDE_EPS2);
         if (j < j1) {
             const double4 s = make_double4(x[j], y[j], z[j], m[j]);
             tile[threadIdx.x] = s;
