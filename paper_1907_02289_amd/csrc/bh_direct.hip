@@ -99,13 +99,14 @@ __global__ void __launch_bounds__(DT) k_direct_part(const double *x, const doubl
     double ax = 0, ay = 0, az = 0, cx = 0, cy = 0, cz = 0;
     for (int64_t b = j0; b < j1; b += DT) {
         const int64_t j = b + threadIdx.x;
-        bool wide = far_i || !(eps2 < WIDE_EPS2);
+        bool wide = !(eps2 < WIDE_EPS2);
         if (j < j1) {
             const double4 s = make_double4(x[j], y[j], z[j], m[j]);
             tile[threadIdx.x] = s;
             wide = wide || !(fabs(s.x) < WIDE && fabs(s.y) < WIDE && fabs(s.z) < WIDE && fabs(s.w) < WIDE);
         }
-        const bool exact = __syncthreads_or(wide);
+        // a far target decides for its own lane: the others' bits do not depend on it
+        const bool exact = __syncthreads_or(wide) || far_i;
         const int cnt = (int)((j1 - b < DT) ? j1 - b : DT);
         const int q0 = cnt * w / 4, q1 = cnt * (w + 1) / 4;
         double tx = 0, ty = 0, tz = 0;
