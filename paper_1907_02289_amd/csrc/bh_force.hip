@@ -587,8 +587,9 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
                     else
                         tile_pass<R, POT, ZERO_EPS, true, false>(tile, sub, jl0, L, xi, yi, zi, eps2, rce2, ax,
                                                                  ay, az, pot, cmin);
+                    // the real entries only: the padding has no particle, and at a radius of 1e18 it is in reach
                     if (__ballot(ion && cmin <= rcd2) != 0)
-                        contact_pass<R, POT>(tile, jidx, jl0, L, xi, yi, zi, eps2, rcd2, ion, i, d,
+                        contact_pass<R, POT>(tile, jidx, jl0, min(L, ct - jl0), xi, yi, zi, eps2, rcd2, ion, i, d,
                                              &cacc[0][tid]);
                 } else if (e8) {
                     const int Q = (je - jb) >> 3;
