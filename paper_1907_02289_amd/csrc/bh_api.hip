@@ -594,13 +594,6 @@ bh_status make_lists(bh_ctx *c, hipStream_t s) {
     return order_lists(c, s);
 }
 
-// Persistent workgroups of the force kernel: as many as stay resident (FP32:
-// 6 per CU by its register cap; FP64: 5 by its cap, 3 with the collision branch).
-int force_blocks(const bh_ctx *c) {
-    if (c->P.precision == BH_FP32_REL) return c->n_cu * 6;
-    return c->n_cu * (c->P.r_coll > 0.0 ? 3 : 5);
-}
-
 // kick_h != 0: the launch also applies the closing half kick v += kick_h a.
 // The kernels with the collision branch ignore it, so callers pass it only
 // when the branch is off.
@@ -617,7 +610,7 @@ bh_status run_forces(bh_ctx *c, hipStream_t s, bool pot, double kick_h) {
     }
     auto &pr = c->force_ev[c->force_ev_used++];
     HIPCHK(c, hipEventRecord(pr.first, s));
-    bhk::forces(c->d, c->n_groups, c->P.precision == BH_FP32_REL, pot, force_blocks(c), kick_h, s);
+    bhk::forces(c->d, c->n_groups, c->P.precision == BH_FP32_REL, pot, c->n_cu, kick_h, s);
     HIPCHK(c, hipEventRecord(pr.second, s));
     c->ev_from[EV_FORCE] = pr.first;
     c->ev_to[EV_FORCE] = pr.second;
@@ -1061,7 +1054,7 @@ bh_status bh_autotune(bh_ctx *c, const int32_t *cand, int32_t n_cand, int32_t re
             // one evaluation before the timed ones: the first on new lists finds no
             // sources in the caches, and would count against the tile tried first
             refresh_state(c);
-            bhk::forces(c->d, c->n_groups, c->P.precision == BH_FP32_REL, false, force_blocks(c), 0.0, s);
+            bhk::forces(c->d, c->n_groups, c->P.precision == BH_FP32_REL, false, c->n_cu, 0.0, s);
             for (int tile : tiles) {
                 c->P.force_tile = tile;
                 refresh_state(c);

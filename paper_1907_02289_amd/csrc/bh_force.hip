@@ -405,15 +405,20 @@ __device__ __forceinline__ ForceItem uniform_item(const ForceItem *p) {
     return u.item;
 }
 
-// FP32: registers capped so that 6 workgroups (24 waves) fit a CU; the
-// pair loop needs the occupancy to hide LDS and rsqrt latency (measured:
-// 100 VGPRs / 4 waves per SIMD ran 18% slower; the collision variant, at
-// 5 workgroups without spills, ran 3% slower than at 6 with a few).  FP64
-// gravity-only: 5 workgroups (<= 96 VGPRs, no spills); the FP64 collision
-// variant keeps the default.
+// Workgroups per CU: the kernels' register caps, and what a launch starts, so
+// that every block is resident from the start (a block's first item is the one
+// of its number, among the most expensive; a block that waits for room would
+// begin it when the others have emptied the queue).
+// FP32: 6 (24 waves); the pair loop needs them to hide LDS and rsqrt latency
+// (measured: 100 VGPRs / 4 waves per SIMD ran 18% slower; the collision
+// variant, at 5 without spills, ran 3% slower than at 6 with some 40 spilled).
+// FP64 gravity-only: 5 (<= 96 VGPRs, no spills); with the collision branch 3
+// (141 VGPRs; uncapped, the variant with potentials took 169 and held 2 of the
+// 3: 130003 particles in 3084 groups 0.178 -> 0.128 ms per evaluation, 2^20 in
+// 3039 groups 1.92 -> 1.47 ms).
 template <typename R, bool COLL>
 struct ForceOcc {
-    static constexpr int blocks = sizeof(R) == 4 ? 6 : (COLL ? 1 : 5);
+    static constexpr int blocks = sizeof(R) == 4 ? 6 : (COLL ? 3 : 5);
 };
 
 template <typename R, bool POT, bool ZERO_EPS, bool COLL, int TJ>
@@ -808,44 +813,47 @@ __global__ void __launch_bounds__(FT, (ForceOcc<R, COLL>::blocks)) k_force(DevSt
     }
 }
 
+// n_cu compute units, items: an upper bound of the launch's items
+template <typename R, bool POT, bool ZERO_EPS, bool COLL, int TJ>
+void launch_kernel(const DevState &d, size_t items, int n_cu, double kick_h, hipStream_t s) {
+    const unsigned blocks = (unsigned)std::min<size_t>((size_t)n_cu * ForceOcc<R, COLL>::blocks, items);
+    k_force<R, POT, ZERO_EPS, COLL, TJ><<<blocks, FT, 0, s>>>(d, kick_h);
+}
+
 template <typename R, bool POT, bool ZERO_EPS>
-void launch_gravity(const DevState &d, int blocks, double kick_h, hipStream_t s) {
+void launch(const DevState &d, size_t items, int n_cu, double kick_h, hipStream_t s) {
+    if (d.rc > 0.0) {
+        launch_kernel<R, POT, ZERO_EPS, true, TJ_MAX>(d, items, n_cu, 0.0, s);
+        return;
+    }
     if constexpr (sizeof(R) == 4) {
         if (d.force_tile == 256) {
-            k_force<R, POT, ZERO_EPS, false, 256><<<blocks, FT, 0, s>>>(d, kick_h);
+            launch_kernel<R, POT, ZERO_EPS, false, 256>(d, items, n_cu, kick_h, s);
             return;
         }
     }
-    k_force<R, POT, ZERO_EPS, false, TJ_MAX><<<blocks, FT, 0, s>>>(d, kick_h);
+    launch_kernel<R, POT, ZERO_EPS, false, TJ_MAX>(d, items, n_cu, kick_h, s);
 }
 
 template <typename R, bool POT>
-void launch(const DevState &d, int blocks, double kick_h, hipStream_t s) {
-    if (d.rc > 0.0) {
-        if (d.eps2 == 0.0)
-            k_force<R, POT, true, true, TJ_MAX><<<blocks, FT, 0, s>>>(d, 0.0);
-        else
-            k_force<R, POT, false, true, TJ_MAX><<<blocks, FT, 0, s>>>(d, 0.0);
-    } else if (d.eps2 == 0.0) {
-        launch_gravity<R, POT, true>(d, blocks, kick_h, s);
-    } else {
-        launch_gravity<R, POT, false>(d, blocks, kick_h, s);
-    }
+void launch(const DevState &d, size_t items, int n_cu, double kick_h, hipStream_t s) {
+    if (d.eps2 == 0.0) launch<R, POT, true>(d, items, n_cu, kick_h, s);
+    else launch<R, POT, false>(d, items, n_cu, kick_h, s);
 }
 
 }  // namespace
 
 namespace bhk {
 
-void forces(const DevState &d, uint32_t n_groups, bool fp32, bool pot, int blocks, double kick_h, hipStream_t s) {
+void forces(const DevState &d, uint32_t n_groups, bool fp32, bool pot, int n_cu, double kick_h, hipStream_t s) {
     if (n_groups == 0) return;
-    blocks = (int)std::min<size_t>((size_t)blocks, max_items(n_groups, d.n));
+    const size_t items = max_items(n_groups, d.n);
     if (fp32) {
-        if (pot) launch<float, true>(d, blocks, kick_h, s);
-        else launch<float, false>(d, blocks, kick_h, s);
+        if (pot) launch<float, true>(d, items, n_cu, kick_h, s);
+        else launch<float, false>(d, items, n_cu, kick_h, s);
     } else {
-        if (pot) launch<double, true>(d, blocks, kick_h, s);
-        else launch<double, false>(d, blocks, kick_h, s);
+        if (pot) launch<double, true>(d, items, n_cu, kick_h, s);
+        else launch<double, false>(d, items, n_cu, kick_h, s);
     }
 }
 

@@ -266,10 +266,10 @@ void walk(const DevState &d, uint32_t n_groups, bool reset, hipStream_t s);
 constexpr size_t ORDER_WORDS = 64 * 128;      // d.hist holds at least as many
 void order_groups(const DevState &d, uint32_t n_groups, hipStream_t s);
 
-// forces (bh_force.hip): blocks = persistent workgroups
+// forces (bh_force.hip) on n_cu compute units
 // kick_h != 0 (no collision branch): the closing half kick v += kick_h a is
 // applied in the same launch; with the collision branch it is ignored.
-void forces(const DevState &d, uint32_t n_groups, bool fp32, bool pot, int blocks, double kick_h, hipStream_t s);
+void forces(const DevState &d, uint32_t n_groups, bool fp32, bool pot, int n_cu, double kick_h, hipStream_t s);
 // items of n_groups groups of n particles, at most
 inline size_t max_items(uint32_t n_groups, uint32_t n) { return (size_t)n_groups + n / ITEM_PARTICLES; }
 
