@@ -37,6 +37,9 @@ struct DevCounters {
     alignas(128) unsigned long long interactions;
     unsigned long long cand_used;       // learned rule: candidate pairs recorded (may exceed capacity)
     uint32_t stale[BH_NLEVELS];         // drift monitor: particles in drifted nodes, per level
+    struct alignas(128) {
+        unsigned long long taken;
+    } walk_round[8];                    // the walk's rounds taken per XCD, beyond one per block
 };
 
 // ---------------------------------------------------------------- wave helpers
@@ -240,6 +243,7 @@ __device__ __forceinline__ void reset_walk_counters(const DevState &d) {
     d.cnt->flags[FLAG_WALK_BOUND] = 0;
     d.cnt->flags[FLAG_CAND_BAD] = 0;
     d.cnt->cand_used = 0;
+    for (auto &r : d.cnt->walk_round) r.taken = 0;
 }
 
 namespace bhk {

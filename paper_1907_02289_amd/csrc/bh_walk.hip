@@ -18,6 +18,8 @@
 // cylindrical tree coordinates (Sec. 4.3) the phi axis is periodic with one
 // turn = 2^21 grid units: its distance is that of the node's nearest image
 // (a node and a group box inside one turn overlap only directly).
+#include <algorithm>
+
 #include "bh_learned.hpp"
 
 namespace {
@@ -107,19 +109,33 @@ __device__ __forceinline__ Verdict judge(const DevState &d, const GroupCtx &gc, 
     return NETWORK;
 }
 
+// Rounds: four consecutive groups, one per wave of a block.  Runs of WALK_CHUNK
+// rounds go to the XCDs in turn: walk_share is the most that one XCD has.
+constexpr uint32_t WALK_CHUNK = 8;
+__host__ __device__ inline uint32_t walk_rounds(uint32_t n_groups) { return (n_groups + WALK_TPB / 64 - 1) / (WALK_TPB / 64); }
+__host__ __device__ inline uint32_t walk_share(uint32_t rounds) {
+    return (rounds + 8 * WALK_CHUNK - 1) / (8 * WALK_CHUNK) * WALK_CHUNK;
+}
+
 // Persistent blocks of four waves, one group per wave and round.  What
 // bounded an earlier form was neither the walk's memory traffic nor its
 // arithmetic but atomics on one cache line: each wave popped its groups from
 // a counter and reserved its list space with four more returning atomics per
 // group, and same-line atomics of the whole chip are served one per 12 ns
 // (measured: walk time / number of atomics = 11.6..12.4 ns from 172 to
-// 138,763 groups).  Now a wave's groups follow from its index (no counter),
-// the four waves of a block reserve list space together, the two pools with
-// one instruction on two cache lines (one atomic per pool and four groups),
-// and the interaction total is summed in registers and added once per block.
-// Blocks are dealt to the eight XCDs in turn, so each XCD takes one eighth of
-// the groups, contiguous along the curve: neighbouring groups open the same
-// nodes, which then stay in that XCD's L2.
+// 138,763 groups).  Now a block takes rounds of four consecutive groups, the
+// first by its number, further ones from its XCD's counter; its waves reserve
+// list space together, the two pools and the next round with one instruction on
+// three cache lines, and the interaction total is summed in registers and added
+// once per block.
+// Blocks are dealt to the eight XCDs in turn, and so are runs of WALK_CHUNK
+// rounds along the curve: neighbouring groups open the same nodes, which stay in
+// that XCD's L2, while a region of long walks (a dense centre, one large system
+// among small ones) spreads over all XCDs.  One contiguous eighth per XCD with
+// its rounds dealt by block number left XCDs idle: Plummer sphere of 2^22
+// particles, theta 0.1, 121 -> 100 ms; of 2^21 with 3000 rings of 100 beside it
+// 55.9 -> 39.9 ms; ring of 2^22 in 400,633 groups, theta 0.3, 3.5 -> 2.8 ms.
+// Runs of 4 rounds take the same time, runs of 32 up to 5% more.
 // The next 64 nodes are loaded before the current 64 are tested; a leaf's
 // particle count rides in the node record, so a visit is one 16-byte load.
 // Kernel time before and after: 172 groups (4096-particle ring) 105 -> 15 us,
@@ -128,10 +144,10 @@ __device__ __forceinline__ Verdict judge(const DevState &d, const GroupCtx &gc, 
 // 10^4-entry lists (2^24, theta 0.0865) the visits themselves take the time,
 // 5.2 -> 4.9 ms.
 // GEO: the instance of the geometric rule, without the registers of the
-// network.  The other one has 248 (two waves per SIMD): held to 168 or 128 its
-// walks took 3% and 10% longer.
+// network.  The other one has 227 (two waves per SIMD, as many as are launched):
+// held to 168 or 128 its walks took 3% and 10% longer.
 template <bool GEO>
-__global__ void __launch_bounds__(WALK_TPB, (GEO ? 8 : 1)) k_walk(DevState d) {
+__global__ void __launch_bounds__(WALK_TPB, (GEO ? 8 : 2)) k_walk(DevState d) {
     constexpr uint32_t WPB = WALK_TPB / 64;
     const uint32_t wib = threadIdx.x >> 6;
     const uint32_t wave = blockIdx.x * WPB + wib;
@@ -159,17 +175,18 @@ __global__ void __launch_bounds__(WALK_TPB, (GEO ? 8 : 1)) k_walk(DevState d) {
         __syncthreads();
     }
     __shared__ uint32_t s_len[WPB][2];             // list lengths of the block's four groups
-    __shared__ unsigned long long s_at[2];         // the block's starts in the two pools
+    __shared__ unsigned long long s_at[3];         // the block's starts in the two pools, and its next round
     __shared__ unsigned long long s_cost[WPB];
     unsigned long long cost_sum = 0;
 
-    // the block's groups: every bx-th group of four in its XCD's eighth
-    const uint32_t xcd = blockIdx.x & 7u, bx = gridDim.x >> 3;        // gridDim.x is a multiple of 8
-    const uint32_t g_lo = (uint32_t)((unsigned long long)ng * xcd >> 3);
-    const uint32_t g_hi = (uint32_t)((unsigned long long)ng * (xcd + 1) >> 3);
-    for (uint32_t g0 = g_lo + (blockIdx.x >> 3) * WPB; g0 < g_hi; g0 += bx * WPB) {
+    const uint32_t rounds = walk_rounds(ng), xcd = blockIdx.x & 7u, bx = gridDim.x >> 3;    // gridDim.x is a multiple of 8
+    const bool more = bx < walk_share(rounds);     // rounds beyond one per block
+    for (uint32_t k = blockIdx.x >> 3;;) {
+        const uint32_t round = (k / WALK_CHUNK * 8 + xcd) * WALK_CHUNK + k % WALK_CHUNK;
+        if (round >= rounds) break;
+        const uint32_t g0 = round * WPB;
         const uint32_t g = g0 + wib;
-        const bool has = g < g_hi;
+        const bool has = g < ng;
         uint32_t npc = 0, npp = 0, n_part = 0;
         unsigned long long pp_particles = 0;
         bool skip = !has;       // no lists to store (no group, or its walk was cut short)
@@ -300,23 +317,29 @@ __global__ void __launch_bounds__(WALK_TPB, (GEO ? 8 : 1)) k_walk(DevState d) {
             s_len[wib][1] = npp;
         }
         __syncthreads();
-        if (threadIdx.x < 2) {
-            unsigned long long sum = 0;
-            for (uint32_t k = 0; k < WPB; ++k) sum += s_len[k][threadIdx.x];
-            unsigned long long *head = threadIdx.x == 0 ? &d.cnt->pc_used : &d.cnt->pp_used;
+        if (threadIdx.x < 3) {                  // three cache lines in one instruction
+            unsigned long long sum = more ? 1 : 0;
+            if (threadIdx.x < 2) {
+                sum = 0;
+                for (uint32_t q = 0; q < WPB; ++q) sum += s_len[q][threadIdx.x];
+            }
+            unsigned long long *head = threadIdx.x == 0   ? &d.cnt->pc_used
+                                       : threadIdx.x == 1 ? &d.cnt->pp_used
+                                                          : &d.cnt->walk_round[xcd].taken;
             s_at[threadIdx.x] = sum ? atomicAdd(head, sum) : 0ull;
         }
         __syncthreads();
         unsigned long long at_pc = s_at[0], at_pp = s_at[1];
-        for (uint32_t k = 0; k < wib; ++k) {
-            at_pc += s_len[k][0];
-            at_pp += s_len[k][1];
+        k = __builtin_amdgcn_readfirstlane((uint32_t)s_at[2]) + bx;     // past the end when there is no more
+        for (uint32_t q = 0; q < wib; ++q) {
+            at_pc += s_len[q][0];
+            at_pp += s_len[q][1];
         }
         const bool fit = !skip && (at_pc + npc <= d.pc_cap) && (at_pp + npp <= d.pp_cap);
         if (fit) {
             __threadfence_block();              // the scratch lists, written by other lanes
-            for (uint32_t k = lane; k < npc; k += 64) d.pc_pool[at_pc + k] = pcb[k];
-            for (uint32_t k = lane; k < npp; k += 64) d.pp_pool[at_pp + k] = ppb[k];
+            for (uint32_t q = lane; q < npc; q += 64) d.pc_pool[at_pc + q] = pcb[q];
+            for (uint32_t q = lane; q < npp; q += 64) d.pp_pool[at_pp + q] = ppb[q];
         } else if (lane == 0 && !skip) {
             atomicOr(&d.cnt->flags[FLAG_POOL_OVF], 1u);
         }
@@ -446,14 +469,10 @@ namespace bhk {
 void walk(const DevState &d, uint32_t n_groups, bool reset, hipStream_t s) {
     if (reset) k_walk_reset<<<1, 64, 0, s>>>(d);
     if (n_groups == 0) return;
-    // as many blocks as stay resident (and have scratch), fewer when there are
-    // fewer groups than waves; a multiple of 8, one share per XCD
+    // as many blocks as stay resident (and have scratch), one per round when there are
+    // fewer rounds; a multiple of 8, one share per XCD
     const uint32_t waves = d.walk_mode == WALK_GEOMETRIC ? d.walk_waves : d.walk_waves_net;
-    constexpr uint32_t WPB = WALK_TPB / 64;
-    const uint32_t most = waves / WPB & ~7u;
-    const uint32_t want = ((n_groups + WPB - 1) / WPB + 7) & ~7u;
-    // each XCD's share of the groups may need one more block than the even split
-    const uint32_t blocks = want + 8 < most ? want + 8 : most;
+    const uint32_t blocks = std::min(waves / (WALK_TPB / 64) & ~7u, 8 * walk_share(walk_rounds(n_groups)));
     if (d.walk_mode == WALK_GEOMETRIC)
         k_walk<true><<<blocks, WALK_TPB, 0, s>>>(d);
     else
