@@ -20,8 +20,11 @@
 #include <type_traits>
 
 #include "bh_internal.hpp"
+#include "bh_sort_plan.hpp"
 
 namespace {
+
+using namespace bhk;
 
 constexpr int SCAN_BLOCKS = 256;
 constexpr int SCAN_THREADS = 256;
@@ -445,7 +448,6 @@ __device__ __forceinline__ PairSpan block_span(const uint64_t *kin, const uint32
 // launch, n^2 comparisons dealt to blocks of RANK_ROWS pairs (4096 pairs:
 // 10 us; one block sorting them in its LDS took 36 to 43).  The
 // sample sort ranks its sample the same way.
-constexpr uint32_t SMALL_MAX = 8192;
 constexpr uint32_t RANK_ROWS = 32, RANK_CHUNK = 2048, RANK_THREADS = 1024;
 
 // Ranks of pairs row0 .. row0 + 31 of the block among m pairs with systems
@@ -516,17 +518,14 @@ __global__ void __launch_bounds__(RANK_THREADS) k_sort_small(const uint64_t *key
 }
 
 // ---------------------------------------------------------------- sample sort
-// n pairs, B buckets (8..1024) of n / B pairs on average, cut by a sample of 8
-// pairs per bucket.  A bucket outgrows the LDS of its block (4096 pairs, 8192
-// above 2^20 pairs: four and three times the average) only where the sample
-// misses a stretch of 25 times its mean gap and more (below 1e-3 per sort of
-// the largest size, 1e-4 at 2^20) or in an input made to defeat it; such a
-// bucket is sorted by its block over memory.  Keys that fill a bucket by
+// n pairs, B buckets (8..1024) of n / B pairs on average, cut by a sample of 8 or
+// 16 pairs per bucket (sample_plan).  A bucket outgrows the LDS of its block only
+// where the sample happens to miss a stretch of its pairs (the plan states how
+// often) or in an input made to defeat it; such a bucket is sorted by its block
+// over memory.  Keys that fill a bucket by
 // themselves show as repeated splitters and get a bucket of their own, which
 // needs no sorting: with lb (ub) splitters below (not above)
 // a pair, its bucket is ub, and lb + 1 when it equals two splitters or more.
-constexpr uint32_t SAMPLE_MAX = 5u << 19;       // 2.6e6 pairs
-constexpr uint32_t BUCKETS_MAX = 1024;
 constexpr int SS_THREADS = 512;                 // histogram and scatter
 constexpr int SS_SORT = 512;                    // bucket sort: 1024 threads took 25 instead of 30 us at 2e5 pairs, 44 instead of 31 at 2^20
 constexpr uint32_t SS_TILE = 4096;              // pairs per scatter block
@@ -540,19 +539,14 @@ struct SampleLayout {
     uint16_t *bucket;                           // [n]
 };
 
-__host__ __device__ inline uint32_t ss_buckets(uint32_t n) {
-    const uint32_t b = (n + 1023) / 1024;
-    return b < 8 ? 8u : (b > BUCKETS_MAX ? BUCKETS_MAX : b);
-}
-
 inline size_t ss_words(uint32_t n) {
-    return 3 * (size_t)BUCKETS_MAX + (size_t)ss_buckets(n) * ((n + SS_TILE - 1) / SS_TILE) + (n + 1) / 2;
+    return 3 * (size_t)BUCKETS_MAX + (size_t)sample_plan(n, false).buckets * ((n + SS_TILE - 1) / SS_TILE) + (n + 1) / 2;
 }
 
-inline SampleLayout ss_layout(uint32_t n, uint32_t *scratch) {
+inline SampleLayout ss_layout(uint32_t n, const SamplePlan &p, uint32_t *scratch) {
     SampleLayout s;
-    s.buckets = ss_buckets(n);
-    s.per = 8;
+    s.buckets = p.buckets;
+    s.per = p.per;
     s.stretch = ((uint64_t)n << 32) / (s.buckets * s.per);
     s.tiles = (n + SS_TILE - 1) / SS_TILE;
     s.split_key = reinterpret_cast<uint64_t *>(scratch);
@@ -842,9 +836,10 @@ void radix_sort(uint64_t *key_a, uint32_t *val_a, uint64_t *key_b, uint32_t *val
         return;
     }
     if (n <= SAMPLE_MAX) {
-        const SampleLayout L = ss_layout(n, hist);
+        const bool sys = n_sys > 1;
+        const SamplePlan plan = sample_plan(n, sys);
+        const SampleLayout L = ss_layout(n, plan, hist);
         const uint32_t rows = (L.buckets * L.per + RANK_ROWS - 1) / RANK_ROWS;
-        const bool sys = n_sys > 1, wide = n > (1u << 20);
         k_ss_gather<<<(L.buckets * L.per + 255) / 256, 256, 0, s>>>(key_a, val_a, sys_off, n_sys, L, key_b, val_b);
         if (sys) k_ss_rank<true><<<rows, RANK_THREADS, 0, s>>>(key_b, val_b, L);
         else k_ss_rank<false><<<rows, RANK_THREADS, 0, s>>>(key_b, val_b, L);
@@ -854,8 +849,8 @@ void radix_sort(uint64_t *key_a, uint32_t *val_a, uint64_t *key_b, uint32_t *val
         auto last = [&](auto kernel) {
             kernel<<<L.buckets, SS_SORT, 0, s>>>(key_b, val_b, key_a, val_a, n, sys_off, n_sys, L);
         };
-        if (wide) sys ? last(k_ss_sort<6144, true>) : last(k_ss_sort<7680, false>);
-        else sys ? last(k_ss_sort<4096, true>) : last(k_ss_sort<4096, false>);
+        if (plan.capacity > CAP_NARROW) sys ? last(k_ss_sort<CAP_WIDE_SYS, true>) : last(k_ss_sort<CAP_WIDE, false>);
+        else sys ? last(k_ss_sort<CAP_NARROW, true>) : last(k_ss_sort<CAP_NARROW, false>);
         return;
     }
     uint32_t nb = (n + RS_TILE - 1) / RS_TILE;
