@@ -318,9 +318,10 @@ bh_status bh_force_timing(bh_ctx *ctx, double *total_ms, int64_t *launches, int3
 /* Group-size and tile autotuner (the scheduling of Sec. 4.6 leaves the
  * group size free): for each candidate group size, regroup the current tree,
  * walk and evaluate forces, timing both with HIP events (FP32 without the
- * collision branch: once per force tile, 512 and 256 sources); keep the pair
- * with the smallest force time + walk time / rebuild_every (tile 256 only when
- * it wins by 2%), set n_group and
+ * collision branch: once per force tile, 512 and 256 sources, after an untimed
+ * evaluation; the group size takes 256 when its force time is 2% below that of
+ * 512); keep the group size with the smallest force time + walk time /
+ * rebuild_every, set n_group and
  * force_tile of the context's parameters to it and leave its lists in place.
  * Speed at the context's theta only: a larger group is also more accurate
  * at equal theta, which this call does not weigh.  Requires bh_build_tree.

@@ -14,6 +14,7 @@
 
 #include "bh.h"
 #include "bh_learned.hpp"
+#include "bh_tune.hpp"
 
 namespace {
 
@@ -1032,8 +1033,8 @@ bh_status bh_autotune(bh_ctx *c, const int32_t *cand, int32_t n_cand, int32_t re
     int best_g = cand[0], best_tile = c->P.force_tile;
     // the force kernel's tile (sources per LDS tile) is tried for each group
     // size where there is a choice: the FP32 gravity-only kernels
-    std::vector<int> tiles{c->P.force_tile == 256 ? 256 : 512};
-    if (c->P.precision == BH_FP32_REL && !(c->P.r_coll > 0.0)) tiles = {512, 256};
+    const bool tiles = c->P.precision == BH_FP32_REL && !(c->P.r_coll > 0.0);
+    const int tile0 = c->P.force_tile == 256 ? 256 : 512;
     for (int pass = 0; pass < 2; ++pass) {
         for (int k = 0; k < (pass == 0 ? n_cand : 1); ++k) {
             c->n_grp_used = pass == 0 ? cand[k] : best_g;
@@ -1050,23 +1051,27 @@ bh_status bh_autotune(bh_ctx *c, const int32_t *cand, int32_t n_cand, int32_t re
             }
             double ms[EV_N];
             STCHK(bh_stage_times(c, ms));
-            const double walk_ms = ms[EV_WALK];
-            // one evaluation before the timed ones: the first on new lists finds no
-            // sources in the caches, and would count against the tile tried first
-            refresh_state(c);
-            bhk::forces(c->d, c->n_groups, c->P.precision == BH_FP32_REL, false, c->n_cu, 0.0, s);
-            for (int tile : tiles) {
+            bhk::TuneTimes times{0.0, 0.0, ms[EV_WALK]};
+            if (tiles) {
+                // one evaluation before the timed ones: the first on new lists finds no
+                // sources in the caches, and would count against the tile tried first
+                refresh_state(c);
+                bhk::forces(c->d, c->n_groups, true, false, c->n_cu, 0.0, s);
+            }
+            for (int tile : {512, 256}) {
+                if (!tiles && tile != tile0) continue;
                 c->P.force_tile = tile;
                 refresh_state(c);
                 STCHK(run_forces(c, s, false));
                 STCHK(bh_stage_times(c, ms));
-                // the smaller tile wins by 2% or not at all: single timings differ by as much
-                const double t = (ms[EV_FORCE] + walk_ms / rebuild_every) * (tile == 256 && tiles.size() > 1 ? 1.02 : 1.0);
-                if (t < best) {
-                    best = t;
-                    best_g = cand[k];
-                    best_tile = tile;
-                }
+                (tile == 256 ? times.force256 : times.force512) = ms[EV_FORCE];
+            }
+            const int tile = tiles ? bhk::tune_tile(times) : tile0;
+            const double t = bhk::tune_cost(times, tile, rebuild_every);
+            if (t < best) {
+                best = t;
+                best_g = cand[k];
+                best_tile = tile;
             }
         }
     }
