@@ -165,6 +165,8 @@ T *P(DevBuf &b) {
 
 // bytes of n_sys + 1 particle offsets, padded for the pointers that follow them
 size_t off_bytes(int n_sys) { return ((size_t)(n_sys + 1) * sizeof(uint32_t) + 15) & ~(size_t)15; }
+// the systems' table: their offsets, their pointers, their root-box blocks' offsets
+size_t tab_bytes(int n_sys) { return 2 * off_bytes(n_sys) + n_sys * sizeof(SysPtr); }
 
 void refresh_state(bh_ctx *c) {
     DevState &d = c->d;
@@ -174,6 +176,7 @@ void refresh_state(bh_ctx *c) {
     d.sys_tab = reinterpret_cast<SysPtr *>(P<char>(c->sys_tab_b) + off_bytes(c->n_sys));
     d.box = P<double4>(c->box_b);
     d.box_part = P<double>(c->box_part_b);
+    d.box_off = reinterpret_cast<uint32_t *>(P<char>(c->sys_tab_b) + off_bytes(c->n_sys) + c->n_sys * sizeof(SysPtr));
     d.box_blocks = c->box_blocks;
     d.sys_m0 = P<double>(c->sys_m0_b);
     d.pos_in = P<double4>(c->pos_in);
@@ -327,7 +330,7 @@ bh_status ensure_systems(bh_ctx *c, int n_sys) {
     if ((uint32_t)n_sys <= c->sys_cap && c->h_systab) return BH_OK;
     uint32_t cap = std::max<uint32_t>(n_sys, 16);
     STCHK(wait_tables(c));
-    HIPCHK(c, grow(c->sys_tab_b, off_bytes(cap) + cap * sizeof(SysPtr)));
+    HIPCHK(c, grow(c->sys_tab_b, tab_bytes(cap)));
     HIPCHK(c, grow(c->acc_tab_b, cap * sizeof(bhk::AccPtr)));
     HIPCHK(c, grow(c->box_b, cap * sizeof(double4)));
     HIPCHK(c, grow(c->sys_m0_b, cap * sizeof(double)));
@@ -335,7 +338,7 @@ bh_status ensure_systems(bh_ctx *c, int n_sys) {
     if (c->h_acctab) (void)hipHostFree(c->h_acctab);
     c->h_systab = nullptr;
     c->h_acctab = nullptr;
-    HIPCHK(c, hipHostMalloc((void **)&c->h_systab, off_bytes(cap) + cap * sizeof(SysPtr)));
+    HIPCHK(c, hipHostMalloc((void **)&c->h_systab, tab_bytes(cap)));
     HIPCHK(c, hipHostMalloc((void **)&c->h_acctab, cap * sizeof(bhk::AccPtr)));
     c->sys_cap = cap;
     return BH_OK;
@@ -640,6 +643,8 @@ bh_status set_systems(bh_ctx *c, const bh_system *sys, int32_t n_sys, hipStream_
     c->n = (uint32_t)total;
     c->sys_off.assign(n_sys + 1, 0);
     SysPtr *tab = reinterpret_cast<SysPtr *>(c->h_systab + off_bytes(n_sys));
+    uint32_t *box_off = reinterpret_cast<uint32_t *>(tab + n_sys);
+    c->box_blocks = 0;
     for (int k = 0; k < n_sys; ++k) {
         c->sys_off[k + 1] = c->sys_off[k] + (uint32_t)sys[k].n;
         SysPtr &t = tab[k];
@@ -651,17 +656,16 @@ bh_status set_systems(bh_ctx *c, const bh_system *sys, int32_t n_sys, hipStream_
         t.vz = sys[k].vz;
         t.m = sys[k].m;
         t.n = sys[k].n;
+        box_off[k] = c->box_blocks;
+        c->box_blocks += box_blocks_of((uint64_t)sys[k].n);
     }
+    box_off[n_sys] = c->box_blocks;
     std::copy(c->sys_off.begin(), c->sys_off.end(), reinterpret_cast<uint32_t *>(c->h_systab));
-    HIPCHK(c, hipMemcpyAsync(c->sys_tab_b.p, c->h_systab, off_bytes(n_sys) + n_sys * sizeof(SysPtr),
-                             hipMemcpyHostToDevice, s));
+    HIPCHK(c, hipMemcpyAsync(c->sys_tab_b.p, c->h_systab, tab_bytes(n_sys), hipMemcpyHostToDevice, s));
     HIPCHK(c, hipEventRecord(c->tab_ev, s));
     c->tab_ev_pending = true;
-    // root-box partials: one system alone fills the chip, and the partials
-    // stay O(n / BOX_PER_BLOCK) however the particles split into systems
-    const uint64_t per = (total + (uint64_t)n_sys - 1) / (uint64_t)n_sys;
-    c->box_blocks = (uint32_t)std::min<uint64_t>(BOX_BLOCKS_MAX, std::max<uint64_t>(1, per / BOX_PER_BLOCK));
-    HIPCHK(c, grow(c->box_part_b, (size_t)n_sys * c->box_blocks * 8 * sizeof(double)));
+    // at most n_sys + n / BOX_PER_BLOCK partials, however the particles split into systems
+    HIPCHK(c, grow(c->box_part_b, (size_t)c->box_blocks * 8 * sizeof(double)));
     STCHK(ensure_particles(c, c->n));
     if (c->node_cap < c->n + (uint32_t)n_sys) STCHK(ensure_nodes(c, c->n + n_sys + 1024));
     if (!c->pc_pool.p) STCHK(ensure_pools(c, (uint64_t)c->n * 8 + 65536, (uint64_t)c->n * 2 + 65536));

@@ -94,17 +94,19 @@ __device__ __forceinline__ void tree_coords(const DevState &d, double4 p, double
 
 // ---------------------------------------------------------------- root box
 // LOAD: from the caller's arrays, which the same pass copies into the library's
-// records (a launch and 32 bytes per particle less than two passes).
+// records (a launch and 32 bytes per particle less than two passes).  Blocks are
+// numbered over all systems, as many each as its own size asks for.
 template <bool LOAD>
 __global__ void __launch_bounds__(TPB) k_box_partial(DevState d) {
-    const int s = blockIdx.y;
+    const int s = sys_of(d.box_off, d.n_sys, blockIdx.x);
     const uint32_t b0 = d.sys_off[s], b1 = d.sys_off[s + 1];
+    const uint32_t first = d.box_off[s], blocks = d.box_off[s + 1] - first;
     // per axis 0..2 the tree coordinates, axis 3 the mass
     double lo[4] = {INFINITY, INFINITY, INFINITY, INFINITY}, hi[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
     bool bad = false;
     SysPtr sp;
     if (LOAD) sp = d.sys_tab[s];
-    for (uint32_t i = b0 + blockIdx.x * TPB + threadIdx.x; i < b1; i += d.box_blocks * TPB) {
+    for (uint32_t i = b0 + (blockIdx.x - first) * TPB + threadIdx.x; i < b1; i += blocks * TPB) {
         double4 p;
         if (LOAD) {
             const uint32_t j = i - b0;
@@ -145,7 +147,7 @@ __global__ void __launch_bounds__(TPB) k_box_partial(DevState d) {
         int a = threadIdx.x;
         double v = red[0][a];
         for (int k = 1; k < TPB / 64; ++k) v = (a < 4) ? fmin(v, red[k][a]) : fmax(v, red[k][a]);
-        d.box_part[((size_t)s * d.box_blocks + blockIdx.x) * 8 + a] = v;
+        d.box_part[(size_t)blockIdx.x * 8 + a] = v;
     }
 }
 
@@ -157,8 +159,8 @@ __global__ void k_box_final(DevState d) {
         lo[a] = INFINITY;
         hi[a] = -INFINITY;
     }
-    for (uint32_t b = threadIdx.x; b < d.box_blocks; b += 64) {
-        const double *p = d.box_part + ((size_t)s * d.box_blocks + b) * 8;
+    for (uint32_t b = d.box_off[s] + threadIdx.x; b < d.box_off[s + 1]; b += 64) {
+        const double *p = d.box_part + (size_t)b * 8;
         for (int a = 0; a < 4; ++a) {
             lo[a] = fmin(lo[a], p[a]);
             hi[a] = fmax(hi[a], p[4 + a]);
@@ -893,9 +895,8 @@ __global__ void __launch_bounds__(TPB) k_group_box(DevState d) {
 namespace bhk {
 
 void root_box_keys(const DevState &d, bool load, hipStream_t s) {
-    const dim3 boxes(d.box_blocks, d.n_sys);
-    if (load) k_box_partial<true><<<boxes, TPB, 0, s>>>(d);
-    else k_box_partial<false><<<boxes, TPB, 0, s>>>(d);
+    if (load) k_box_partial<true><<<d.box_blocks, TPB, 0, s>>>(d);
+    else k_box_partial<false><<<d.box_blocks, TPB, 0, s>>>(d);
     k_box_final<<<d.n_sys, 64, 0, s>>>(d);
     if (sorts_small(d.n)) {
         k_keys<<<grid_for(d.n), TPB, 0, s>>>(d, d.key_tmp, d.val_tmp);
