@@ -565,9 +565,14 @@ bh_status walk_until_fits(bh_ctx *c, hipStream_t s) {
 bh_status run_forces(bh_ctx *c, hipStream_t s, bool pot, double kick_h = 0.0);
 
 bh_status order_lists(bh_ctx *c, hipStream_t s) {
-    const size_t need = bhk::max_items(c->n_groups, c->n) * sizeof(ForceItem);
-    if (need > c->force_items.bytes || !c->force_items.p) {
-        HIPCHK(c, grow(c->force_items, need + need / 4 + 4096));
+    // Room for every group count of these particles while that is up to ITEMS_ONCE
+    // items (84 MB), twice the need beyond: freeing the old records waits for the
+    // device, in the middle of an integration.
+    constexpr size_t ITEMS_ONCE = (size_t)1 << 20;
+    const size_t need = bhk::max_items(c->n_groups, c->n), most = bhk::max_items(c->n, c->n);
+    if (need * sizeof(ForceItem) > c->force_items.bytes || !c->force_items.p) {
+        const size_t items = std::min(most, std::max(2 * need, ITEMS_ONCE));
+        HIPCHK(c, grow(c->force_items, items * sizeof(ForceItem)));
         c->d.force_items = P<ForceItem>(c->force_items);
     }
     bhk::order_groups(c->d, c->n_groups, s);
