@@ -518,7 +518,7 @@ __global__ void __launch_bounds__(RANK_THREADS) k_sort_small(const uint64_t *key
 }
 
 // ---------------------------------------------------------------- sample sort
-// n pairs, B buckets (8..1024) of n / B pairs on average, cut by a sample of 8 or
+// n pairs, B buckets (8..1024) of n / B pairs on average, cut by a sample of 8 to
 // 16 pairs per bucket (sample_plan).  A bucket outgrows the LDS of its block only
 // where the sample happens to miss a stretch of its pairs (the plan states how
 // often) or in an input made to defeat it; such a bucket is sorted by its block

@@ -14,11 +14,14 @@ constexpr uint32_t BUCKETS_MAX = 1024;
 // memory, while the chip waits for it.  In randomly ordered input a bucket is
 // the sum of `per` gaps between sampled pairs, so its share of the n pairs is
 // Beta(per, buckets per + 1 - per) distributed and the expected number of
-// buckets above the capacity follows: 8 per bucket hold 4096 at n = 2^20 (four
-// times the average) but for 1e-4 of the sorts.  Above, the LDS of two blocks
-// per CU has room for 7680 pairs, 6144 with their systems, down to 2.4 times
-// the average: with 8 per bucket 0.05 and 1.3 buckets of a sort at SAMPLE_MAX
-// were larger, with 16 it is 3e-5 and 0.015.
+// buckets above the capacity follows.  Up to 2^20 pairs the capacity is 4096,
+// four times the average: 1e-4 of the sorts at 8 per bucket.  Above, the LDS of
+// two blocks per CU has room for 7680 pairs, 6144 with their systems, down to
+// 2.4 times the average: at 8 per bucket 0.05 and 1.3 buckets of a sort at
+// SAMPLE_MAX were larger.  More sampled pairs narrow the distribution, and their
+// ranking grows with the square (2.2e6 pairs of 64 systems: 54 us at 16 per
+// bucket), so as many are taken as the capacity asks for: 8 down to 3.5 times
+// the average (5e-3), 12 down to 2.8 times (5e-3), 16 below (0.015).
 struct SamplePlan {
     uint32_t buckets, per, capacity;
 };
@@ -26,10 +29,11 @@ struct SamplePlan {
 constexpr uint32_t CAP_NARROW = 4096, CAP_WIDE = 7680, CAP_WIDE_SYS = 6144;
 
 inline SamplePlan sample_plan(uint32_t n, bool several_systems) {
-    const uint32_t b = (n + 1023) / 1024;
-    const bool wide = n > (1u << 20);
-    return {b < 8 ? 8u : (b > BUCKETS_MAX ? BUCKETS_MAX : b), wide ? 16u : 8u,
-            !wide ? CAP_NARROW : several_systems ? CAP_WIDE_SYS : CAP_WIDE};
+    const uint32_t want = (n + 1023) / 1024;
+    const uint32_t buckets = want < 8 ? 8u : (want > BUCKETS_MAX ? BUCKETS_MAX : want);
+    const uint32_t capacity = n <= (1u << 20) ? CAP_NARROW : several_systems ? CAP_WIDE_SYS : CAP_WIDE;
+    const uint64_t room = 10ull * capacity * buckets;       // ten times capacity / average, times n
+    return {buckets, room >= 35ull * n ? 8u : room >= 28ull * n ? 12u : 16u, capacity};
 }
 
 }  // namespace bhk

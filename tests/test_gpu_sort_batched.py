@@ -14,10 +14,10 @@ pytestmark = pytest.mark.gpu
 
 
 def _missed(n, total, seed):
-    """n particles of total pairs: those at the places of a sample of 16 pairs in each of 1024 buckets form a
+    """n particles of total pairs: those at the places of a sample of 8 pairs in each of 1024 buckets form a
     ring, all others a clump that no splitter cuts."""
     s = inputs.ring(n, seed)
-    m = 1024 * 16
+    m = 1024 * 8
     j = np.arange(m, dtype=np.uint64)
     stretch = (total << 32) // m
     a, b = (j * stretch) >> np.uint64(32), ((j + 1) * stretch) >> np.uint64(32)
