@@ -748,8 +748,11 @@ __device__ void block_sort_memory(uint64_t *ka, uint32_t *va, uint64_t *kb, uint
 }
 
 // One block per bucket: from (kin, vin), where the scatter put it, to (kout, vout).
+// Two blocks per CU, by LDS and by a cap of 128 VGPRs: without it three of the four
+// instances took 129 to 153, room for one (2.2e6 pairs of 64 systems 0.63 -> 0.60 ms
+// for keys, sort and permutation, 2.6e6 of one 0.79 -> 0.75).
 template <int CAP, bool SYS>
-__global__ void __launch_bounds__(SS_SORT) k_ss_sort(uint64_t *kin, uint32_t *vin, uint64_t *kout, uint32_t *vout,
+__global__ void __launch_bounds__(SS_SORT, 4) k_ss_sort(uint64_t *kin, uint32_t *vin, uint64_t *kout, uint32_t *vout,
                                                        uint32_t n, const uint32_t *sys_off, int n_sys,
                                                        SampleLayout s) {
     __shared__ BlockSortLds<SS_SORT, CAP, SYS> L;

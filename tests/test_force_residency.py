@@ -2,7 +2,7 @@
 library's own kernel descriptors).  A block's first work item is the one of its
 number, so a launch must not start more blocks than the registers and LDS of
 its kernel leave room for: 6 per CU in FP32, 5 in FP64, 3 in FP64 with the
-collision branch.  gfx950: 512 VGPRs per lane and SIMD in units of 8, 160 KB of
+collision branch.  The same for the two blocks of the bucket sort.  gfx950: 512 VGPRs per lane and SIMD in units of 8, 160 KB of
 LDS per CU, a block of 256 threads puts one wave on each SIMD."""
 import os
 import re
@@ -47,20 +47,37 @@ def _kernels(elf):
             p += (descsz + 3) // 4 * 4
 
 
-def test_every_launched_block_is_resident():
+def _built(pattern):
+    """The library's kernels whose name matches, by the match's groups."""
     if not os.path.exists(LIB):
         from paper_1907_02289_amd import build
         build.build()
-    data = open(LIB, "rb").read()
     found = {}
-    for elf in _code_objects(data):
+    for elf in _code_objects(open(LIB, "rb").read()):
         for k in _kernels(elf):
-            m = re.search(r"k_forceI([fd])Lb([01])ELb([01])ELb([01])ELi(\d+)E", k[".name"])
+            m = re.search(pattern, k[".name"])
             if m:
                 found[m.groups()] = k
+    return found
+
+
+def _resident(k, waves_per_simd):
+    """Blocks of a kernel that fit a CU, with that many of a block's waves on each SIMD."""
+    vgprs = (k[".vgpr_count"] + 7) // 8 * 8
+    return min(512 // vgprs // waves_per_simd, 160 * 1024 // k[".group_segment_fixed_size"])
+
+
+def test_every_launched_block_is_resident():
+    found = _built(r"k_forceI([fd])Lb([01])ELb([01])ELb([01])ELi(\d+)E")
     assert len(found) == 4 * (2 + 1) + 4 * 2          # FP32 tiles 512 and 256 and collisions, FP64 and collisions
-    for (real, _, _, coll, tile), k in found.items():
+    for (real, _, _, coll, _), k in found.items():
         want = 6 if real == "f" else 3 if coll == "1" else 5
-        vgprs = (k[".vgpr_count"] + 7) // 8 * 8
-        lds = k[".group_segment_fixed_size"]
-        assert min(512 // vgprs, 160 * 1024 // lds) >= want, (k[".name"], vgprs, lds)
+        assert _resident(k, 1) >= want, (k[".name"], k[".vgpr_count"], k[".group_segment_fixed_size"])
+
+
+def test_two_blocks_of_the_bucket_sort_fit_a_cu():
+    """The sample sort's bucket capacities are chosen for two blocks (of 512 threads) per CU."""
+    found = _built(r"k_ss_sortILi(\d+)ELb([01])E")
+    assert len(found) == 4
+    for k in found.values():
+        assert _resident(k, 2) >= 2, (k[".name"], k[".vgpr_count"], k[".group_segment_fixed_size"])
