@@ -411,7 +411,9 @@ __device__ __forceinline__ ForceItem uniform_item(const ForceItem *p) {
 // begin it when the others have emptied the queue).
 // FP32: 6 (24 waves); the pair loop needs them to hide LDS and rsqrt latency
 // (measured: 100 VGPRs / 4 waves per SIMD ran 18% slower; the collision
-// variant, at 5 without spills, ran 3% slower than at 6 with some 40 spilled).
+// variant, at 5 without spills, ran 3% slower than at 6 with some 40 spilled;
+// in the gravity-only one pair_loop's named registers push 29 out, saved around
+// the tiles: 0.6 of the 1.8 GB that a launch on 2^24 particles writes).
 // FP64 gravity-only: 5 (<= 96 VGPRs, no spills); with the collision branch 3
 // (141 VGPRs; uncapped, the variant with potentials took 169 and held 2 of the
 // 3: 130003 particles in 3084 groups 0.178 -> 0.128 ms per evaluation, 2^20 in

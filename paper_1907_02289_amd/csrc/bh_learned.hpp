@@ -111,7 +111,7 @@ __device__ __forceinline__ double accept_below(const PairGeom &p, double M, doub
 // register 4 q + i, and v_permlane32_swap of registers with neighbouring units
 // gives the next layer's B operands, units in order.  One lane per input with
 // the weights from memory was bound by them: some 340 loads per 64 nodes of a walk,
-// 72% of the waves' time spent waiting.  Walk of 2^19 particles: 1581 -> 477
+// 72% of the waves' time spent waiting.  Walk of 2^19 particles: 1581 -> 455
 // us in 1914 groups; whole steps 33.6 -> 13.4 ms with groups of up to 64, 47.7
 // -> 25.6 ms at 2^21 particles.
 struct WaveNet {

@@ -16,7 +16,7 @@
 //     LDS and then writes each digit's run to consecutive addresses.
 // Below SAMPLE_MAX the radix passes are bound by their 40 launches (27 us a
 // pass at 2^20 keys, 17 at 4096): 63-bit keys took 180 us of launches at 4096,
-// 190 at 2e5, 270 at 2^20 and 330 at 2e6; now 13, 85, 110 and 190.
+// 190 at 2e5, 270 at 2^20 and 330 at 2e6; now 10, 80, 100 and 185.
 #include <type_traits>
 
 #include "bh_internal.hpp"

@@ -1,5 +1,5 @@
 // bh_tree.hip -- tree construction, Iwasawa et al. (2019) Sec. 4.2 step (3a):
-// root box and keys, sort and permutation, level-synchronous octree,
+// root box and keys, sort and permutation, octree (all levels at once),
 // monopole moments (Sec. 5.1: nodes act through their centre of mass),
 // and the particle groups of step (3d) taken from the tree itself.
 //

@@ -138,11 +138,11 @@ __host__ __device__ inline uint32_t walk_share(uint32_t rounds) {
 // Runs of 4 rounds take the same time, runs of 32 up to 5% more.
 // The next 64 nodes are loaded before the current 64 are tested; a leaf's
 // particle count rides in the node record, so a visit is one 16-byte load.
-// Kernel time before and after: 172 groups (4096-particle ring) 105 -> 15 us,
-// 9,311 groups (200k, theta 0.2) 560 -> 81 us, 15,739 groups (2^20, theta 0.5)
-// 863 -> 100 us, 64 Plummer spheres 878 -> 230 us; with 60,426 groups of
+// Kernel time with the counter per group and now: 172 groups (4096-particle ring)
+// 105 -> 14 us, 9,311 groups (200k, theta 0.2) 560 -> 78 us, 15,739 groups (2^20,
+// theta 0.5) 863 -> 89 us, 64 Plummer spheres 878 -> 200 us; with 60,447 groups of
 // 10^4-entry lists (2^24, theta 0.0865) the visits themselves take the time,
-// 5.2 -> 4.9 ms.
+// 6.0 -> 5.7 ms (stage, one card in turn).
 // GEO: the instance of the geometric rule, without the registers of the
 // network.  The other one has 227 (two waves per SIMD, as many as are launched):
 // held to 168 or 128 its walks took 3% and 10% longer.
