@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -309,7 +310,8 @@ bh_status wait_tables(bh_ctx *c) {
 }
 
 bh_status read_counters(bh_ctx *c, hipStream_t s) {
-    HIPCHK(c, hipMemcpyAsync(c->h_cnt, c->counters.p, sizeof(DevCounters), hipMemcpyDeviceToHost, s));
+    // all but the walk's rounds, which the host does not read
+    HIPCHK(c, hipMemcpyAsync(c->h_cnt, c->counters.p, offsetof(DevCounters, walk_round), hipMemcpyDeviceToHost, s));
     HIPCHK(c, hipStreamSynchronize(s));
     c->host_syncs += 1;
     return BH_OK;

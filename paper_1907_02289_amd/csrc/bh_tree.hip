@@ -93,6 +93,12 @@ __device__ __forceinline__ void tree_coords(const DevState &d, double4 p, double
 }
 
 // ---------------------------------------------------------------- root box
+// Blocks [first, end) of system s; one system alone has them all, without a load.
+__device__ __forceinline__ void box_span(const DevState &d, int s, uint32_t &first, uint32_t &end) {
+    first = d.n_sys == 1 ? 0u : d.box_off[s];
+    end = d.n_sys == 1 ? d.box_blocks : d.box_off[s + 1];
+}
+
 // LOAD: from the caller's arrays, which the same pass copies into the library's
 // records (a launch and 32 bytes per particle less than two passes).  Blocks are
 // numbered over all systems, as many each as its own size asks for.
@@ -100,13 +106,14 @@ template <bool LOAD>
 __global__ void __launch_bounds__(TPB) k_box_partial(DevState d) {
     const int s = sys_of(d.box_off, d.n_sys, blockIdx.x);
     const uint32_t b0 = d.sys_off[s], b1 = d.sys_off[s + 1];
-    const uint32_t first = d.box_off[s], blocks = d.box_off[s + 1] - first;
+    uint32_t first, end;
+    box_span(d, s, first, end);
     // per axis 0..2 the tree coordinates, axis 3 the mass
     double lo[4] = {INFINITY, INFINITY, INFINITY, INFINITY}, hi[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
     bool bad = false;
     SysPtr sp;
     if (LOAD) sp = d.sys_tab[s];
-    for (uint32_t i = b0 + (blockIdx.x - first) * TPB + threadIdx.x; i < b1; i += blocks * TPB) {
+    for (uint32_t i = b0 + (blockIdx.x - first) * TPB + threadIdx.x; i < b1; i += (end - first) * TPB) {
         double4 p;
         if (LOAD) {
             const uint32_t j = i - b0;
@@ -159,7 +166,9 @@ __global__ void k_box_final(DevState d) {
         lo[a] = INFINITY;
         hi[a] = -INFINITY;
     }
-    for (uint32_t b = d.box_off[s] + threadIdx.x; b < d.box_off[s + 1]; b += 64) {
+    uint32_t first, end;
+    box_span(d, s, first, end);
+    for (uint32_t b = first + threadIdx.x; b < end; b += 64) {
         const double *p = d.box_part + (size_t)b * 8;
         for (int a = 0; a < 4; ++a) {
             lo[a] = fmin(lo[a], p[a]);
